@@ -387,7 +387,7 @@ def work(case):
         row = (8 if c["key64"] else 4) + (8 if c["val64"] else 4)
         return {"bytes": row * c["rows"] + 16 * _groups(c["rows"], c["groups"]), "flops": 0}
     g = _groups(c["rows"] * live, 0.2 * c["build"])
-    return {"bytes": 20 * c["rows"] + 16 * c["build"] + 16 * g, "flops": 0}  # four of the five columns are needed
+    return {"bytes": 16 * c["rows"] + 16 * c["build"] + 16 * g, "flops": 0}  # three of the five columns are needed
 
 
 # ------------------------------------------------------------------ the same in plain torch
