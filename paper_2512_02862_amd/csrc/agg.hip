@@ -29,6 +29,55 @@ constexpr uint64_t kAggSeed = 0xd6e8feb86659fd93ull;
 
 __device__ __forceinline__ uint64_t agg_hash(int64_t key) { return fmix64(static_cast<uint64_t>(key) ^ kAggSeed); }
 
+// ---------------------------------------------------------------- plan by key range
+// A pass over the keys finds their least and greatest value (k_key_range), and
+// one block chooses from them how the rows are grouped (k_gb_plan), on the
+// device, so nothing is read back:
+//   kGbSmall  the keys span at most `small_max` (<= 8192) values: every block
+//             adds its rows up in an LDS array indexed by key - kmin and a
+//             second kernel adds the blocks' arrays up: the rows are read once
+//             more and never moved.  The rule is the LDS: 8192 sums and flags
+//             are 72 KiB, two 1024-thread blocks per CU.
+//   kGbRange  they span at most 4096 buckets of 8192 values, and a sample finds
+//             no crowded bucket or part: the moves split the rows by (key -
+//             kmin) >> shift instead of by hash bits, so that a bucket's LDS
+//             array is indexed directly (no probing, no compare-and-swap) and
+//             the groups come out in key order (no sort).
+//   kGbHash   otherwise: hash buckets, each summed in an LDS hash table.
+//   kGbTable  the same where hash buckets have no memory or too many groups: the
+//             table in HBM (k_gb_insert).
+// Measured at 60M rows, start to end, ordered by key: 2407 int32 keys with int64
+// values 1953 -> 362 us (kGbSmall: 138 us for the sums, 5.2 TB/s; hash buckets
+// left 2407 busy blocks of uneven size), 15M int32 keys with int32 values 2232
+// -> 1632 us (kGbRange: 193 us for the bucket sums against 376 with hash tables,
+// and nothing left to sort).  The range costs 60 - 68 us there.
+constexpr int kDirectSlotsLg = 13;
+constexpr int kDirectSlots = 1 << kDirectSlotsLg;  // LDS sums of one direct-addressed table
+constexpr int kSamples = 16384;
+
+__device__ __forceinline__ bool plan_moves(const GbPlan *p) { return !p || p->mode == kGbHash || p->mode == kGbRange; }
+
+// Bucket of a key for both moves: 12 bits, the first move takes the upper 6.
+// (Wave-uniform choice; kernels that never see a plan compile it out.)
+struct BucketFn {
+  int64_t kmin = 0;
+  int32_t shift = 0;
+  bool ranged = false;
+  __device__ __forceinline__ explicit BucketFn(const GbPlan *p) {
+    if (p && p->mode == kGbRange) {
+      ranged = true;
+      kmin = p->kmin;
+      shift = p->shift;
+    }
+  }
+  __device__ __forceinline__ uint32_t of_range(int64_t key) const {
+    return static_cast<uint32_t>((static_cast<uint64_t>(key) - static_cast<uint64_t>(kmin)) >> shift);
+  }
+  __device__ __forceinline__ uint32_t wide(int64_t key) const {
+    return ranged ? of_range(key) : static_cast<uint32_t>(agg_hash(key) >> (64 - 2 * kRadixLg));
+  }
+};
+
 // The rows a block of a move reads: with b = xcd_block(blockIdx.x), segment b / bps of the input
 // (segment s is [seg_off[s * seg_stride], seg_off[(s + 1) * seg_stride]), or the
 // whole input [0, min(*count, cap)) without seg_off), split evenly into bps parts.
@@ -40,7 +89,7 @@ struct MoveArgs {
   const int32_t *seg_off;
   int seg_stride;
   int bps;
-  int shift;  // bucket = (hash >> shift) & (kRadix - 1)
+  int sub;  // destination = (bucket >> sub) & (kRadix - 1)
   // With `aligned`, block part of segment seg reads the rows that the first
   // move's blocks [part * G, (part + 1) * G) wrote to it, G = seg_stride / bps
   // (their counts are known from the first pass), instead of an even split.
@@ -53,6 +102,7 @@ struct MoveArgs {
   const int32_t *sel = nullptr;
   int k64 = 0, v64 = 0;
   uint32_t *err = nullptr;
+  GbPlan *plan = nullptr;  // null: hash buckets
 };
 
 __device__ __forceinline__ int64_t move_key(const MoveArgs &m, int64_t i) {
@@ -94,8 +144,11 @@ constexpr int kMoveItems = 8;
 // (top 12 bits of the hash: the first move's 6 and the second's 6), from
 // which both moves' positions follow (k_narrow_counts), so the second move
 // needs no counting pass of its own.
+template <bool PLANNED>
 __global__ __launch_bounds__(kAggBlock) void k_move_hist_both(MoveArgs m, int32_t *counts) {
   __shared__ int32_t s_c[kAggBuckets];
+  if (PLANNED && !plan_moves(m.plan)) return;
+  const BucketFn bucket(PLANNED ? m.plan : nullptr);
   for (int i = threadIdx.x; i < kAggBuckets; i += kAggBlock) s_c[i] = 0;
   __syncthreads();
   int seg, part;
@@ -111,7 +164,7 @@ __global__ __launch_bounds__(kAggBlock) void k_move_hist_both(MoveArgs m, int32_
     }
 #pragma unroll
     for (int u = 0; u < kMoveItems; ++u)
-      if (k[u] != kEmpty64) atomicAdd(&s_c[agg_hash(k[u]) >> (64 - 2 * kRadixLg)], 1);
+      if (k[u] != kEmpty64) atomicAdd(&s_c[bucket.wide(k[u])], 1);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < kAggBuckets; i += kAggBlock) counts[(int64_t{seg} * m.bps + part) * kAggBuckets + i] = s_c[i];
@@ -126,12 +179,15 @@ __global__ __launch_bounds__(kAggBlock) void k_move_hist_both(MoveArgs m, int32_
 constexpr int kMoveTileItems = 4;
 static_assert(kRadix == kWave, "one wave scans the bucket counts");
 constexpr int kMoveTile = kAggBlock * kMoveTileItems;
+template <bool PLANNED>
 __global__ __launch_bounds__(kAggBlock) void k_move_scatter(MoveArgs m, const int32_t *pos, int64_t *okeys,
                                                            int64_t *ovals) {
   __shared__ int64_t s_k[kMoveTile];
   __shared__ int64_t s_v[kMoveTile];
   __shared__ uint8_t s_b[kMoveTile];
   __shared__ int32_t s_base[kRadix], s_cnt[kRadix], s_off[kRadix + 1];
+  if (PLANNED && !plan_moves(m.plan)) return;
+  const BucketFn bucket(PLANNED ? m.plan : nullptr);
   int seg, part;
   int64_t lo, hi;
   move_range(m, &seg, &part, &lo, &hi);
@@ -150,7 +206,7 @@ __global__ __launch_bounds__(kAggBlock) void k_move_scatter(MoveArgs m, const in
     }
 #pragma unroll
     for (int u = 0; u < kMoveTileItems; ++u) {
-      bk[u] = k[u] != kEmpty64 ? static_cast<int>((agg_hash(k[u]) >> m.shift) & (kRadix - 1)) : -1;
+      bk[u] = k[u] != kEmpty64 ? static_cast<int>((bucket.wide(k[u]) >> m.sub) & (kRadix - 1)) : -1;
       rk[u] = bk[u] >= 0 ? atomicAdd(&s_cnt[bk[u]], 1) : 0;
     }
     __syncthreads();
@@ -191,7 +247,8 @@ __global__ __launch_bounds__(kAggBlock) void k_move_scatter(MoveArgs m, const in
 __global__ __launch_bounds__(kAggBlock) void k_bucket_groups(const int64_t *keys, const int64_t *vals,
                                                             const int32_t *pos, int bps, int64_t *out_keys,
                                                             int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups,
-                                                            uint32_t *err) {
+                                                            uint32_t *err, const GbPlan *plan) {
+  if (plan && plan->mode != kGbHash) return;
   __shared__ uint64_t s_key[kAggSlots];
   __shared__ uint64_t s_sum[kAggSlots];
   __shared__ int32_t s_w[kAggBlock / kWave];
@@ -292,53 +349,67 @@ __global__ __launch_bounds__(kAggBlock) void k_bucket_groups(const int64_t *keys
 // error is latched.
 // The moves and the bucket pass; the first move reads `first` (pairs or columns),
 // the second writes keys/vals (cap entries each).
-__global__ void k_narrow_counts(const int32_t *counts, int32_t *c1, int32_t *c2);
+// With first.plan, `status` holds kAggBuckets look-back words (cleared by k_gb_plan).
+__global__ void k_narrow_counts(const int32_t *counts, int32_t *c1, int32_t *c2, const GbPlan *plan);
+__global__ void k_move_positions(const int32_t *c1, int32_t *p1, const int32_t *c2, int32_t *p2, const GbPlan *plan);
+template <bool NARROW>
+pyst_status launch_direct_groups(pyst_ctx *ctx, GbPlan *plan, uint64_t *status, const void *pairs, const int64_t *vals,
+                                 const int32_t *pos, int bps, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
+                                 int64_t *d_ngroups, hipStream_t stream);
+
+// Scratch of the wide moves: the counts, then the first move's pairs.
+static size_t wide_count_bytes() {
+  const int64_t n1 = int64_t{kRadix} * kAggBlocks1, n2 = int64_t{kAggBuckets} * kAggBlocks2;
+  return ((static_cast<size_t>(kAggBlocks1) * kAggBuckets + static_cast<size_t>(n1 + 1 + n2 + 1) * 2) * sizeof(int32_t) +
+          255) / 256 * 256;
+}
+static size_t wide_groupby_bytes(int64_t cap) { return wide_count_bytes() + static_cast<size_t>(cap) * 16; }
 
 pyst_status pair_groupby_from(pyst_ctx *ctx, MoveArgs first, int64_t *keys, int64_t *vals, const int64_t *count,
                               int64_t cap, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
-                              int64_t *d_ngroups, hipStream_t stream) {
+                              int64_t *d_ngroups, uint64_t *status, void *ws, hipStream_t stream) {
   if (cap >= (int64_t{1} << 31)) return set_error(PYST_ERR_ARG, "group-by: too many pairs");
   const int64_t n1 = int64_t{kRadix} * kAggBlocks1, n2 = int64_t{kAggBuckets} * kAggBlocks2;
-  const size_t counts = (static_cast<size_t>(kAggBlocks1) * kAggBuckets + static_cast<size_t>(n1 + 1 + n2 + 1) * 2) *
-                        sizeof(int32_t);
-  Scratch sc(ctx, (counts + 255) / 256 * 256 + static_cast<size_t>(cap) * 16, stream);
-  if (!sc.p) return set_error(PYST_ERR_NOMEM, "group-by: arena exhausted");
-  int32_t *cnt = sc.as<int32_t>();
+  const size_t counts = wide_count_bytes();
+  int32_t *cnt = static_cast<int32_t *>(ws);
   int32_t *h1 = cnt + static_cast<int64_t>(kAggBlocks1) * kAggBuckets, *p1 = h1 + n1 + 1, *h2 = p1 + n1 + 1,
           *p2 = h2 + n2 + 1;
-  int64_t *tk = reinterpret_cast<int64_t *>(static_cast<char *>(sc.p) + (counts + 255) / 256 * 256);
+  int64_t *tk = reinterpret_cast<int64_t *>(static_cast<char *>(ws) + counts);
   int64_t *tv = tk + cap;
   // One counting pass over all pairs gives every first-move block's counts
   // per final bucket; the first move's positions are per part (hash bits
   // 58..63), the second's per bucket (bits 52..57) and second-move block.
-  // The scans run over one more entry than the counts (zero), so that the
-  // last offset is the total.
   MoveArgs m1 = first;
   m1.count = count;
   m1.cap = cap;
   m1.seg_off = nullptr;
   m1.seg_stride = 0;
   m1.bps = kAggBlocks1;
-  m1.shift = 64 - kRadixLg;
-  k_move_hist_both<<<kAggBlocks1, kAggBlock, 0, stream>>>(m1, cnt);
+  m1.sub = kRadixLg;
+  first.plan ? k_move_hist_both<true><<<kAggBlocks1, kAggBlock, 0, stream>>>(m1, cnt)
+             : k_move_hist_both<false><<<kAggBlocks1, kAggBlock, 0, stream>>>(m1, cnt);
   PYST_LAUNCH_CHECK("k_move_hist_both");
-  k_narrow_counts<<<static_cast<unsigned>(ceil_div(n1 + n2 + 1, 256)), 256, 0, stream>>>(cnt, h1, h2);
+  k_narrow_counts<<<static_cast<unsigned>(ceil_div(n1 + n2 + 1, 256)), 256, 0, stream>>>(cnt, h1, h2, first.plan);
   PYST_LAUNCH_CHECK("k_narrow_counts");
-  pyst_status st = scan_excl_i32(ctx, h1, p1, n1 + 1, nullptr, stream);
-  if (st == PYST_OK) st = scan_excl_i32(ctx, h2, p2, n2 + 1, nullptr, stream);
-  if (st != PYST_OK) return st;
-  k_move_scatter<<<kAggBlocks1, kAggBlock, 0, stream>>>(m1, p1, tk, tv);
+  k_move_positions<<<2, kAggBlock, 0, stream>>>(h1, p1, h2, p2, first.plan);
+  PYST_LAUNCH_CHECK("k_move_positions");
+  first.plan ? k_move_scatter<true><<<kAggBlocks1, kAggBlock, 0, stream>>>(m1, p1, tk, tv)
+             : k_move_scatter<false><<<kAggBlocks1, kAggBlock, 0, stream>>>(m1, p1, tk, tv);
   PYST_LAUNCH_CHECK("k_move_scatter");
   // Second move: block j of part p reads what the first move's blocks
   // [64 j, 64 (j + 1)) wrote to part p, and writes it by bucket into keys/vals.
-  MoveArgs m2{tk, tv, count, cap, p1, kAggBlocks1, kAggBlocks2, 64 - 2 * kRadixLg};
+  MoveArgs m2{tk, tv, count, cap, p1, kAggBlocks1, kAggBlocks2, 0};
   m2.aligned = 1;
-  k_move_scatter<<<kRadix * kAggBlocks2, kAggBlock, 0, stream>>>(m2, p2, keys, vals);
+  m2.plan = first.plan;
+  first.plan ? k_move_scatter<true><<<kRadix * kAggBlocks2, kAggBlock, 0, stream>>>(m2, p2, keys, vals)
+             : k_move_scatter<false><<<kRadix * kAggBlocks2, kAggBlock, 0, stream>>>(m2, p2, keys, vals);
   PYST_LAUNCH_CHECK("k_move_scatter");
   const int gblocks = static_cast<int>(std::min<int64_t>(kAggBuckets, std::max(1, ctx_num_cus(ctx))));
   k_bucket_groups<<<gblocks, kAggBlock, 0, stream>>>(keys, vals, p2, kAggBlocks2, out_keys, out_sums, out_cap,
-                                                     d_ngroups, ctx_err_word(ctx));
+                                                     d_ngroups, ctx_err_word(ctx), first.plan);
   PYST_LAUNCH_CHECK("k_bucket_groups");
+  if (first.plan) return launch_direct_groups<false>(ctx, first.plan, status, keys, vals, p2, kAggBlocks2, out_keys,
+                                                     out_sums, out_cap, d_ngroups, stream);
   return PYST_OK;
 }
 
@@ -368,7 +439,12 @@ struct NarrowArgs {
   const int32_t *sel;    // nullptr: rows 0..count-1
   const int64_t *count;  // rows (or selected rows) to group
   int64_t cap;           // upper bound of *count
+  GbPlan *plan;          // null: hash buckets
 };
+
+__device__ __forceinline__ uint32_t narrow_bucket(const BucketFn &f, int32_t key) {
+  return f.ranged ? f.of_range(key) : narrow_hash(key) >> 20;
+}
 
 __device__ __forceinline__ void narrow_range(const NarrowArgs &a, int blk, int nblk, int64_t *lo, int64_t *hi) {
   const int64_t n = *a.count < a.cap ? *a.count : a.cap;
@@ -380,6 +456,8 @@ __device__ __forceinline__ void narrow_range(const NarrowArgs &a, int blk, int n
 // Per first-move block: counts of its rows in each of the 4096 buckets.
 __global__ __launch_bounds__(kAggBlock) void k_narrow_hist(NarrowArgs a, int32_t *counts) {
   __shared__ int32_t s_c[kAggBuckets];
+  if (!plan_moves(a.plan)) return;
+  const BucketFn bucket(a.plan);
   for (int i = threadIdx.x; i < kAggBuckets; i += kAggBlock) s_c[i] = 0;
   __syncthreads();
   int64_t lo, hi;
@@ -394,16 +472,16 @@ __global__ __launch_bounds__(kAggBlock) void k_narrow_hist(NarrowArgs a, int32_t
     }
 #pragma unroll
     for (int u = 0; u < kNItems; ++u)
-      if (i0 + int64_t{u} * kAggBlock < hi) atomicAdd(&s_c[narrow_hash(k[u]) >> 20], 1);
+      if (i0 + int64_t{u} * kAggBlock < hi) atomicAdd(&s_c[narrow_bucket(bucket, k[u])], 1);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < kAggBuckets; i += kAggBlock) counts[int64_t{blk} * kAggBuckets + i] = s_c[i];
 }
 
 // c1[p * kNB1 + b]: rows of first-move block b in part p; c2[(p * 64 + q) * kNB2
-// + j]: rows of bucket (p, q) that second-move block j of part p moves.  The
-// entry after each array is zero so that its exclusive scan ends in the total.
-__global__ void k_narrow_counts(const int32_t *counts, int32_t *c1, int32_t *c2) {
+// + j]: rows of bucket (p, q) that second-move block j of part p moves.
+__global__ void k_narrow_counts(const int32_t *counts, int32_t *c1, int32_t *c2, const GbPlan *plan) {
+  if (!plan_moves(plan)) return;
   const int64_t t = blockIdx.x * int64_t{blockDim.x} + threadIdx.x;
   constexpr int64_t n1 = int64_t{kRadix} * kNB1, n2 = int64_t{kAggBuckets} * kNB2;
   if (t < n1) {
@@ -417,9 +495,54 @@ __global__ void k_narrow_counts(const int32_t *counts, int32_t *c1, int32_t *c2)
     int32_t c = 0;
     for (int b = j * kNG; b < (j + 1) * kNG; ++b) c += counts[int64_t{b} * kAggBuckets + bucket];
     c2[u] = c;
-  } else if (t == n1 + n2) {
-    c1[n1] = 0;
-    c2[n2] = 0;
+  }
+}
+
+// Exclusive scans of both count arrays, one block each; the entry after the
+// last is the total.  Every thread holds its 32 counts in registers (eight
+// 16-byte loads, tile by tile), so a scan is one memory round trip: 6 us where
+// two look-back scans with their cleared status words took 20.
+constexpr int kPosLen = kRadix * kNB1;  // entries of c1, and of c2
+constexpr int kPosTiles = kPosLen / (4 * kAggBlock);
+static_assert(kPosLen == kAggBuckets * kNB2 && kPosLen % (4 * kAggBlock) == 0, "both arrays are whole tiles");
+__global__ __launch_bounds__(kAggBlock) void k_move_positions(const int32_t *c1, int32_t *p1, const int32_t *c2,
+                                                             int32_t *p2, const GbPlan *plan) {
+  constexpr int NW = kAggBlock / kWave;
+  __shared__ int32_t s_w[kPosTiles * NW];  // per (tile, wave) sums, then their exclusive prefix
+  if (!plan_moves(plan)) return;
+  const int32_t *in = blockIdx.x ? c2 : c1;
+  int32_t *out = blockIdx.x ? p2 : p1;
+  const int tid = static_cast<int>(threadIdx.x), w = tid / kWave, lane = lane_id();
+  int32_t v[kPosTiles][4], excl[kPosTiles];
+#pragma unroll
+  for (int q = 0; q < kPosTiles; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[q][j] = in[q * 4 * kAggBlock + tid * 4 + j];
+#pragma unroll
+  for (int q = 0; q < kPosTiles; ++q) {
+    const int32_t sum = v[q][0] + v[q][1] + v[q][2] + v[q][3];
+    const int32_t incl = wave_inclusive_scan(sum);
+    excl[q] = incl - sum;
+    if (lane == kWave - 1) s_w[q * NW + w] = incl;
+  }
+  __syncthreads();
+  if (w == 0) {  // kPosTiles * NW = 128 partial sums, two a lane
+    static_assert(kPosTiles * NW == 2 * kWave, "two partial sums a lane");
+    const int32_t a = s_w[2 * lane], b = s_w[2 * lane + 1];
+    const int32_t incl = wave_inclusive_scan(a + b);
+    s_w[2 * lane] = incl - a - b;
+    s_w[2 * lane + 1] = incl - b;
+    if (lane == kWave - 1) out[kPosLen] = incl;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kPosTiles; ++q) {
+    int32_t run = s_w[q * NW + w] + excl[q];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      out[q * 4 * kAggBlock + tid * 4 + j] = run;
+      run += v[q][j];
+    }
   }
 }
 
@@ -434,6 +557,8 @@ __global__ __launch_bounds__(kAggBlock) void k_narrow_move(NarrowArgs a, const u
   __shared__ uint64_t s_p[kMoveTile];
   __shared__ uint8_t s_b[kMoveTile];
   __shared__ int32_t s_base[kRadix], s_cnt[kRadix], s_off[kRadix + 1];
+  if (!plan_moves(a.plan)) return;
+  const BucketFn bucket(a.plan);
   const int tid = static_cast<int>(threadIdx.x);
   int64_t lo, hi;
   int part = 0;
@@ -448,7 +573,7 @@ __global__ __launch_bounds__(kAggBlock) void k_narrow_move(NarrowArgs a, const u
     hi = pos1[int64_t{part} * kNB1 + (j + 1) * kNG];
     if (tid < kRadix) s_base[tid] = pos2[(int64_t{part} * kRadix + tid) * kNB2 + j];
   }
-  const int shift = FIRST ? 26 : 20;
+  constexpr int sub = FIRST ? kRadixLg : 0;
   for (int64_t t0 = lo; t0 < hi; t0 += kMoveTile) {  // block-uniform
     if (tid < kRadix) s_cnt[tid] = 0;
     __syncthreads();
@@ -468,7 +593,8 @@ __global__ __launch_bounds__(kAggBlock) void k_narrow_move(NarrowArgs a, const u
 #pragma unroll
     for (int u = 0; u < kMoveTileItems; ++u) {
       const int64_t i = t0 + int64_t{u} * kAggBlock + tid;
-      bk[u] = i < hi ? static_cast<int>((narrow_hash(static_cast<int32_t>(pr[u] >> 32)) >> shift) & (kRadix - 1)) : -1;
+      bk[u] = i < hi ? static_cast<int>((narrow_bucket(bucket, static_cast<int32_t>(pr[u] >> 32)) >> sub) & (kRadix - 1))
+                     : -1;
       rk[u] = bk[u] >= 0 ? atomicAdd(&s_cnt[bk[u]], 1) : 0;
     }
     __syncthreads();
@@ -526,7 +652,8 @@ __device__ __forceinline__ uint32_t narrow_empty(int b) { return static_cast<uin
 
 __global__ __launch_bounds__(kAggBlock) void k_narrow_groups(const uint64_t *pairs, const int32_t *pos2,
                                                             int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
-                                                            int64_t *d_ngroups, uint32_t *err) {
+                                                            int64_t *d_ngroups, uint32_t *err, const GbPlan *plan) {
+  if (plan && plan->mode != kGbHash) return;
   __shared__ uint32_t s_h[kAggSlots];
   __shared__ uint64_t s_sum[kAggSlots];
   __shared__ int32_t s_w[kAggBlock / kWave];
@@ -660,7 +787,7 @@ size_t narrow_groupby_bytes(int64_t cap) {
 // *d_ngroups must be zero on entry.  Fewer than 2^31 rows.
 pyst_status narrow_groupby(pyst_ctx *ctx, const int32_t *kcol, const int32_t *vcol, const int32_t *sel,
                            const int64_t *count, int64_t cap, void *ws, int64_t *out_keys, int64_t *out_sums,
-                           int64_t out_cap, int64_t *d_ngroups, hipStream_t stream) {
+                           int64_t out_cap, int64_t *d_ngroups, GbPlan *plan, uint64_t *status, hipStream_t stream) {
   if (cap >= (int64_t{1} << 31)) return set_error(PYST_ERR_ARG, "group-by: too many rows");
   const int64_t n1 = int64_t{kRadix} * kNB1, n2 = int64_t{kAggBuckets} * kNB2;
   int32_t *counts = static_cast<int32_t *>(ws);
@@ -670,23 +797,24 @@ pyst_status narrow_groupby(pyst_ctx *ctx, const int32_t *kcol, const int32_t *vc
                         sizeof(int32_t);
   uint64_t *tmp = reinterpret_cast<uint64_t *>(static_cast<char *>(ws) + (cbytes + 255) / 256 * 256);
   uint64_t *pairs = tmp + cap;
-  NarrowArgs a{kcol, vcol, sel, count, cap};
+  NarrowArgs a{kcol, vcol, sel, count, cap, plan};
   k_narrow_hist<<<kNB1, kAggBlock, 0, stream>>>(a, counts);
   PYST_LAUNCH_CHECK("k_narrow_hist");
-  k_narrow_counts<<<static_cast<unsigned>(ceil_div(n1 + n2 + 1, 256)), 256, 0, stream>>>(counts, c1, c2);
+  k_narrow_counts<<<static_cast<unsigned>(ceil_div(n1 + n2 + 1, 256)), 256, 0, stream>>>(counts, c1, c2, plan);
   PYST_LAUNCH_CHECK("k_narrow_counts");
-  pyst_status st = scan_excl_i32(ctx, c1, p1, n1 + 1, nullptr, stream);
-  if (st == PYST_OK) st = scan_excl_i32(ctx, c2, p2, n2 + 1, nullptr, stream);
-  if (st != PYST_OK) return st;
+  k_move_positions<<<2, kAggBlock, 0, stream>>>(c1, p1, c2, p2, plan);
+  PYST_LAUNCH_CHECK("k_move_positions");
   k_narrow_move<true><<<kNB1, kAggBlock, 0, stream>>>(a, nullptr, p1, p2, tmp);
   PYST_LAUNCH_CHECK("k_narrow_move<1>");
   k_narrow_move<false><<<kRadix * kNB2, kAggBlock, 0, stream>>>(a, tmp, p1, p2, pairs);
   PYST_LAUNCH_CHECK("k_narrow_move<2>");
   const int gblocks = static_cast<int>(std::min<int64_t>(kAggBuckets, std::max(1, ctx_num_cus(ctx))));
   k_narrow_groups<<<gblocks, kAggBlock, 0, stream>>>(pairs, p2, out_keys, out_sums, out_cap, d_ngroups,
-                                                     ctx_err_word(ctx));
+                                                     ctx_err_word(ctx), plan);
   PYST_LAUNCH_CHECK("k_narrow_groups");
-  return PYST_OK;
+  if (!plan) return PYST_OK;
+  return launch_direct_groups<true>(ctx, plan, status, pairs, nullptr, p2, kNB2, out_keys, out_sums, out_cap, d_ngroups,
+                                    stream);
 }
 
 pyst_status pair_groupby(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const int64_t *count, int64_t cap,
@@ -695,23 +823,467 @@ pyst_status pair_groupby(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const int6
   MoveArgs first{};
   first.keys = keys;
   first.vals = vals;
-  return pair_groupby_from(ctx, first, keys, vals, count, cap, out_keys, out_sums, out_cap, d_ngroups, stream);
+  Scratch ws(ctx, wide_groupby_bytes(cap), stream);
+  if (!ws.p) return set_error(PYST_ERR_NOMEM, "group-by: arena exhausted");
+  return pair_groupby_from(ctx, first, keys, vals, count, cap, out_keys, out_sums, out_cap, d_ngroups, nullptr, ws.p,
+                           stream);
 }
 
-// Group-by of the rows [0, *count) of a selection over (key, val) columns: the
-// first move reads the columns, so no widened copy of the pairs is written.
-// pk/pv: scratch for cap pairs.
-pyst_status column_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *val, const int32_t *sel,
-                           const int64_t *count, int64_t *pk, int64_t *pv, int64_t *out_keys, int64_t *out_sums,
-                           int64_t out_cap, int64_t *d_ngroups, hipStream_t stream) {
-  MoveArgs first{};
-  first.kcol = key->data;
-  first.vcol = val->data;
-  first.sel = sel;
-  first.k64 = key->dtype == PYST_I64;
-  first.v64 = val->dtype == PYST_I64;
-  first.err = ctx_err_word(ctx);
-  return pair_groupby_from(ctx, first, pk, pv, count, key->n, out_keys, out_sums, out_cap, d_ngroups, stream);
+// ---------------------------------------------------------------- planned group-by of columns
+// Least and greatest key of the rows (per-block partial results) and a sample
+// of the keys at jittered even steps.  One read of the keys, coalesced 4- or
+// 8-byte loads with eight in flight a thread.  An EMPTY int64 key is latched.
+constexpr int kRangeBlocks = 2048, kRangeItems = 8;
+__global__ __launch_bounds__(256) void k_key_range(const void *key, int key64, const int32_t *sel, const int64_t *d_nsel,
+                                                   int64_t n, int64_t *lo_out, int64_t *hi_out, int64_t *samples,
+                                                   uint32_t *err) {
+  __shared__ int64_t s_lo[4], s_hi[4];
+  int64_t cnt = count_of(d_nsel, n);
+  if (cnt > n) cnt = n;
+  const int64_t gtid = int64_t{blockIdx.x} * 256 + threadIdx.x;
+  if (gtid < kSamples && cnt > 0) {
+    const uint64_t jitter = fmix32(static_cast<uint32_t>(gtid) ^ kNarrowSeed) >> 16;
+    int64_t i = static_cast<int64_t>(((static_cast<uint64_t>(gtid) << 16) + jitter) * static_cast<uint64_t>(cnt) / (uint64_t{kSamples} << 16));
+    samples[gtid] = load_as_i64(key, key64, row_of(sel, i < cnt ? i : cnt - 1));
+  }
+  int64_t lo = INT64_MAX, hi = INT64_MIN;
+  bool bad = false;
+  for (int64_t i0 = gtid; i0 < cnt; i0 += int64_t{gridDim.x} * 256 * kRangeItems) {
+    int64_t k[kRangeItems], row[kRangeItems];
+#pragma unroll
+    for (int u = 0; u < kRangeItems; ++u) {
+      const int64_t i = i0 + int64_t{u} * gridDim.x * 256;
+      row[u] = i < cnt ? i : i0;
+    }
+    if (sel) load_items<kRangeItems>(sel, 0, row, cnt, row);
+    load_items<kRangeItems>(key, key64, row, n, k);
+#pragma unroll
+    for (int u = 0; u < kRangeItems; ++u) {
+      if (k[u] == kEmpty64) {  // only an int64 column can hold it
+        bad = true;
+        continue;
+      }
+      lo = k[u] < lo ? k[u] : lo;
+      hi = k[u] > hi ? k[u] : hi;
+    }
+  }
+  if (bad) latch(err, kErrKey);
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    const int64_t l = __shfl_xor(lo, o), h = __shfl_xor(hi, o);
+    lo = l < lo ? l : lo;
+    hi = h > hi ? h : hi;
+  }
+  if (lane_id() == 0) {
+    s_lo[threadIdx.x / kWave] = lo;
+    s_hi[threadIdx.x / kWave] = hi;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) {
+      lo = s_lo[w] < lo ? s_lo[w] : lo;
+      hi = s_hi[w] > hi ? s_hi[w] : hi;
+    }
+    lo_out[blockIdx.x] = lo;
+    hi_out[blockIdx.x] = hi;
+  }
+}
+
+// One block: reduces the partial ranges, chooses the mode and clears what the
+// later kernels start from zero (look-back words, ticket, group count).
+// A bucket of the sample with over 1/256 of it, or a part (64 buckets, moved by
+// 8 blocks of the second move) with over 1/12, makes the ranged moves and sums
+// wait for one block each; such keys take hash buckets.
+__global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64_t *lo_in, const int64_t *hi_in,
+                                                      int nblocks, const int64_t *samples, const int64_t *d_nsel,
+                                                      int64_t n, int64_t small_max, int allow_range, int otherwise,
+                                                      uint64_t *status, int64_t *d_ngroups) {
+  __shared__ int32_t s_c[kAggBuckets];
+  __shared__ int64_t s_lo[kAggBlock / kWave], s_hi[kAggBlock / kWave];
+  __shared__ int32_t s_crowded;
+  const int tid = static_cast<int>(threadIdx.x);
+  for (int i = tid; i < kAggBuckets; i += kAggBlock) {
+    s_c[i] = 0;
+    status[i] = 0;
+  }
+  if (tid == 0) s_crowded = 0;
+  int64_t lo = INT64_MAX, hi = INT64_MIN;
+  for (int i = tid; i < nblocks; i += kAggBlock) {
+    lo = lo_in[i] < lo ? lo_in[i] : lo;
+    hi = hi_in[i] > hi ? hi_in[i] : hi;
+  }
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    const int64_t l = __shfl_xor(lo, o), h = __shfl_xor(hi, o);
+    lo = l < lo ? l : lo;
+    hi = h > hi ? h : hi;
+  }
+  if (lane_id() == 0) {
+    s_lo[tid / kWave] = lo;
+    s_hi[tid / kWave] = hi;
+  }
+  __syncthreads();
+  for (int w = 0; w < kAggBlock / kWave; ++w) {
+    lo = s_lo[w] < lo ? s_lo[w] : lo;
+    hi = s_hi[w] > hi ? s_hi[w] : hi;
+  }
+  const uint64_t range = lo > hi ? 0 : static_cast<uint64_t>(hi) - static_cast<uint64_t>(lo) + 1;
+  int32_t mode = otherwise, shift = 0;
+  if (range <= static_cast<uint64_t>(small_max)) {
+    mode = kGbSmall;
+  } else if (allow_range && range <= static_cast<uint64_t>(kAggBuckets) * kDirectSlots) {  // block-uniform
+    mode = kGbRange;
+    while (((range - 1) >> shift) >= kAggBuckets) ++shift;
+    for (int i = tid; i < kSamples; i += kAggBlock) {
+      const uint64_t off = static_cast<uint64_t>(samples[i]) - static_cast<uint64_t>(lo);
+      if (off < range) atomicAdd(&s_c[off >> shift], 1);
+    }
+    __syncthreads();
+    for (int b = tid; b < kAggBuckets; b += kAggBlock) {
+      const int c = s_c[b];
+      if (c > kSamples / 256 || wave_sum(c) > kSamples / 12) s_crowded = 1;  // a wave holds one part's 64 buckets
+    }
+    __syncthreads();
+    if (s_crowded) mode = otherwise;
+  }
+  if (tid == 0) {
+    int64_t cnt = count_of(d_nsel, n);
+    plan->kmin = lo;
+    plan->range = range;
+    plan->count = cnt < n ? cnt : n;
+    plan->mode = mode;
+    plan->shift = shift;
+    plan->sort_count = 0;
+    plan->ticket = 0;
+    *d_ngroups = 0;
+  }
+}
+
+// kGbSmall: a block's rows (one contiguous range of them) summed in LDS, then
+// written as its partial arrays.  With few keys each lane adds to one of
+// `copies` interleaved tables, so that a wave's 64 adds do not all meet in a
+// few words.  Bound by the read of the rows (12 bytes each for int32 keys and
+// int64 values).
+__global__ __launch_bounds__(kAggBlock, 8) void k_small_sums(const void *key, int key64, const void *val, int val64,
+                                                            const int32_t *sel, int64_t rows, const GbPlan *plan,
+                                                            uint64_t *psum, uint8_t *pflag) {
+  __shared__ uint64_t s_sum[kDirectSlots];
+  __shared__ uint8_t s_flag[kDirectSlots];
+  if (plan->mode != kGbSmall || plan->range == 0) return;
+  constexpr int U = 8;
+  const int tid = static_cast<int>(threadIdx.x);
+  const uint32_t range = static_cast<uint32_t>(plan->range);
+  const int64_t kmin = plan->kmin;
+  int lgc = 0;  // copies = 1 << lgc
+  while (lgc < 4 && (range << (lgc + 1)) <= kDirectSlots) ++lgc;
+  for (int i = tid; i < kDirectSlots; i += kAggBlock) {
+    s_sum[i] = 0;
+    s_flag[i] = 0;
+  }
+  __syncthreads();
+  const int64_t n = plan->count, per = (n + gridDim.x - 1) / gridDim.x;
+  const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
+  const int64_t lo = per * blk < n ? per * blk : n, hi = lo + per < n ? lo + per : n;
+  const uint32_t copy = static_cast<uint32_t>(tid) & ((1u << lgc) - 1);
+  for (int64_t i0 = lo + tid; i0 < hi; i0 += int64_t{kAggBlock} * U) {
+    int64_t k[U], v[U], row[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + int64_t{u} * kAggBlock;
+      row[u] = i < hi ? i : i0;
+    }
+    if (sel) load_items<U>(sel, 0, row, hi, row);
+    load_items<U>(key, key64, row, rows, k);
+    load_items<U>(val, val64, row, rows, v);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t off = static_cast<uint64_t>(k[u]) - static_cast<uint64_t>(kmin);
+      if (i0 + int64_t{u} * kAggBlock >= hi || off >= range) continue;  // past the end, or an EMPTY key
+      const uint32_t s = (static_cast<uint32_t>(off) << lgc) | copy;
+      atomicAdd(reinterpret_cast<unsigned long long *>(&s_sum[s]), static_cast<unsigned long long>(v[u]));
+      s_flag[s] = 1;
+    }
+  }
+  __syncthreads();
+  for (uint32_t o = tid; o < range; o += kAggBlock) {
+    uint64_t sum = 0;
+    uint32_t f = 0;
+    for (uint32_t c = 0; c < (1u << lgc); ++c) {
+      sum += s_sum[(o << lgc) | c];
+      f |= s_flag[(o << lgc) | c];
+    }
+    psum[blk * range + o] = sum;
+    pflag[blk * range + o] = static_cast<uint8_t>(f);
+  }
+}
+
+// Adds up the blocks' partial arrays, 64 keys per block, and writes the groups
+// that occur in key order (look-back over the blocks).
+__global__ __launch_bounds__(kAggBlock) void k_small_groups(GbPlan *plan, const uint64_t *psum, const uint8_t *pflag,
+                                                           int nparts, uint64_t *status, int64_t *out_keys,
+                                                           int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups,
+                                                           uint32_t *err) {
+  constexpr int NW = kAggBlock / kWave, U = 4;
+  __shared__ uint64_t s_sum[NW][kWave];
+  __shared__ uint32_t s_flag[NW][kWave];
+  __shared__ int64_t s_tile;
+  if (plan->mode != kGbSmall) return;
+  const int64_t range = static_cast<int64_t>(plan->range), ntiles = (range + kWave - 1) / kWave;
+  if (threadIdx.x == 0) s_tile = static_cast<int64_t>(atomicAdd(&plan->ticket, 1ull));
+  __syncthreads();
+  const int64_t t = s_tile;
+  if (t >= ntiles) return;  // block-uniform
+  const int w = static_cast<int>(threadIdx.x) / kWave, lane = lane_id();
+  const int64_t o = t * kWave + lane;
+  uint64_t sum = 0;
+  uint32_t f = 0;
+  for (int b0 = w; b0 < nparts; b0 += NW * U) {
+    uint64_t x[U];
+    uint32_t y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int b = b0 + u * NW;
+      const bool ok = b < nparts && o < range;
+      x[u] = ok ? psum[int64_t{b} * range + o] : 0;
+      y[u] = ok ? pflag[int64_t{b} * range + o] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      sum += x[u];
+      f |= y[u];
+    }
+  }
+  s_sum[w][lane] = sum;
+  s_flag[w][lane] = f;
+  __syncthreads();
+  if (w != 0) return;
+  for (int k = 1; k < NW; ++k) {
+    sum += s_sum[k][lane];
+    f |= s_flag[k][lane];
+  }
+  const uint64_t m = __ballot(f != 0);
+  const int64_t agg = __popcll(m), ex = lookback_exclusive(status, t, agg);
+  const int64_t p = ex + mbcnt(m);
+  if (f) {
+    if (p < out_cap) {
+      out_keys[p] = plan->kmin + o;
+      out_sums[p] = static_cast<int64_t>(sum);
+    } else {
+      latch(err, kErrCapacity);
+    }
+  }
+  if (lane == 0 && t == ntiles - 1) *d_ngroups = ex + agg;
+}
+
+// kGbRange: the pairs of each bucket summed in an LDS array indexed by the low
+// `shift` bits of key - kmin; the groups leave in key order.  Blocks take
+// buckets by ticket, in order, and find their output position by look-back, so
+// a bucket only waits on buckets that are already running.  Two blocks per CU.
+template <bool NARROW>
+__global__ __launch_bounds__(kAggBlock, 8) void k_direct_groups(GbPlan *plan, const void *pairs, const int64_t *vals,
+                                                               const int32_t *pos, int bps, uint64_t *status,
+                                                               int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
+                                                               int64_t *d_ngroups, uint32_t *err) {
+  constexpr int NW = kAggBlock / kWave, U = NARROW ? 8 : 4, PER = kDirectSlots / kAggBlock;
+  __shared__ uint64_t s_sum[kDirectSlots];
+  __shared__ uint8_t s_flag[kDirectSlots];
+  __shared__ int32_t s_cnt[PER * NW];
+  __shared__ int64_t s_base;
+  __shared__ int32_t s_b;
+  static_assert(PER * NW == 2 * kWave, "one wave scans the counts, two a lane");
+  if (plan->mode != kGbRange) return;
+  const int tid = static_cast<int>(threadIdx.x), w = tid / kWave, lane = lane_id();
+  const int64_t kmin = plan->kmin;
+  const int shift = plan->shift;
+  const int nbuckets = static_cast<int>((plan->range - 1) >> shift) + 1;
+  const uint32_t mask = (1u << shift) - 1;
+  const int used = static_cast<int>((mask + kAggBlock) / kAggBlock);  // rounds of 1024 slots in use
+  for (int i = tid; i < kDirectSlots; i += kAggBlock) {
+    s_sum[i] = 0;
+    s_flag[i] = 0;
+  }
+  while (true) {
+    if (tid == 0) s_b = static_cast<int32_t>(atomicAdd(&plan->ticket, 1ull));
+    __syncthreads();  // also: the table is clear, s_base and s_cnt are read
+    const int b = s_b;
+    if (b >= nbuckets) break;  // block-uniform
+    const int64_t lo = pos[int64_t{b} * bps], hi = pos[int64_t{b + 1} * bps];
+    for (int64_t i0 = lo + tid; i0 < hi; i0 += int64_t{kAggBlock} * U) {
+      int64_t k[U], v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = i0 + int64_t{u} * kAggBlock < hi ? i0 + int64_t{u} * kAggBlock : i0;
+        if (NARROW) {
+          const uint64_t pr = static_cast<const uint64_t *>(pairs)[i];
+          k[u] = static_cast<int32_t>(pr >> 32);
+          v[u] = static_cast<int32_t>(pr & 0xffffffffu);
+        } else {
+          k[u] = static_cast<const int64_t *>(pairs)[i];
+          v[u] = vals[i];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (i0 + int64_t{u} * kAggBlock >= hi) continue;
+        const uint32_t s = static_cast<uint32_t>(k[u] - kmin) & mask;
+        atomicAdd(reinterpret_cast<unsigned long long *>(&s_sum[s]), static_cast<unsigned long long>(v[u]));
+        s_flag[s] = 1;
+      }
+    }
+    __syncthreads();
+    uint64_t m[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      m[j] = j < used ? __ballot(s_flag[j * kAggBlock + tid] != 0) : 0;
+      if (lane == 0) s_cnt[j * NW + w] = __popcll(m[j]);
+    }
+    __syncthreads();
+    if (w == 0) {
+      const int32_t a = s_cnt[2 * lane], c = s_cnt[2 * lane + 1];
+      const int32_t incl = wave_inclusive_scan(a + c);
+      s_cnt[2 * lane] = incl - a - c;
+      s_cnt[2 * lane + 1] = incl - c;
+      const int64_t agg = __shfl(incl, kWave - 1);
+      const int64_t ex = lookback_exclusive(status, b, agg);
+      if (lane == 0) {
+        s_base = ex;
+        if (b == nbuckets - 1) {
+          *d_ngroups = ex + agg;
+          if (ex + agg > out_cap) latch(err, kErrCapacity);
+        }
+      }
+    }
+    __syncthreads();
+    const int64_t base = s_base;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int s = j * kAggBlock + tid;
+      if (j < used && ((m[j] >> lane) & 1ull)) {
+        const int64_t p = base + s_cnt[j * NW + w] + mbcnt(m[j]);
+        if (p < out_cap) {
+          out_keys[p] = kmin + ((int64_t{b} << shift) | s);
+          out_sums[p] = static_cast<int64_t>(s_sum[s]);
+        }
+        s_sum[s] = 0;
+        s_flag[s] = 0;
+      }
+    }
+  }
+}
+
+template <bool NARROW>
+pyst_status launch_direct_groups(pyst_ctx *ctx, GbPlan *plan, uint64_t *status, const void *pairs, const int64_t *vals,
+                                 const int32_t *pos, int bps, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
+                                 int64_t *d_ngroups, hipStream_t stream) {
+  const int blocks = static_cast<int>(std::min<int64_t>(kAggBuckets, 2 * std::max(1, ctx_num_cus(ctx))));
+  k_direct_groups<NARROW><<<blocks, kAggBlock, 0, stream>>>(plan, pairs, vals, pos, bps, status, out_keys, out_sums,
+                                                           out_cap, d_ngroups, ctx_err_word(ctx));
+  PYST_LAUNCH_CHECK("k_direct_groups");
+  return PYST_OK;
+}
+
+// The group count of the hash modes is what remains to be sorted.
+__global__ void k_gb_sort_count(GbPlan *plan, const int64_t *d_ngroups) {
+  plan->sort_count = plan->mode == kGbHash || plan->mode == kGbTable ? *d_ngroups : 0;
+}
+
+// Small scratch of a planned group-by: the plan, the look-back words, the
+// blocks' key ranges and the sample.
+constexpr size_t kPlanBytes = 256 + sizeof(uint64_t) * kAggBuckets + 2 * sizeof(int64_t) * kRangeBlocks +
+                              sizeof(int64_t) * kSamples;
+
+// GROUP BY of key->n >= 2^20 rows (of a selection).  hash_buckets: few enough
+// groups (kRadixGroupsMax) for LDS hash tables; else keys without a small range
+// take the table in HBM (`bound` groups at most) and the ranged moves are used
+// only where the arena also has room for them.
+pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *val, const int32_t *sel,
+                            const int64_t *d_nsel, int64_t max_groups, int64_t bound, double max_load,
+                            bool hash_buckets, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
+                            int64_t *d_ngroups, int sort_by_key, hipStream_t stream) {
+  const int64_t n = key->n;
+  const bool narrow = key->dtype == PYST_I32 && val->dtype == PYST_I32;  // 8-byte pairs, else 16-byte ones
+  const int k64 = key->dtype == PYST_I64, v64 = val->dtype == PYST_I64;
+  uint32_t *err = ctx_err_word(ctx);
+  GbPlan *plan = nullptr;
+  Scratch ps(ctx, stream);
+  {
+    const int64_t cap_alloc = hash_buckets ? 0 : table_capacity_host(bound, max_load);
+    Scratch table(ctx, stream), ws(ctx, stream), ws2(ctx, stream);
+    if (!hash_buckets) table.alloc(group_bytes(cap_alloc));
+    const size_t wsb = narrow ? narrow_groupby_bytes(n) : static_cast<size_t>(n) * 16;
+    hash_buckets ? ws.alloc(wsb) : ws.try_alloc(wsb);
+    if (!narrow && ws.p) hash_buckets ? ws2.alloc(wide_groupby_bytes(n)) : ws2.try_alloc(wide_groupby_bytes(n));
+    const bool moves = ws.p && (narrow || ws2.p);
+    if (hash_buckets ? !moves : !table.p) return set_error(PYST_ERR_NOMEM, "pyst_groupby_sum: arena exhausted");
+    ps.try_alloc(kPlanBytes);
+    const int64_t *count = d_nsel;
+    uint64_t *status = nullptr;
+    pyst_status st;
+    if (ps.p) {
+      plan = ps.as<GbPlan>();
+      count = &plan->count;
+      status = reinterpret_cast<uint64_t *>(static_cast<char *>(ps.p) + 256);
+      int64_t *lo = reinterpret_cast<int64_t *>(status + kAggBuckets), *hi = lo + kRangeBlocks,
+              *samples = hi + kRangeBlocks;
+      const int rblocks = static_cast<int>(std::min<int64_t>(kRangeBlocks, ceil_div(n, 256 * kRangeItems)));
+      // the blocks' partial arrays of kGbSmall take the memory of the moves, or of the table
+      const size_t room = moves ? static_cast<size_t>(n) * 16 : group_bytes(cap_alloc);
+      const int parts = std::max(1, std::min(512, 2 * ctx_num_cus(ctx)));
+      const int64_t small_max = std::min<int64_t>(kDirectSlots, static_cast<int64_t>(room / (parts * 9)));
+      k_key_range<<<rblocks, 256, 0, stream>>>(key->data, k64, sel, d_nsel, n, lo, hi, samples, err);
+      PYST_LAUNCH_CHECK("k_key_range");
+      k_gb_plan<<<1, kAggBlock, 0, stream>>>(plan, lo, hi, rblocks, samples, d_nsel, n, small_max, moves,
+                                             hash_buckets ? kGbHash : kGbTable, status, d_ngroups);
+      PYST_LAUNCH_CHECK("k_gb_plan");
+      uint64_t *psum = moves ? ws.as<uint64_t>() : table.as<uint64_t>();
+      uint8_t *pflag = reinterpret_cast<uint8_t *>(psum + parts * small_max);
+      k_small_sums<<<parts, kAggBlock, 0, stream>>>(key->data, k64, val->data, v64, sel, n, plan, psum, pflag);
+      PYST_LAUNCH_CHECK("k_small_sums");
+      k_small_groups<<<static_cast<unsigned>(ceil_div(std::max<int64_t>(small_max, 1), kWave)), kAggBlock, 0,
+                       stream>>>(plan, psum, pflag, parts, status, out_keys, out_sums, out_cap, d_ngroups, err);
+      PYST_LAUNCH_CHECK("k_small_groups");
+    } else if (hash_buckets) {  // no room for a plan: hash buckets for any keys
+      if ((st = fill_u64(d_ngroups, 1, 0, stream)) != PYST_OK) return st;
+      if (!count) {
+        if (!ps.alloc(256)) return set_error(PYST_ERR_NOMEM, "pyst_groupby_sum: arena exhausted");
+        if ((st = fill_u64(ps.p, 1, static_cast<uint64_t>(n), stream)) != PYST_OK) return st;
+        count = ps.as<int64_t>();
+      }
+    }
+    if (hash_buckets || (plan && moves)) {
+      if (narrow) {
+        st = narrow_groupby(ctx, static_cast<const int32_t *>(key->data), static_cast<const int32_t *>(val->data), sel,
+                            count, n, ws.p, out_keys, out_sums, out_cap, d_ngroups, plan, status, stream);
+      } else {
+        MoveArgs first{};
+        first.kcol = key->data;
+        first.vcol = val->data;
+        first.sel = sel;
+        first.k64 = k64;
+        first.v64 = v64;
+        first.err = err;
+        first.plan = plan;
+        int64_t *pk = ws.as<int64_t>();
+        st = pair_groupby_from(ctx, first, pk, pk + n, count, n, out_keys, out_sums, out_cap, d_ngroups, status, ws2.p,
+                               stream);
+      }
+      if (st != PYST_OK) return st;
+    }
+    if (!hash_buckets) {
+      const GroupDev g = group_view(table.p, cap_alloc);
+      st = table_groupby(ctx, g, key, val, sel, d_nsel, max_groups, max_load, out_keys, out_sums, out_cap, d_ngroups,
+                         plan, stream);
+      if (st != PYST_OK) return st;
+    }
+  }
+  if (!sort_by_key) return PYST_OK;
+  const int64_t *sort_count = d_ngroups;
+  if (plan) {
+    k_gb_sort_count<<<1, 1, 0, stream>>>(plan, d_ngroups);
+    PYST_LAUNCH_CHECK("k_gb_sort_count");
+    sort_count = &plan->sort_count;
+  }
+  return sort_pairs_by_key(ctx, out_keys, out_sums, sort_count, out_cap, stream);
 }
 
 }  // namespace pyst

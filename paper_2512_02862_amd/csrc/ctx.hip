@@ -163,7 +163,7 @@ pyst_status hip_error(hipError_t e, const char *what) {
   return set_error(PYST_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-void *ctx_alloc(pyst_ctx *c, size_t bytes, hipStream_t stream) {
+static void *arena_alloc(pyst_ctx *c, size_t bytes, hipStream_t stream, bool wait) {
   bytes = (bytes + kAlign - 1) / kAlign * kAlign;
   if (bytes == 0) bytes = kAlign;
   size_t off = 0;
@@ -191,7 +191,7 @@ void *ctx_alloc(pyst_ctx *c, size_t bytes, hipStream_t stream) {
       break;
     }
     if (take_first_fit(c, bytes, &off)) break;
-    if (c->pending.empty()) return nullptr;
+    if (c->pending.empty() || !wait) return nullptr;
     // Backpressure: give every pending block an event, wait for the oldest, retry.
     if (!mark_pending(c)) {  // an event could not be recorded: wait for the whole device
       (void)hipDeviceSynchronize();
@@ -203,6 +203,9 @@ void *ctx_alloc(pyst_ctx *c, size_t bytes, hipStream_t stream) {
   c->used += c->live[off];
   return c->base + off;
 }
+
+void *ctx_alloc(pyst_ctx *c, size_t bytes, hipStream_t stream) { return arena_alloc(c, bytes, stream, true); }
+void *ctx_try_alloc(pyst_ctx *c, size_t bytes, hipStream_t stream) { return arena_alloc(c, bytes, stream, false); }
 
 void ctx_free(pyst_ctx *c, void *p, hipStream_t stream) {
   if (!p) return;

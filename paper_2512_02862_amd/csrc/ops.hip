@@ -958,7 +958,9 @@ __global__ __launch_bounds__(BLOCK) void k_join_probe(const void *key, const int
 
 // ============================================================== group-by SUM
 // 16-byte slots {int64 key, uint64 sum}; EMPTY key = INT64_MIN.
-__global__ void k_gb_init(GroupDev g, const int64_t *d_nsel, int64_t n, int64_t max_groups, double max_load) {
+__global__ void k_gb_init(GroupDev g, const int64_t *d_nsel, int64_t n, int64_t max_groups, double max_load,
+                          const GbPlan *plan) {
+  if (plan && plan->mode != kGbTable) return;
   int64_t cnt = count_of(d_nsel, n);
   if (max_groups > 0 && max_groups < cnt) cnt = max_groups;
   const int64_t cap = table_capacity(cnt, max_load, g.cap_alloc);
@@ -971,7 +973,8 @@ __global__ void k_gb_init(GroupDev g, const int64_t *d_nsel, int64_t n, int64_t 
 
 __global__ __launch_bounds__(256) void k_gb_insert(const void *key, int key64, const void *val, int val64,
                                                    const int32_t *sel, const int64_t *d_nsel, int64_t n, GroupDev g,
-                                                   uint32_t *err, int skip_empty) {
+                                                   uint32_t *err, int skip_empty, const GbPlan *plan) {
+  if (plan && plan->mode != kGbTable) return;
   // skip_empty: the input is a pair buffer whose unused slots hold the EMPTY key
   int64_t cnt = count_of(d_nsel, n);
   if (cnt > n) cnt = n;
@@ -991,9 +994,11 @@ __global__ __launch_bounds__(256) void k_gb_insert(const void *key, int key64, c
 template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void k_gb_compact(GroupDev g, int64_t *out_keys, int64_t *out_sums,
                                                      int64_t out_cap, int64_t *d_ngroups, uint64_t *status,
-                                                     unsigned long long *ticket, int64_t ntiles, uint32_t *err) {
+                                                     unsigned long long *ticket, int64_t ntiles, uint32_t *err,
+                                                     const GbPlan *plan) {
   constexpr int NW = BLOCK / kWave;
   constexpr int64_t TILE = int64_t{BLOCK} * ITEMS;
+  if (plan && plan->mode != kGbTable) return;
   __shared__ int64_t s_tile, s_prefix;
   __shared__ int32_t s_cnt[NW];
   if (threadIdx.x == 0) s_tile = static_cast<int64_t>(atomicAdd(ticket, 1ull));
@@ -1043,7 +1048,7 @@ __global__ __launch_bounds__(BLOCK) void k_gb_compact(GroupDev g, int64_t *out_k
 }
 
 pyst_status group_compact(pyst_ctx *ctx, const GroupDev &g, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
-                          int64_t *d_ngroups, hipStream_t stream) {
+                          int64_t *d_ngroups, hipStream_t stream, const GbPlan *plan) {
   constexpr int BLOCK = 256, ITEMS = 8;
   const int64_t ntiles = std::max<int64_t>(1, ceil_div(g.cap_alloc, int64_t{BLOCK} * ITEMS));
   Scratch sc(ctx, (ntiles + 1) * sizeof(uint64_t), stream);
@@ -1053,17 +1058,32 @@ pyst_status group_compact(pyst_ctx *ctx, const GroupDev &g, int64_t *out_keys, i
   uint64_t *status = sc.as<uint64_t>();
   k_gb_compact<BLOCK, ITEMS><<<static_cast<unsigned>(ntiles), BLOCK, 0, stream>>>(
       g, out_keys, out_sums, out_cap, d_ngroups, status, reinterpret_cast<unsigned long long *>(status + ntiles),
-      ntiles, ctx_err_word(ctx));
+      ntiles, ctx_err_word(ctx), plan);
   PYST_LAUNCH_CHECK("k_gb_compact");
   return PYST_OK;
 }
 
 pyst_status group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int64_t max_groups, double max_load,
-                       hipStream_t stream) {
+                       hipStream_t stream, const GbPlan *plan) {
   const int blocks = static_cast<int>(std::min<int64_t>(ceil_div(g.cap_alloc, 256), 4096));
-  k_gb_init<<<blocks, 256, 0, stream>>>(g, d_nsel, n, max_groups, max_load);
+  k_gb_init<<<blocks, 256, 0, stream>>>(g, d_nsel, n, max_groups, max_load, plan);
   PYST_LAUNCH_CHECK("k_gb_init");
   return PYST_OK;
+}
+
+pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val,
+                          const int32_t *sel, const int64_t *d_nsel, int64_t max_groups, double max_load,
+                          int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups,
+                          const GbPlan *plan, hipStream_t stream) {
+  pyst_status st = group_init(g, d_nsel, key->n, max_groups, max_load, stream, plan);
+  if (st != PYST_OK) return st;
+  if (key->n > 0) {
+    const int blocks = grid_for(ctx, key->n, 256, 8);
+    k_gb_insert<<<blocks, 256, 0, stream>>>(key->data, key->dtype == PYST_I64, val->data, val->dtype == PYST_I64, sel,
+                                            d_nsel, key->n, g, ctx_err_word(ctx), 0, plan);
+    PYST_LAUNCH_CHECK("k_gb_insert");
+  }
+  return group_compact(ctx, g, out_keys, out_sums, out_cap, d_ngroups, stream, plan);
 }
 
 // ============================================================== gather (materialize)
@@ -1200,15 +1220,11 @@ __global__ __launch_bounds__(BLOCK) void k_gather_rows(const int64_t *rows, Gath
 }
 
 // Defined with the pair aggregation and the context.
-pyst_status column_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *val, const int32_t *sel,
-                           const int64_t *count, int64_t *pk, int64_t *pv, int64_t *out_keys, int64_t *out_sums,
-                           int64_t out_cap, int64_t *d_ngroups, hipStream_t stream);
+pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *val, const int32_t *sel,
+                            const int64_t *d_nsel, int64_t max_groups, int64_t bound, double max_load,
+                            bool hash_buckets, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
+                            int64_t *d_ngroups, int sort_by_key, hipStream_t stream);
 bool ctx_groupby_hash_only(const pyst_ctx *ctx);
-
-size_t narrow_groupby_bytes(int64_t cap);
-pyst_status narrow_groupby(pyst_ctx *ctx, const int32_t *kcol, const int32_t *vcol, const int32_t *sel,
-                           const int64_t *count, int64_t cap, void *ws, int64_t *out_keys, int64_t *out_sums,
-                           int64_t out_cap, int64_t *d_ngroups, hipStream_t stream);
 
 // The radix path groups 4096 hash buckets in an LDS table of 8192 slots each:
 // up to 16M groups a bucket holds 4096 keys on average, 64 standard deviations
@@ -1604,53 +1620,25 @@ pyst_status pyst_groupby_sum(pyst_ctx *ctx, const pyst_col *key, const pyst_col 
   const int64_t bound = max_groups > 0 ? std::min<int64_t>(max_groups, key->n) : key->n;
   const int64_t out_cap = max_groups > 0 ? max_groups : key->n;
   if (out_cap > 0 && (!out_keys || !out_sums)) return set_error(PYST_ERR_ARG, "pyst_groupby_sum: NULL outputs");
-  if (!ctx_groupby_hash_only(ctx) && key->n >= kRadixRowsMin && bound <= kRadixGroupsMax) {
-    // Radix-partitioned: the rows are moved twice by hash bits into 4096 buckets
-    // (the first move reading the columns) and each bucket is summed in LDS,
+  if (!ctx_groupby_hash_only(ctx) && key->n >= kRadixRowsMin) {
+    // By key range where that is small enough for LDS arrays, else radix-partitioned:
+    // the rows are moved twice into 4096 buckets and each bucket is summed in LDS,
     // instead of two random L2 atomics per row.
-    TimedRegion timed(ctx, "groupby_radix", stream);
-    if (key->dtype == PYST_I32 && val->dtype == PYST_I32) {  // 8-byte pairs
-      Scratch ws(ctx, narrow_groupby_bytes(key->n) + 256, stream);
-      if (!ws.p) return set_error(PYST_ERR_NOMEM, "pyst_groupby_sum: arena exhausted");
-      int64_t *d_cnt = reinterpret_cast<int64_t *>(static_cast<char *>(ws.p) + narrow_groupby_bytes(key->n));
-      pyst_status st = fill_u64(d_ngroups, 1, 0, stream);
-      if (st == PYST_OK && !d_nsel) st = fill_u64(d_cnt, 1, static_cast<uint64_t>(key->n), stream);
-      if (st == PYST_OK)
-        st = narrow_groupby(ctx, static_cast<const int32_t *>(key->data), static_cast<const int32_t *>(val->data), sel,
-                            d_nsel ? d_nsel : d_cnt, key->n, ws.p, out_keys, out_sums, out_cap, d_ngroups, stream);
-      if (st != PYST_OK) return st;
-      if (sort_by_key) return sort_pairs_by_key(ctx, out_keys, out_sums, d_ngroups, out_cap, stream);
-      return PYST_OK;
-    }
-    Scratch pairs(ctx, static_cast<size_t>(key->n) * 16 + 256, stream);
-    if (!pairs.p) return set_error(PYST_ERR_NOMEM, "pyst_groupby_sum: arena exhausted");
-    int64_t *pk = pairs.as<int64_t>(), *pv = pk + key->n, *d_cnt = pv + key->n;
-    pyst_status st = fill_u64(d_ngroups, 1, 0, stream);
-    if (st == PYST_OK && !d_nsel) st = fill_u64(d_cnt, 1, static_cast<uint64_t>(key->n), stream);
-    if (st != PYST_OK) return st;
-    st = column_groupby(ctx, key, val, sel, d_nsel ? d_nsel : d_cnt, pk, pv, out_keys, out_sums, out_cap, d_ngroups,
-                        stream);
-    if (st != PYST_OK) return st;
-    if (sort_by_key) return sort_pairs_by_key(ctx, out_keys, out_sums, d_ngroups, out_cap, stream);
-    return PYST_OK;
+    const bool radix = bound <= kRadixGroupsMax;
+    TimedRegion timed(ctx, radix ? "groupby_radix" : "groupby_hash", stream);
+    return planned_groupby(ctx, key, val, sel, d_nsel, max_groups, bound, max_load, radix, out_keys, out_sums, out_cap,
+                           d_ngroups, sort_by_key, stream);
   }
   TimedRegion timed(ctx, "groupby_hash", stream);
   const int64_t cap_alloc = table_capacity_host(bound, max_load);
-  Scratch mem(ctx, group_bytes(cap_alloc), stream);
-  if (!mem.p) return set_error(PYST_ERR_NOMEM, "pyst_groupby_sum: arena exhausted");
-  GroupDev g = group_view(mem.p, cap_alloc);
-  pyst_status st = group_init(g, d_nsel, key->n, max_groups, max_load, stream);
-  if (st != PYST_OK) return st;
-  if (key->n > 0) {
-    const int blocks = grid_for(ctx, key->n, 256, 8);
-    k_gb_insert<<<blocks, 256, 0, stream>>>(key->data, key->dtype == PYST_I64, val->data, val->dtype == PYST_I64, sel,
-                                            d_nsel, key->n, g, ctx_err_word(ctx), 0);
-    PYST_LAUNCH_CHECK("k_gb_insert");
+  {
+    Scratch mem(ctx, group_bytes(cap_alloc), stream);
+    if (!mem.p) return set_error(PYST_ERR_NOMEM, "pyst_groupby_sum: arena exhausted");
+    pyst_status st = table_groupby(ctx, group_view(mem.p, cap_alloc), key, val, sel, d_nsel, max_groups, max_load,
+                                   out_keys, out_sums, out_cap, d_ngroups, nullptr, stream);
+    if (st != PYST_OK || !sort_by_key) return st;
   }
-  st = group_compact(ctx, g, out_keys, out_sums, out_cap, d_ngroups, stream);
-  if (st != PYST_OK) return st;
-  if (sort_by_key) return sort_pairs_by_key(ctx, out_keys, out_sums, d_ngroups, out_cap, stream);
-  return PYST_OK;
+  return sort_pairs_by_key(ctx, out_keys, out_sums, d_ngroups, out_cap, stream);
 }
 
 }  // extern "C"

@@ -213,6 +213,8 @@ struct CtxImpl;  // defined in ctx.cpp
 
 // Stream-ordered sub-allocation from the context arena (see ctx.cpp).
 void *ctx_alloc(pyst_ctx *ctx, size_t bytes, hipStream_t stream);
+// ctx_try_alloc never waits for another stream's work: nullptr where ctx_alloc would.
+void *ctx_try_alloc(pyst_ctx *ctx, size_t bytes, hipStream_t stream);
 // ctx_free keeps the block for `stream` (reused by it at once; other streams
 // get it after an event that is recorded only when they need the memory), so
 // `stream` must stay valid until pyst_ctx_check on it or the context's end.
@@ -252,12 +254,15 @@ struct Scratch {
   hipStream_t stream = nullptr;
   void *p = nullptr;
   Scratch() = default;
+  Scratch(pyst_ctx *c, hipStream_t s) : ctx(c), stream(s) {}  // nothing yet: alloc() once
   Scratch(pyst_ctx *c, size_t bytes, hipStream_t s) : ctx(c), stream(s), p(ctx_alloc(c, bytes, s)) {}
   Scratch(const Scratch &) = delete;
   Scratch &operator=(const Scratch &) = delete;
   ~Scratch() {
     if (p) ctx_free(ctx, p, stream);
   }
+  void *alloc(size_t bytes) { return p = ctx_alloc(ctx, bytes, stream); }
+  void *try_alloc(size_t bytes) { return p = ctx_try_alloc(ctx, bytes, stream); }
   template <typename T>
   T *as() const { return static_cast<T *>(p); }
 };

@@ -37,6 +37,19 @@ struct GroupDev {
   int64_t cap_alloc;
 };
 
+// How the rows of a group-by are grouped: chosen on the device from the keys'
+// range (see the planned group-by).  Kernels of the other modes return at once.
+enum : int32_t { kGbHash = 0, kGbSmall = 1, kGbRange = 2, kGbTable = 3 };
+struct GbPlan {
+  int64_t kmin;
+  uint64_t range;      // greatest - least key + 1; 0 without rows
+  int64_t count;       // rows to group
+  int64_t sort_count;  // groups that still need sorting (0 where they come out in key order)
+  int32_t mode;
+  int32_t shift;       // kGbRange: bucket = (key - kmin) >> shift
+  unsigned long long ticket;
+};
+
 __host__ __device__ inline int64_t next_pow2(int64_t x) {
   int64_t p = 1;
   while (p < x) p <<= 1;
@@ -109,9 +122,14 @@ __device__ __forceinline__ bool group_add(uint64_t *slots, int64_t mask, int64_t
 // Host helpers implemented in ops.hip / sort.hip.
 pyst_status table_init(const TableDev &t, const int64_t *d_nsel, int64_t n, double max_load, hipStream_t stream);
 pyst_status group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int64_t max_groups, double max_load,
-                       hipStream_t stream);
+                       hipStream_t stream, const GbPlan *plan = nullptr);
 pyst_status group_compact(pyst_ctx *ctx, const GroupDev &g, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
-                          int64_t *d_ngroups, hipStream_t stream);
+                          int64_t *d_ngroups, hipStream_t stream, const GbPlan *plan = nullptr);
+// Group-by of columns through the table `g` in HBM (with a plan: only in mode kGbTable).
+pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val,
+                          const int32_t *sel, const int64_t *d_nsel, int64_t max_groups, double max_load,
+                          int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups,
+                          const GbPlan *plan, hipStream_t stream);
 pyst_status filter_impl(pyst_ctx *ctx, const PredSet &ps, int64_t n, int32_t *sel_out, int64_t *d_nsel,
                         hipStream_t stream);
 pyst_status scan_excl_i32(pyst_ctx *ctx, const int32_t *in, int32_t *out, int64_t len, int64_t *d_total,

@@ -1,0 +1,118 @@
+"""GPU parity of the group-by's key-range plans (LDS arrays over a small range,
+ranged buckets in key order) and of the hash buckets and table they give way
+to, at the edges where the choice changes, against the oracle.  Sums are exact
+integers: equality, no tolerance."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+SMALL, RANGED = 8192, 1 << 25
+
+
+@pytest.fixture(scope="module")
+def ctx(gpu):
+    c = gpu.Ctx(0, 4 << 30)
+    yield c
+    c.close()
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def keys_over(rng, n, span, base, dtype):
+    """n keys that span exactly [base, base + span)."""
+    k = rng.integers(0, span, n)
+    k[0], k[-1] = 0, span - 1
+    return (k + base).astype(dtype)
+
+
+def check(gpu, ctx, k, v, sel=None, **kw):
+    if sel is not None:
+        kw.update(sel=dev(sel) if len(sel) else dev(np.zeros(1, np.int32)), nsel=dev(np.array([len(sel)], np.int64)))
+    gk, gs, ng = gpu.groupby_sum(ctx, dev(k), dev(v), sort_by_key=True, **kw)
+    ctx.check()
+    m = int(ng.item())
+    wk, ws = oracle.groupby_sum(k, v, sel)
+    assert m == len(wk)
+    np.testing.assert_array_equal(gk[:m].cpu().numpy(), wk)
+    np.testing.assert_array_equal(gs[:m].cpu().numpy(), ws)
+
+
+@pytest.mark.parametrize("kt,vt", [(np.int32, np.int32), (np.int32, np.int64), (np.int64, np.int64),
+                                   (np.int64, np.int32)])
+@pytest.mark.parametrize("span,base", [(1, -5), (2, 0), (63, 7), (512, -1), (SMALL - 1, -100), (SMALL, -2**31 + 1),
+                                       (SMALL + 1, -SMALL), (100_000, -2**31 + 1), (RANGED - 1, 3), (RANGED, -RANGED // 2),
+                                       (RANGED + 1, 0)])
+def test_key_ranges(gpu, ctx, kt, vt, span, base):
+    rng = np.random.default_rng(span)
+    n = (1 << 20) + 17
+    k = keys_over(rng, n, span, base, kt)
+    info = np.iinfo(vt)
+    check(gpu, ctx, k, rng.integers(info.min, info.max, n, dtype=vt, endpoint=True))
+
+
+@pytest.mark.parametrize("vt", [np.int32, np.int64])
+@pytest.mark.parametrize("span", [3000, 1_000_000])
+@pytest.mark.parametrize("picked", [0, 1, 100_003])
+def test_selections(gpu, ctx, vt, span, picked):
+    rng = np.random.default_rng(picked + span)
+    n = 1 << 20
+    k = keys_over(rng, n, span, 11, np.int32)
+    sel = np.sort(rng.choice(n, picked, replace=False)).astype(np.int32)
+    check(gpu, ctx, k, rng.integers(-1000, 1000, n).astype(vt), sel)
+
+
+@pytest.mark.parametrize("vt", [np.int32, np.int64])
+def test_crowded_keys_take_hash_buckets(gpu, ctx, vt):
+    # half of the rows in one value, the rest in a far narrower range than the whole
+    rng = np.random.default_rng(5)
+    n = 1_500_000
+    k = np.where(rng.random(n) < 0.5, 77, rng.integers(0, 40_000, n)).astype(np.int32)
+    k[1] = 20_000_000
+    check(gpu, ctx, k, rng.integers(-1000, 1000, n).astype(vt))
+
+
+def test_widest_int64_range_and_sorted_input(gpu, ctx):
+    rng = np.random.default_rng(6)
+    n = 1 << 20
+    k = rng.integers(-2**63 + 1, 2**63 - 1, n, endpoint=True)
+    k[:2] = [-2**63 + 1, 2**63 - 1]
+    check(gpu, ctx, k, rng.integers(-2**62, 2**62, n))
+    check(gpu, ctx, np.sort(keys_over(rng, n, 900_000, -450_000, np.int64)), rng.integers(-2**62, 2**62, n))
+
+
+@pytest.mark.parametrize("span", [900, 5_000_000])
+def test_over_max_groups_keeps_the_count(gpu, ctx, span):
+    n = 1 << 20
+    rng = np.random.default_rng(span)
+    k, v = keys_over(rng, n, span, 0, np.int32), np.ones(n, np.int32)
+    need = len(np.unique(k))
+    gk, gs, ng = gpu.groupby_sum(ctx, dev(k), dev(v), max_groups=need - 1)
+    with pytest.raises(gpu.PystError) as e:
+        ctx.check()
+    assert e.value.status == gpu.ERR_CAPACITY and int(ng.item()) == need
+
+
+@pytest.mark.parametrize("kt,span", [(np.int32, 2500), (np.int32, 3_000_000), (np.int64, 1 << 40)])
+@pytest.mark.parametrize("budget", [4 << 30, 1200 << 20])
+def test_unbounded_groups(gpu, kt, span, budget):
+    # more rows than hash buckets take (2^24) and no bound on the groups: ranges where the arena
+    # has room for the moves beside the table in HBM, else the table
+    c = gpu.Ctx(0, budget)
+    rng = np.random.default_rng(9)
+    n = (1 << 24) + 5
+    k, v = keys_over(rng, n, span, -9, kt), rng.integers(-2**31, 2**31, n).astype(np.int32)
+    gk, gs, ng = gpu.groupby_sum(c, dev(k), dev(v))
+    c.check()
+    m = int(ng.item())
+    gk, gs = gk[:m].cpu().numpy(), gs[:m].cpu().numpy()
+    o = np.argsort(gk)
+    wk, ws = oracle.groupby_sum(k, v)
+    np.testing.assert_array_equal(gk[o], wk)
+    np.testing.assert_array_equal(gs[o], ws)
+    c.close()
