@@ -173,22 +173,9 @@ struct PartArgs {
   int64_t n;
   uint32_t fanout;
   int32_t fbits;        // bits needed to hold fanout - 1
-  int32_t radix_shift;  // >= 0: destination = byte of (key ^ sign bit) at this shift (sort pass); < 0: hash
 };
 
-__device__ __forceinline__ uint32_t part_dest(const PartArgs &a, int64_t row) {
-  if (a.radix_shift >= 0) {
-    const uint64_t k = static_cast<uint64_t>(load_as_i64(a.key, a.key64, row)) ^ (1ull << 63);
-    return static_cast<uint32_t>((k >> a.radix_shift) & 0xffu);
-  }
-  uint32_t h;
-  if (a.key64) h = static_cast<uint32_t>(fmix64(static_cast<uint64_t>(static_cast<const int64_t *>(a.key)[row])));
-  else h = fmix32(static_cast<uint32_t>(static_cast<const int32_t *>(a.key)[row]));
-  return (a.fanout & (a.fanout - 1)) == 0 ? (h & (a.fanout - 1)) : (h % a.fanout);
-}
-
 __device__ __forceinline__ uint32_t part_dest_key(const PartArgs &a, int64_t k) {
-  if (a.radix_shift >= 0) return static_cast<uint32_t>(((static_cast<uint64_t>(k) ^ (1ull << 63)) >> a.radix_shift) & 0xffu);
   const uint32_t h = a.key64 ? static_cast<uint32_t>(fmix64(static_cast<uint64_t>(k)))
                              : fmix32(static_cast<uint32_t>(static_cast<int32_t>(k)));
   return (a.fanout & (a.fanout - 1)) == 0 ? (h & (a.fanout - 1)) : (h % a.fanout);
@@ -489,7 +476,7 @@ __global__ __launch_bounds__(BLOCK) void k_part_scatter(PartArgs a, const int32_
 template <int FMAX>
 static void launch_partition(const PartArgs &a, int32_t *hist, int32_t *scan, int64_t ntiles, hipStream_t stream,
                              bool hist_phase) {
-  if (hist_phase && FMAX <= 64 && !a.sel && !a.key64 && a.radix_shift < 0 && !a.d_nsel && kPartTile == 4096 &&
+  if (hist_phase && FMAX <= 64 && !a.sel && !a.key64 && !a.d_nsel && kPartTile == 4096 &&
       (reinterpret_cast<uintptr_t>(a.key) & 15) == 0)
     k_part_hist_i32<64><<<static_cast<unsigned>(ntiles), 256, 0, stream>>>(a, hist, ntiles);
   else if (hist_phase)
@@ -556,37 +543,6 @@ static pyst_status partition_run(pyst_ctx *ctx, const PartArgs &a, int64_t *d_of
   Scratch sc(ctx, partition_scratch_bytes(a.n, a.fanout), stream);
   if (!sc.p) return set_error(PYST_ERR_NOMEM, "partition: arena exhausted");
   return partition_run_ws(ctx, a, d_offsets, sc.p, stream);
-}
-
-// LSD radix sort of (key, value) int64 pairs, 8 stable byte passes; the first
-// *d_count of `cap` entries are sorted in place (ping-pong through scratch).
-pyst_status sort_pairs_by_key(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const int64_t *d_count, int64_t cap,
-                              hipStream_t stream) {
-  if (cap <= 0) return PYST_OK;
-  Scratch tmp(ctx, 2 * cap * sizeof(int64_t), stream);
-  if (!tmp.p) return set_error(PYST_ERR_NOMEM, "sort: arena exhausted");
-  int64_t *bk[2] = {keys, tmp.as<int64_t>()};
-  int64_t *bv[2] = {vals, tmp.as<int64_t>() + cap};
-  for (int pass = 0; pass < 8; ++pass) {
-    const int src = pass & 1, dst = src ^ 1;
-    PartArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.key = bk[src];
-    a.key64 = 1;
-    a.npay = 1;
-    a.pay[0] = bv[src];
-    a.pay64[0] = 1;
-    a.out[0] = bk[dst];
-    a.out[1] = bv[dst];
-    a.d_nsel = d_count;
-    a.n = cap;
-    a.fanout = 256;
-    a.fbits = 8;
-    a.radix_shift = 8 * pass;
-    pyst_status st = partition_run(ctx, a, nullptr, stream);
-    if (st != PYST_OK) return st;
-  }
-  return PYST_OK;
 }
 
 // Exclusive scan with caller-provided look-back status: (tiles + 1) words,
@@ -1429,7 +1385,6 @@ static pyst_status partition_args(const pyst_col *key, const pyst_col *payloads,
   int bits = 0;
   while ((1u << bits) < fanout) ++bits;
   a.fbits = bits;
-  a.radix_shift = -1;
   return PYST_OK;
 }
 
@@ -1638,7 +1593,7 @@ pyst_status pyst_groupby_sum(pyst_ctx *ctx, const pyst_col *key, const pyst_col 
                                    out_keys, out_sums, out_cap, d_ngroups, nullptr, stream);
     if (st != PYST_OK || !sort_by_key) return st;
   }
-  return sort_pairs_by_key(ctx, out_keys, out_sums, d_ngroups, out_cap, stream);
+  return sort_pairs_by_key(ctx, out_keys, out_sums, d_ngroups, out_cap, key->dtype == PYST_I64 ? 64 : 32, stream);
 }
 
 }  // extern "C"

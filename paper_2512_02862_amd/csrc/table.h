@@ -135,7 +135,7 @@ pyst_status filter_impl(pyst_ctx *ctx, const PredSet &ps, int64_t n, int32_t *se
 pyst_status scan_excl_i32(pyst_ctx *ctx, const int32_t *in, int32_t *out, int64_t len, int64_t *d_total,
                           hipStream_t stream);
 pyst_status sort_pairs_by_key(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const int64_t *d_count, int64_t cap,
-                              hipStream_t stream);
+                              int key_bits, hipStream_t stream);
 int grid_for(pyst_ctx *ctx, int64_t work, int block, int per_cu);
 
 }  // namespace pyst
