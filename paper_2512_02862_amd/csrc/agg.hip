@@ -43,6 +43,9 @@ __device__ __forceinline__ uint64_t agg_hash(int64_t key) { return fmix64(static
 //             kmin) >> shift instead of by hash bits, so that a bucket's LDS
 //             array is indexed directly (no probing, no compare-and-swap) and
 //             the groups come out in key order (no sort).
+//   kGbFew    the sample finds few different keys, over any range: a table in HBM
+//             behind an LDS table per block (k_gb_insert).  The sample promises
+//             nothing: a table that runs full sends the rows on to kGbHash.
 //   kGbHash   otherwise: hash buckets, each summed in an LDS hash table.
 //   kGbTable  the same where hash buckets have no memory or too many groups: the
 //             table in HBM (k_gb_insert).
@@ -54,8 +57,12 @@ __device__ __forceinline__ uint64_t agg_hash(int64_t key) { return fmix64(static
 constexpr int kDirectSlotsLg = 13;
 constexpr int kDirectSlots = 1 << kDirectSlotsLg;  // LDS sums of one direct-addressed table
 constexpr int kSamples = 16384;
+constexpr int kFewKeys = 1500;                    // different keys of the sample, at most
+constexpr int64_t kFewSlots = int64_t{1} << 16;   // slots of the table in HBM
 
-__device__ __forceinline__ bool plan_moves(const GbPlan *p) { return !p || p->mode == kGbHash || p->mode == kGbRange; }
+__device__ __forceinline__ bool plan_moves(const GbPlan *p) {
+  return !p || plan_mode(p) == kGbHash || plan_mode(p) == kGbRange;
+}
 
 // Bucket of a key for both moves: 12 bits, the first move takes the upper 6.
 // (Wave-uniform choice; kernels that never see a plan compile it out.)
@@ -248,7 +255,7 @@ __global__ __launch_bounds__(kAggBlock) void k_bucket_groups(const int64_t *keys
                                                             const int32_t *pos, int bps, int64_t *out_keys,
                                                             int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups,
                                                             uint32_t *err, const GbPlan *plan) {
-  if (plan && plan->mode != kGbHash) return;
+  if (plan && plan_mode(plan) != kGbHash) return;
   __shared__ uint64_t s_key[kAggSlots];
   __shared__ uint64_t s_sum[kAggSlots];
   __shared__ int32_t s_w[kAggBlock / kWave];
@@ -653,7 +660,7 @@ __device__ __forceinline__ uint32_t narrow_empty(int b) { return static_cast<uin
 __global__ __launch_bounds__(kAggBlock) void k_narrow_groups(const uint64_t *pairs, const int32_t *pos2,
                                                             int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
                                                             int64_t *d_ngroups, uint32_t *err, const GbPlan *plan) {
-  if (plan && plan->mode != kGbHash) return;
+  if (plan && plan_mode(plan) != kGbHash) return;
   __shared__ uint32_t s_h[kAggSlots];
   __shared__ uint64_t s_sum[kAggSlots];
   __shared__ int32_t s_w[kAggBlock / kWave];
@@ -836,8 +843,17 @@ pyst_status pair_groupby(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const int6
 constexpr int kRangeBlocks = 2048, kRangeItems = 8;
 __global__ __launch_bounds__(256) void k_key_range(const void *key, int key64, const int32_t *sel, const int64_t *d_nsel,
                                                    int64_t n, int64_t *lo_out, int64_t *hi_out, int64_t *samples,
-                                                   uint32_t *err) {
+                                                   GroupDev few, uint64_t *few_status, int64_t few_words, uint32_t *err) {
   __shared__ int64_t s_lo[4], s_hi[4];
+  if (few.slots) {  // the table of kGbFew starts empty
+    const int64_t g0 = int64_t{blockIdx.x} * 256 + threadIdx.x, step = int64_t{gridDim.x} * 256;
+    if (g0 == 0) few.hdr[0] = few.cap_alloc;
+    for (int64_t i = g0; i < few.cap_alloc; i += step) {
+      few.slots[2 * i] = static_cast<uint64_t>(kEmpty64);
+      few.slots[2 * i + 1] = 0;
+    }
+    for (int64_t i = g0; i < few_words; i += step) few_status[i] = 0;
+  }
   int64_t cnt = count_of(d_nsel, n);
   if (cnt > n) cnt = n;
   const int64_t gtid = int64_t{blockIdx.x} * 256 + threadIdx.x;
@@ -896,17 +912,17 @@ __global__ __launch_bounds__(256) void k_key_range(const void *key, int key64, c
 // wait for one block each; such keys take hash buckets.
 __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64_t *lo_in, const int64_t *hi_in,
                                                       int nblocks, const int64_t *samples, const int64_t *d_nsel,
-                                                      int64_t n, int64_t small_max, int allow_range, int otherwise,
-                                                      uint64_t *status, int64_t *d_ngroups) {
+                                                      int64_t n, int64_t small_max, int allow_range, int allow_few,
+                                                      int otherwise, uint64_t *status, int64_t *d_ngroups) {
   __shared__ int32_t s_c[kAggBuckets];
   __shared__ int64_t s_lo[kAggBlock / kWave], s_hi[kAggBlock / kWave];
-  __shared__ int32_t s_crowded;
+  __shared__ int32_t s_crowded, s_distinct;
   const int tid = static_cast<int>(threadIdx.x);
   for (int i = tid; i < kAggBuckets; i += kAggBlock) {
     s_c[i] = 0;
     status[i] = 0;
   }
-  if (tid == 0) s_crowded = 0;
+  if (tid == 0) s_crowded = s_distinct = 0;
   int64_t lo = INT64_MAX, hi = INT64_MIN;
   for (int i = tid; i < nblocks; i += kAggBlock) {
     lo = lo_in[i] < lo ? lo_in[i] : lo;
@@ -946,6 +962,21 @@ __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64
     __syncthreads();
     if (s_crowded) mode = otherwise;
   }
+  if (mode == otherwise && allow_few) {  // block-uniform: different keys of the sample, by their hash bits
+    constexpr int kBits = kAggBuckets * 32;
+    __syncthreads();
+    for (int i = tid; i < kAggBuckets; i += kAggBlock) s_c[i] = 0;
+    __syncthreads();
+    int32_t news = 0;
+    for (int i = tid; i < kSamples; i += kAggBlock) {
+      const uint32_t h = static_cast<uint32_t>(agg_hash(samples[i])) & (kBits - 1);
+      news += !(atomicOr(&s_c[h >> 5], 1 << (h & 31)) >> (h & 31) & 1);
+    }
+    news = wave_sum(news);
+    if (lane_id() == 0) atomicAdd(&s_distinct, news);
+    __syncthreads();
+    if (s_distinct <= kFewKeys) mode = kGbFew;
+  }
   if (tid == 0) {
     int64_t cnt = count_of(d_nsel, n);
     plan->kmin = lo;
@@ -954,6 +985,8 @@ __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64
     plan->mode = mode;
     plan->shift = shift;
     plan->sort_count = 0;
+    plan->few_failed = 0;
+    plan->otherwise = otherwise;
     plan->ticket = 0;
     *d_ngroups = 0;
   }
@@ -1184,7 +1217,7 @@ pyst_status launch_direct_groups(pyst_ctx *ctx, GbPlan *plan, uint64_t *status, 
 
 // The group count of the hash modes is what remains to be sorted.
 __global__ void k_gb_sort_count(GbPlan *plan, const int64_t *d_ngroups) {
-  plan->sort_count = plan->mode == kGbHash || plan->mode == kGbTable ? *d_ngroups : 0;
+  plan->sort_count = plan_mode(plan) == kGbSmall || plan_mode(plan) == kGbRange ? 0 : *d_ngroups;
 }
 
 // Small scratch of a planned group-by: the plan, the look-back words, the
@@ -1208,7 +1241,7 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
   Scratch ps(ctx, stream);
   {
     const int64_t cap_alloc = hash_buckets ? 0 : table_capacity_host(bound, max_load);
-    Scratch table(ctx, stream), ws(ctx, stream), ws2(ctx, stream);
+    Scratch table(ctx, stream), ws(ctx, stream), ws2(ctx, stream), few(ctx, stream);
     if (!hash_buckets) table.alloc(group_bytes(cap_alloc));
     const size_t wsb = narrow ? narrow_groupby_bytes(n) : static_cast<size_t>(n) * 16;
     hash_buckets ? ws.alloc(wsb) : ws.try_alloc(wsb);
@@ -1219,21 +1252,26 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
     const int64_t *count = d_nsel;
     uint64_t *status = nullptr;
     pyst_status st;
+    const int64_t few_words = group_compact_words(kFewSlots);
+    if (ps.p) few.try_alloc(group_bytes(kFewSlots) + few_words * sizeof(uint64_t));
     if (ps.p) {
       plan = ps.as<GbPlan>();
       count = &plan->count;
       status = reinterpret_cast<uint64_t *>(static_cast<char *>(ps.p) + 256);
       int64_t *lo = reinterpret_cast<int64_t *>(status + kAggBuckets), *hi = lo + kRangeBlocks,
               *samples = hi + kRangeBlocks;
+      const GroupDev fg = few.p ? group_view(few.p, kFewSlots) : GroupDev{};
+      uint64_t *few_status = few.p ? reinterpret_cast<uint64_t *>(static_cast<char *>(few.p) + group_bytes(kFewSlots)) : nullptr;
       const int rblocks = static_cast<int>(std::min<int64_t>(kRangeBlocks, ceil_div(n, 256 * kRangeItems)));
       // the blocks' partial arrays of kGbSmall take the memory of the moves, or of the table
       const size_t room = moves ? static_cast<size_t>(n) * 16 : group_bytes(cap_alloc);
       const int parts = std::max(1, std::min(512, 2 * ctx_num_cus(ctx)));
       const int64_t small_max = std::min<int64_t>(kDirectSlots, static_cast<int64_t>(room / (parts * 9)));
-      k_key_range<<<rblocks, 256, 0, stream>>>(key->data, k64, sel, d_nsel, n, lo, hi, samples, err);
+      k_key_range<<<rblocks, 256, 0, stream>>>(key->data, k64, sel, d_nsel, n, lo, hi, samples, fg, few_status,
+                                               few_words, err);
       PYST_LAUNCH_CHECK("k_key_range");
       k_gb_plan<<<1, kAggBlock, 0, stream>>>(plan, lo, hi, rblocks, samples, d_nsel, n, small_max, moves,
-                                             hash_buckets ? kGbHash : kGbTable, status, d_ngroups);
+                                             few.p != nullptr, hash_buckets ? kGbHash : kGbTable, status, d_ngroups);
       PYST_LAUNCH_CHECK("k_gb_plan");
       uint64_t *psum = moves ? ws.as<uint64_t>() : table.as<uint64_t>();
       uint8_t *pflag = reinterpret_cast<uint8_t *>(psum + parts * small_max);
@@ -1242,6 +1280,11 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
       k_small_groups<<<static_cast<unsigned>(ceil_div(std::max<int64_t>(small_max, 1), kWave)), kAggBlock, 0,
                        stream>>>(plan, psum, pflag, parts, status, out_keys, out_sums, out_cap, d_ngroups, err);
       PYST_LAUNCH_CHECK("k_small_groups");
+      if (few.p) {
+        st = table_groupby(ctx, fg, key, val, sel, d_nsel, 0, 0.5, out_keys, out_sums, out_cap, d_ngroups, plan, kGbFew,
+                           few_status, stream);
+        if (st != PYST_OK) return st;
+      }
     } else if (hash_buckets) {  // no room for a plan: hash buckets for any keys
       if ((st = fill_u64(d_ngroups, 1, 0, stream)) != PYST_OK) return st;
       if (!count) {
@@ -1272,7 +1315,7 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
     if (!hash_buckets) {
       const GroupDev g = group_view(table.p, cap_alloc);
       st = table_groupby(ctx, g, key, val, sel, d_nsel, max_groups, max_load, out_keys, out_sums, out_cap, d_ngroups,
-                         plan, stream);
+                         plan, kGbTable, nullptr, stream);
       if (st != PYST_OK) return st;
     }
   }

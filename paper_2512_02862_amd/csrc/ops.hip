@@ -915,35 +915,118 @@ __global__ __launch_bounds__(BLOCK) void k_join_probe(const void *key, const int
 // ============================================================== group-by SUM
 // 16-byte slots {int64 key, uint64 sum}; EMPTY key = INT64_MIN.
 __global__ void k_gb_init(GroupDev g, const int64_t *d_nsel, int64_t n, int64_t max_groups, double max_load,
-                          const GbPlan *plan) {
-  if (plan && plan->mode != kGbTable) return;
+                          const GbPlan *plan, int mode, uint64_t *status, int64_t nstatus) {
+  if (plan && plan_mode(plan) != mode) return;
   int64_t cnt = count_of(d_nsel, n);
   if (max_groups > 0 && max_groups < cnt) cnt = max_groups;
   const int64_t cap = table_capacity(cnt, max_load, g.cap_alloc);
   if (blockIdx.x == 0 && threadIdx.x == 0) g.hdr[0] = cap;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < cap; i += (int64_t)gridDim.x * blockDim.x) {
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = i0; i < cap; i += step) {
     g.slots[2 * i] = static_cast<uint64_t>(kEmpty64);
     g.slots[2 * i + 1] = 0;
   }
+  for (int64_t i = i0; i < nstatus; i += step) status[i] = 0;
 }
 
-__global__ __launch_bounds__(256) void k_gb_insert(const void *key, int key64, const void *val, int val64,
-                                                   const int32_t *sel, const int64_t *d_nsel, int64_t n, GroupDev g,
-                                                   uint32_t *err, int skip_empty, const GbPlan *plan) {
-  if (plan && plan->mode != kGbTable) return;
+// Rows added to a table in HBM, a block's rows first to an LDS table of its own:
+// keys that repeat within a block cost LDS operations, and only the block's
+// distinct keys go to the L2, whose atomics retire at 23e9/s when they are
+// spread out and one by one when they meet in a word.  A row that finds no place
+// near its LDS slot goes to the table directly, and a block whose rows hardly
+// repeat (more than half of them claimed a slot) stops using its LDS table.
+// Two blocks per CU; the rows are read once, coalesced.
+// Into few groups every add met in the same L2 words: 195k rows into 5 int32 keys
+// 801 -> 20 us with the whole call, 13.4M rows into 4 int64 keys 6876 -> 141 us
+// (this kernel 57 us).  Where a block's keys hardly repeat it costs: 100k rows into
+// 5000 keys 14 -> 18 us.
+__device__ __forceinline__ bool few_full(GbPlan *plan) {
+  return __hip_atomic_load(&plan->few_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+constexpr int kPreSlots = 4096, kPreProbes = 8, kPreItems = 4;
+constexpr int64_t kFewProbes = 256;  // a kGbFew table without a place this near counts as full
+__global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key64, const void *val, int val64,
+                                                       const int32_t *sel, const int64_t *d_nsel, int64_t n, GroupDev g,
+                                                       uint32_t *err, int skip_empty, GbPlan *plan, int mode) {
   // skip_empty: the input is a pair buffer whose unused slots hold the EMPTY key
+  constexpr int U = kPreItems;
+  constexpr unsigned long long kE = static_cast<unsigned long long>(kEmpty64);
+  __shared__ unsigned long long s_key[kPreSlots], s_sum[kPreSlots];
+  __shared__ int32_t s_claimed;
+  __shared__ bool s_stop;
+  if (plan && plan_mode(plan) != mode) return;
   int64_t cnt = count_of(d_nsel, n);
   if (cnt > n) cnt = n;
+  const int tid = static_cast<int>(threadIdx.x);
+  const int64_t tiles = (cnt + 1023) / 1024, per = (tiles + gridDim.x - 1) / gridDim.x * 1024;
+  const int64_t lo = per * blockIdx.x, hi = lo + per < cnt ? lo + per : cnt;
+  if (lo >= hi) return;  // block-uniform
   const int64_t mask = g.hdr[0] - 1;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < cnt; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t row = row_of(sel, i);
-    const int64_t k = load_as_i64(key, key64, row);
-    if (k == kEmpty64) {
-      if (!skip_empty) latch(err, kErrKey);
-      continue;
+  const bool few = plan && mode == kGbFew;
+  const int64_t probes = few ? kFewProbes : mask + 1;
+  int nslots = 2048;  // at least two slots a row where a block has few rows
+  while (nslots < kPreSlots && nslots < 2 * per) nslots *= 2;
+  for (int i = tid; i < nslots; i += 1024) {
+    s_key[i] = kE;
+    s_sum[i] = 0;
+  }
+  if (tid == 0) s_claimed = 0;
+  __syncthreads();
+  bool direct = false, full = false;
+  for (int64_t t0 = lo; t0 < hi; t0 += 1024 * U) {  // block-uniform
+    int64_t row[U], k[U], v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) row[u] = t0 + u * 1024 + tid < hi ? t0 + u * 1024 + tid : hi - 1;
+    if (sel) load_items<U>(sel, 0, row, cnt, row);
+    load_items<U>(key, key64, row, n, k);
+    load_items<U>(val, val64, row, n, v);
+    int claimed = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (t0 + u * 1024 + tid >= hi) continue;
+      if (k[u] == kEmpty64) {
+        if (!skip_empty) latch(err, kErrKey);
+        continue;
+      }
+      bool placed = false;
+      if (!direct) {
+        uint32_t s = static_cast<uint32_t>(table_hash64(k[u]) >> 40) & (nslots - 1);
+        for (int probes = 0; probes < kPreProbes; ++probes) {
+          unsigned long long c = s_key[s];
+          if (c == kE) {
+            c = atomicCAS(&s_key[s], kE, static_cast<unsigned long long>(k[u]));
+            claimed += c == kE;
+          }
+          if (c == kE || c == static_cast<unsigned long long>(k[u])) {
+            atomicAdd(&s_sum[s], static_cast<unsigned long long>(v[u]));
+            placed = true;
+            break;
+          }
+          s = (s + 1) & (nslots - 1);
+        }
+      }
+      if (!placed && !group_add(g.slots, mask, k[u], static_cast<uint64_t>(v[u]), probes)) full = true;
     }
-    const int64_t v = load_as_i64(val, val64, row);
-    if (!group_add(g.slots, mask, k, static_cast<uint64_t>(v))) latch(err, kErrTableFull);
+    if (!direct && t0 + 1024 * U < hi) {  // another tile follows
+      claimed = wave_sum(claimed);
+      if (lane_id() == 0 && claimed) atomicAdd(&s_claimed, claimed);
+      if (tid == 0) s_stop = few && few_full(plan);
+      __syncthreads();
+      direct = s_claimed > (t0 + 1024 * U - lo) / 2;
+      const bool stop = s_stop;
+      __syncthreads();
+      if (stop) break;  // block-uniform: the rows will be grouped another way
+    } else if (few && (full || few_full(plan))) {
+      break;  // no barrier follows within the loop
+    }
+    if (few && full) plan->few_failed = 1;
+  }
+  __syncthreads();
+  for (int i = tid; i < nslots; i += 1024)
+    if (s_key[i] != kE && !group_add(g.slots, mask, static_cast<int64_t>(s_key[i]), s_sum[i], probes)) full = true;
+  if (full) {
+    if (few) plan->few_failed = 1;  // more groups than the sample promised
+    else latch(err, kErrTableFull);
   }
 }
 
@@ -951,10 +1034,10 @@ template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void k_gb_compact(GroupDev g, int64_t *out_keys, int64_t *out_sums,
                                                      int64_t out_cap, int64_t *d_ngroups, uint64_t *status,
                                                      unsigned long long *ticket, int64_t ntiles, uint32_t *err,
-                                                     const GbPlan *plan) {
+                                                     const GbPlan *plan, int mode) {
   constexpr int NW = BLOCK / kWave;
   constexpr int64_t TILE = int64_t{BLOCK} * ITEMS;
-  if (plan && plan->mode != kGbTable) return;
+  if (plan && plan_mode(plan) != mode) return;
   __shared__ int64_t s_tile, s_prefix;
   __shared__ int32_t s_cnt[NW];
   if (threadIdx.x == 0) s_tile = static_cast<int64_t>(atomicAdd(ticket, 1ull));
@@ -1003,43 +1086,80 @@ __global__ __launch_bounds__(BLOCK) void k_gb_compact(GroupDev g, int64_t *out_k
   }
 }
 
-pyst_status group_compact(pyst_ctx *ctx, const GroupDev &g, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
-                          int64_t *d_ngroups, hipStream_t stream, const GbPlan *plan) {
-  constexpr int BLOCK = 256, ITEMS = 8;
-  const int64_t ntiles = std::max<int64_t>(1, ceil_div(g.cap_alloc, int64_t{BLOCK} * ITEMS));
-  Scratch sc(ctx, (ntiles + 1) * sizeof(uint64_t), stream);
-  if (!sc.p) return set_error(PYST_ERR_NOMEM, "group compaction: arena exhausted");
-  pyst_status st = fill_u64(sc.p, ntiles + 1, 0, stream);
-  if (st != PYST_OK) return st;
-  uint64_t *status = sc.as<uint64_t>();
-  k_gb_compact<BLOCK, ITEMS><<<static_cast<unsigned>(ntiles), BLOCK, 0, stream>>>(
+constexpr int kCompactBlock = 256, kCompactItems = 8;
+static int64_t compact_tiles(const GroupDev &g) {
+  return std::max<int64_t>(1, ceil_div(g.cap_alloc, int64_t{kCompactBlock} * kCompactItems));
+}
+
+// status: compact_tiles + 1 cleared words.
+static pyst_status launch_compact(pyst_ctx *ctx, const GroupDev &g, uint64_t *status, int64_t *out_keys,
+                                  int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, const GbPlan *plan, int mode,
+                                  hipStream_t stream) {
+  const int64_t ntiles = compact_tiles(g);
+  k_gb_compact<kCompactBlock, kCompactItems><<<static_cast<unsigned>(ntiles), kCompactBlock, 0, stream>>>(
       g, out_keys, out_sums, out_cap, d_ngroups, status, reinterpret_cast<unsigned long long *>(status + ntiles),
-      ntiles, ctx_err_word(ctx), plan);
+      ntiles, ctx_err_word(ctx), plan, mode);
   PYST_LAUNCH_CHECK("k_gb_compact");
   return PYST_OK;
 }
 
-pyst_status group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int64_t max_groups, double max_load,
-                       hipStream_t stream, const GbPlan *plan) {
+pyst_status group_compact(pyst_ctx *ctx, const GroupDev &g, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
+                          int64_t *d_ngroups, hipStream_t stream) {
+  const int64_t ntiles = compact_tiles(g);
+  Scratch sc(ctx, (ntiles + 1) * sizeof(uint64_t), stream);
+  if (!sc.p) return set_error(PYST_ERR_NOMEM, "group compaction: arena exhausted");
+  pyst_status st = fill_u64(sc.p, ntiles + 1, 0, stream);
+  if (st != PYST_OK) return st;
+  return launch_compact(ctx, g, sc.as<uint64_t>(), out_keys, out_sums, out_cap, d_ngroups, nullptr, 0, stream);
+}
+
+static pyst_status launch_group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int64_t max_groups,
+                                     double max_load, const GbPlan *plan, int mode, uint64_t *status, int64_t nstatus,
+                                     hipStream_t stream) {
   const int blocks = static_cast<int>(std::min<int64_t>(ceil_div(g.cap_alloc, 256), 4096));
-  k_gb_init<<<blocks, 256, 0, stream>>>(g, d_nsel, n, max_groups, max_load, plan);
+  k_gb_init<<<blocks, 256, 0, stream>>>(g, d_nsel, n, max_groups, max_load, plan, mode, status, nstatus);
   PYST_LAUNCH_CHECK("k_gb_init");
   return PYST_OK;
 }
 
+pyst_status group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int64_t max_groups, double max_load,
+                       hipStream_t stream) {
+  return launch_group_init(g, d_nsel, n, max_groups, max_load, nullptr, 0, nullptr, 0, stream);
+}
+
+// Up to two blocks of 1024 threads per CU, at least a row a thread.
+pyst_status group_insert(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val, const int32_t *sel,
+                         const int64_t *d_nsel, int skip_empty, GbPlan *plan, int mode, hipStream_t stream) {
+  if (key->n == 0) return PYST_OK;
+  const int blocks = grid_for(ctx, key->n, 1024, 2);
+  k_gb_insert<<<blocks, 1024, 0, stream>>>(key->data, key->dtype == PYST_I64, val->data, val->dtype == PYST_I64, sel,
+                                          d_nsel, key->n, g, ctx_err_word(ctx), skip_empty, plan, mode);
+  PYST_LAUNCH_CHECK("k_gb_insert");
+  return PYST_OK;
+}
+
+int64_t group_compact_words(int64_t cap_alloc) {
+  GroupDev g{};
+  g.cap_alloc = cap_alloc;
+  return compact_tiles(g) + 1;
+}
+
 pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val,
                           const int32_t *sel, const int64_t *d_nsel, int64_t max_groups, double max_load,
-                          int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups,
-                          const GbPlan *plan, hipStream_t stream) {
-  pyst_status st = group_init(g, d_nsel, key->n, max_groups, max_load, stream, plan);
-  if (st != PYST_OK) return st;
-  if (key->n > 0) {
-    const int blocks = grid_for(ctx, key->n, 256, 8);
-    k_gb_insert<<<blocks, 256, 0, stream>>>(key->data, key->dtype == PYST_I64, val->data, val->dtype == PYST_I64, sel,
-                                            d_nsel, key->n, g, ctx_err_word(ctx), 0, plan);
-    PYST_LAUNCH_CHECK("k_gb_insert");
+                          int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, GbPlan *plan,
+                          int mode, uint64_t *few_status, hipStream_t stream) {
+  Scratch sc(ctx, stream);
+  uint64_t *status = few_status;
+  pyst_status st = PYST_OK;
+  if (!status) {
+    const int64_t words = group_compact_words(g.cap_alloc);
+    if (!sc.alloc(words * sizeof(uint64_t))) return set_error(PYST_ERR_NOMEM, "group compaction: arena exhausted");
+    status = sc.as<uint64_t>();
+    st = launch_group_init(g, d_nsel, key->n, max_groups, max_load, plan, mode, status, words, stream);
   }
-  return group_compact(ctx, g, out_keys, out_sums, out_cap, d_ngroups, stream, plan);
+  if (st == PYST_OK) st = group_insert(ctx, g, key, val, sel, d_nsel, 0, plan, mode, stream);
+  if (st != PYST_OK) return st;
+  return launch_compact(ctx, g, status, out_keys, out_sums, out_cap, d_ngroups, plan, mode, stream);
 }
 
 // ============================================================== gather (materialize)
@@ -1590,7 +1710,7 @@ pyst_status pyst_groupby_sum(pyst_ctx *ctx, const pyst_col *key, const pyst_col 
     Scratch mem(ctx, group_bytes(cap_alloc), stream);
     if (!mem.p) return set_error(PYST_ERR_NOMEM, "pyst_groupby_sum: arena exhausted");
     pyst_status st = table_groupby(ctx, group_view(mem.p, cap_alloc), key, val, sel, d_nsel, max_groups, max_load,
-                                   out_keys, out_sums, out_cap, d_ngroups, nullptr, stream);
+                                   out_keys, out_sums, out_cap, d_ngroups, nullptr, kGbTable, nullptr, stream);
     if (st != PYST_OK || !sort_by_key) return st;
   }
   return sort_pairs_by_key(ctx, out_keys, out_sums, d_ngroups, out_cap, key->dtype == PYST_I64 ? 64 : 32, stream);

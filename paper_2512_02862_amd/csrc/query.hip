@@ -521,13 +521,8 @@ pyst_status agg_finish(pyst_ctx *ctx, const pyst_plan *plan, const QueryShape &q
     if (!gm) return set_error(PYST_ERR_NOMEM, "pyst_query: arena exhausted (group table)");
     GroupDev g = group_view(gm, cap);
     st = group_init(g, s->po.count, s->po.cap, 0, plan->group_max_load, stream);
-    if (st == PYST_OK) {
-      const int blocks = grid_for(ctx, s->po.cap, 256, 8);
-      k_gb_insert<<<blocks, 256, 0, stream>>>(s->po.keys, 1, s->po.vals, 1, nullptr, s->po.count, s->po.cap, g,
-                                              ctx_err_word(ctx), 0, nullptr);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) st = hip_error(e, "k_gb_insert");
-    }
+    const pyst_col pk{s->po.keys, s->po.cap, PYST_I64, 0}, pv{s->po.vals, s->po.cap, PYST_I64, 0};
+    if (st == PYST_OK) st = group_insert(ctx, g, &pk, &pv, nullptr, s->po.count, 1, nullptr, 0, stream);
     if (st == PYST_OK) st = group_compact(ctx, g, out_keys, out_sums, out_cap, d_ngroups, stream);
     ctx_free(ctx, gm, stream);
   }

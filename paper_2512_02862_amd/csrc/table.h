@@ -39,7 +39,7 @@ struct GroupDev {
 
 // How the rows of a group-by are grouped: chosen on the device from the keys'
 // range (see the planned group-by).  Kernels of the other modes return at once.
-enum : int32_t { kGbHash = 0, kGbSmall = 1, kGbRange = 2, kGbTable = 3 };
+enum : int32_t { kGbHash = 0, kGbSmall = 1, kGbRange = 2, kGbTable = 3, kGbFew = 4 };
 struct GbPlan {
   int64_t kmin;
   uint64_t range;      // greatest - least key + 1; 0 without rows
@@ -47,8 +47,14 @@ struct GbPlan {
   int64_t sort_count;  // groups that still need sorting (0 where they come out in key order)
   int32_t mode;
   int32_t shift;       // kGbRange: bucket = (key - kmin) >> shift
+  int32_t few_failed;  // kGbFew: its table had no slot for a group, the mode is `otherwise`
+  int32_t otherwise;
   unsigned long long ticket;
 };
+
+__device__ __forceinline__ int32_t plan_mode(const GbPlan *p) {
+  return p->mode == kGbFew && p->few_failed ? p->otherwise : p->mode;
+}
 
 __host__ __device__ inline int64_t next_pow2(int64_t x) {
   int64_t p = 1;
@@ -100,10 +106,11 @@ inline GroupDev group_view(void *mem, int64_t cap) {
   return g;
 }
 
-// Add v to the group of key k (inserting the key if absent).  False: table full.
-__device__ __forceinline__ bool group_add(uint64_t *slots, int64_t mask, int64_t k, uint64_t v) {
+// Add v to the group of key k (inserting the key if absent).  False: table full,
+// or no place within the first `probes` slots.
+__device__ __forceinline__ bool group_add(uint64_t *slots, int64_t mask, int64_t k, uint64_t v, int64_t probes) {
   int64_t s = static_cast<int64_t>(table_hash64(k)) & mask;
-  for (int64_t step = 0; step <= mask; ++step) {
+  for (int64_t step = 0; step < probes; ++step) {
     uint64_t cur = slots[2 * s];
     if (static_cast<int64_t>(cur) == kEmpty64) {
       const uint64_t old = atomicCAS(reinterpret_cast<unsigned long long *>(&slots[2 * s]),
@@ -118,18 +125,26 @@ __device__ __forceinline__ bool group_add(uint64_t *slots, int64_t mask, int64_t
   }
   return false;
 }
+__device__ __forceinline__ bool group_add(uint64_t *slots, int64_t mask, int64_t k, uint64_t v) {
+  return group_add(slots, mask, k, v, mask + 1);
+}
 
 // Host helpers implemented in ops.hip / sort.hip.
 pyst_status table_init(const TableDev &t, const int64_t *d_nsel, int64_t n, double max_load, hipStream_t stream);
 pyst_status group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int64_t max_groups, double max_load,
-                       hipStream_t stream, const GbPlan *plan = nullptr);
+                       hipStream_t stream);
+pyst_status group_insert(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val, const int32_t *sel,
+                         const int64_t *d_nsel, int skip_empty, GbPlan *plan, int mode, hipStream_t stream);
 pyst_status group_compact(pyst_ctx *ctx, const GroupDev &g, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
-                          int64_t *d_ngroups, hipStream_t stream, const GbPlan *plan = nullptr);
-// Group-by of columns through the table `g` in HBM (with a plan: only in mode kGbTable).
+                          int64_t *d_ngroups, hipStream_t stream);
+// Group-by of columns through the table `g` in HBM (with a plan: only in `mode`).
+// few_status: in mode kGbFew, the table is empty and these group_compact_words
+// are cleared already.
+int64_t group_compact_words(int64_t cap_alloc);
 pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val,
                           const int32_t *sel, const int64_t *d_nsel, int64_t max_groups, double max_load,
-                          int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups,
-                          const GbPlan *plan, hipStream_t stream);
+                          int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, GbPlan *plan,
+                          int mode, uint64_t *few_status, hipStream_t stream);
 pyst_status filter_impl(pyst_ctx *ctx, const PredSet &ps, int64_t n, int32_t *sel_out, int64_t *d_nsel,
                         hipStream_t stream);
 pyst_status scan_excl_i32(pyst_ctx *ctx, const int32_t *in, int32_t *out, int64_t len, int64_t *d_total,

@@ -116,3 +116,29 @@ def test_unbounded_groups(gpu, kt, span, budget):
     np.testing.assert_array_equal(gk[o], wk)
     np.testing.assert_array_equal(gs[o], ws)
     c.close()
+
+
+@pytest.mark.parametrize("kt", [np.int32, np.int64])
+@pytest.mark.parametrize("n", [1, 1023, 4097, 200_001, (1 << 20) + 1, 3_000_000])
+@pytest.mark.parametrize("groups", [1, 5, 1400, 4096, 30_000])
+def test_few_keys_over_a_wide_range(gpu, ctx, kt, n, groups):
+    # below 2^20 rows the table behind per-block LDS tables, above it the plan's choice
+    rng = np.random.default_rng(n + groups)
+    info = np.iinfo(kt)
+    pool = rng.integers(info.min + 1, info.max, groups, dtype=kt, endpoint=True)
+    pool[0], pool[-1] = info.min + 1, info.max
+    k = pool[rng.integers(0, groups, n)]
+    v = rng.integers(-2**62, 2**62, n)
+    check(gpu, ctx, k, v)
+    if n > 2:
+        check(gpu, ctx, k, v, np.arange(1, n, 2, dtype=np.int32))
+
+
+@pytest.mark.parametrize("unbounded", [False, True])
+def test_sample_promises_too_few_keys(gpu, ctx, unbounded):
+    # 19 rows of 20 in 100 keys, the rest all different: the sample finds under 1500 keys, the
+    # table of 2^16 slots runs full, and the rows go to hash buckets (or the table in HBM)
+    rng = np.random.default_rng(3)
+    n = (1 << 24) + 7 if unbounded else 4_000_000
+    k = np.where(rng.random(n) < 0.95, rng.integers(0, 100, n) << 50, rng.integers(-2**62, 2**62, n))
+    check(gpu, ctx, k, rng.integers(-2**62, 2**62, n), max_groups=0 if unbounded else n)
