@@ -575,7 +575,8 @@ pyst_status scan_excl_i32(pyst_ctx *ctx, const int32_t *in, int32_t *out, int64_
 // (a later launch) then sees.
 constexpr uint64_t kEmptySlot = static_cast<uint32_t>(kEmpty32);
 
-__global__ void k_table_init(TableDev t, const int64_t *d_nsel, int64_t n, double max_load) {
+__global__ void k_table_init(TableDev t, const int64_t *d_nsel, int64_t n, double max_load, const JoinPlan *plan) {
+  if (plan && plan->direct) return;
   const int64_t cnt = count_of(d_nsel, n);
   const int64_t cap = table_capacity(cnt, max_load, t.cap_alloc);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -605,7 +606,8 @@ constexpr int kBuildItems = 4;
 template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void k_join_build(const int32_t *key, const int32_t *payload, const int32_t *sel,
                                                       const int64_t *d_nsel, int64_t n, TableDev t, int unique,
-                                                      uint32_t *err) {
+                                                      uint32_t *err, const JoinPlan *plan) {
+  if (plan && plan->direct) return;
   const int64_t cnt = count_of(d_nsel, n);
   const int64_t mask = t.hdr[0] - 1;
   auto *slots = reinterpret_cast<unsigned long long *>(t.slots);
@@ -676,7 +678,8 @@ __device__ __forceinline__ bool join_key(const void *key, int key64, int64_t row
 template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void k_join_build_wide(const void *key, int key64, const void *payload, int pay64,
                                                            const int32_t *sel, const int64_t *d_nsel, int64_t n,
-                                                           TableDev t, int unique, uint32_t *err) {
+                                                           TableDev t, int unique, uint32_t *err, const JoinPlan *plan) {
+  if (plan && plan->direct) return;
   const int64_t cnt = count_of(d_nsel, n);
   const int64_t mask = t.hdr[0] - 1;
   auto *slots = reinterpret_cast<unsigned long long *>(t.slots);  // slot s: words 2s (key), 2s + 1 (payload)
@@ -805,7 +808,8 @@ __global__ __launch_bounds__(BLOCK) void k_join_probe(const void *key, const int
                                                      const int64_t *d_nsel, int64_t n, TableDev t, int unique,
                                                      int32_t *out_row, PayT *out_pay, int64_t out_cap, int64_t *d_nout,
                                                      uint64_t *status, unsigned long long *ticket, int64_t ntiles,
-                                                     uint32_t *err) {
+                                                     uint32_t *err, const JoinPlan *plan) {
+  if (plan && plan->direct) return;
   constexpr int NW = BLOCK / kWave;
   constexpr int64_t TILE = int64_t{BLOCK} * ITEMS;
   __shared__ int64_t s_tile, s_prefix;
@@ -1313,9 +1317,10 @@ int grid_for(pyst_ctx *ctx, int64_t work, int block, int per_cu) {
   return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want, int64_t{ctx_num_cus(ctx)} * per_cu)));
 }
 
-pyst_status table_init(const TableDev &t, const int64_t *d_nsel, int64_t n, double max_load, hipStream_t stream) {
+pyst_status table_init(const TableDev &t, const int64_t *d_nsel, int64_t n, double max_load, hipStream_t stream,
+                       const JoinPlan *plan) {
   const int blocks = static_cast<int>(std::min<int64_t>(ceil_div(t.cap_alloc, 256), 4096));
-  k_table_init<<<blocks, 256, 0, stream>>>(t, d_nsel, n, max_load);
+  k_table_init<<<blocks, 256, 0, stream>>>(t, d_nsel, n, max_load, plan);
   PYST_LAUNCH_CHECK("k_table_init");
   return PYST_OK;
 }
@@ -1330,18 +1335,18 @@ static int join_slot_bytes(const pyst_col *key, const pyst_col *payload) {
 // length, or null for row ids); t.slot_bytes is join_slot_bytes of the columns.
 pyst_status launch_join_build(pyst_ctx *ctx, const TableDev &t, const pyst_col *key, const pyst_col *payload,
                               const int32_t *sel, const int64_t *d_nsel, double max_load, int unique,
-                              hipStream_t stream) {
-  pyst_status st = table_init(t, d_nsel, key->n, max_load, stream);
+                              hipStream_t stream, const JoinPlan *plan = nullptr) {
+  pyst_status st = table_init(t, d_nsel, key->n, max_load, stream, plan);
   if (st != PYST_OK || key->n == 0) return st;
   const int blocks = grid_for(ctx, ceil_div(key->n, int64_t{kBuildItems}), 256, 8);
   if (t.slot_bytes == 16) {
     k_join_build_wide<256, kBuildItems><<<blocks, 256, 0, stream>>>(
         key->data, key->dtype == PYST_I64, payload ? payload->data : nullptr, payload && payload->dtype == PYST_I64,
-        sel, d_nsel, key->n, t, unique, ctx_err_word(ctx));
+        sel, d_nsel, key->n, t, unique, ctx_err_word(ctx), plan);
   } else {
     k_join_build<256, kBuildItems><<<blocks, 256, 0, stream>>>(
         static_cast<const int32_t *>(key->data), payload ? static_cast<const int32_t *>(payload->data) : nullptr, sel,
-        d_nsel, key->n, t, unique, ctx_err_word(ctx));
+        d_nsel, key->n, t, unique, ctx_err_word(ctx), plan);
   }
   PYST_LAUNCH_CHECK("k_join_build");
   return PYST_OK;
@@ -1350,7 +1355,7 @@ pyst_status launch_join_build(pyst_ctx *ctx, const TableDev &t, const pyst_col *
 template <typename PayT>
 pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, const pyst_col *key, const int32_t *sel,
                               const int64_t *d_nsel, int32_t *out_row, PayT *out_pay, int64_t out_cap,
-                              int64_t *d_nout, hipStream_t stream) {
+                              int64_t *d_nout, hipStream_t stream, const JoinPlan *plan = nullptr) {
   constexpr int BLOCK = 256, ITEMS = 8;
   const int64_t ntiles = std::max<int64_t>(1, ceil_div(key->n, int64_t{BLOCK} * ITEMS));
   Scratch sc(ctx, (ntiles + 1) * sizeof(uint64_t), stream);
@@ -1364,16 +1369,20 @@ pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, cons
   const bool wide = t.slot_bytes == 16, k64 = key->dtype == PYST_I64;
   if (wide && k64)
     k_join_probe<BLOCK, ITEMS, true, true, PayT><<<grid, BLOCK, 0, stream>>>(
-        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err);
+        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
+        plan);
   else if (wide)
     k_join_probe<BLOCK, ITEMS, true, false, PayT><<<grid, BLOCK, 0, stream>>>(
-        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err);
+        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
+        plan);
   else if (k64)
     k_join_probe<BLOCK, ITEMS, false, true, PayT><<<grid, BLOCK, 0, stream>>>(
-        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err);
+        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
+        plan);
   else
     k_join_probe<BLOCK, ITEMS, false, false, PayT><<<grid, BLOCK, 0, stream>>>(
-        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err);
+        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
+        plan);
   PYST_LAUNCH_CHECK("k_join_probe");
   return PYST_OK;
 }
@@ -1425,7 +1434,7 @@ pyst_status launch_rows(pyst_ctx *ctx, const GatherArgs &a, int64_t *rows, const
   }
   if (cap == 0) return PYST_OK;
   TimedRegion timed(ctx, "gather_rows", stream);
-  constexpr int BLOCK = 256, ITEMS = RS >= 8 ? 4 : 8;
+  constexpr int BLOCK = 256, ITEMS = RS >= 8 ? 2 : 4;
   const int blocks = grid_for(ctx, ceil_div(cap, int64_t{ITEMS}), BLOCK, 8);
   k_gather_rows<RS, BLOCK, ITEMS><<<blocks, BLOCK, 0, stream>>>(rows, a, idx, d_n, cap, ctx_err_word(ctx));
   PYST_LAUNCH_CHECK("k_gather_rows");
@@ -1645,27 +1654,37 @@ pyst_status pyst_join_materialize(pyst_ctx *ctx, const pyst_col *build_key, cons
   Scratch mem(ctx, table_bytes(cap_alloc, slot_bytes, false), stream);
   if (!mem.p) return set_error(PYST_ERR_NOMEM, "pyst_join_materialize: arena exhausted");
   const TableDev t = table_view(mem.p, cap_alloc, slot_bytes, false);
-  pyst_status st;
+  // several build columns: one random read of a packed row per match instead of one per column
+  Scratch rows(ctx, stream);
+  if (nbcols > 1 && !rows.alloc(static_cast<size_t>(build_key->n) * row_words(nbcols) * sizeof(int64_t)))
+    return set_error(PYST_ERR_NOMEM, "pyst_join_materialize: arena exhausted");
+  // large sides with unique build keys: an array over dense keys where the arena has room for the
+  // moves beside the table's memory (which holds the array), decided on the device
+  Scratch ws(ctx, stream);
+  const JoinPlan *plan = nullptr;
+  int32_t *array = static_cast<int32_t *>(t.slots);
+  if (direct_join_wanted(build_key, probe_key, unique_keys != 0))
+    ws.try_alloc(direct_join_bytes(build_key->n, probe_key->n));
+  pyst_status st = PYST_OK;
   {
     TimedRegion timed(ctx, "join_build", stream);
-    st = launch_join_build(ctx, t, build_key, nullptr, nullptr, nullptr, max_load, unique_keys != 0, stream);
+    if (ws.p) st = direct_join_build(ctx, build_key, probe_key->n, ws.p, array, cap_alloc, &plan, stream);
+    if (st == PYST_OK)
+      st = launch_join_build(ctx, t, build_key, nullptr, nullptr, nullptr, max_load, unique_keys != 0, stream, plan);
   }
   if (st != PYST_OK) return st;
   {
     TimedRegion timed(ctx, "join_probe", stream);
-    st = launch_join_probe(ctx, t, unique_keys != 0, probe_key, nullptr, nullptr, out_probe_row, out_build_row, out_cap,
-                           d_nout, stream);
+    if (ws.p)
+      st = direct_join_probe(ctx, build_key->n, probe_key, ws.p, array, out_probe_row, out_build_row, out_cap, d_nout, stream);
+    if (st == PYST_OK)
+      st = launch_join_probe(ctx, t, unique_keys != 0, probe_key, nullptr, nullptr, out_probe_row, out_build_row, out_cap,
+                             d_nout, stream, plan);
   }
   if (st != PYST_OK) return st;
   if (npcols > 0 && (st = launch_gather(ctx, ga[0], out_probe_row, d_nout, out_cap, stream)) != PYST_OK) return st;
   if (nbcols == 1 && (st = launch_gather(ctx, ga[1], out_build_row, d_nout, out_cap, stream)) != PYST_OK) return st;
-  if (nbcols > 1) {
-    // several build columns: one random read of a packed row per match instead of one per column
-    Scratch rows(ctx, static_cast<size_t>(build_key->n) * row_words(nbcols) * sizeof(int64_t), stream);
-    if (!rows.p && build_key->n > 0) return set_error(PYST_ERR_NOMEM, "pyst_join_materialize: arena exhausted");
-    if ((st = launch_gather_rows(ctx, ga[1], rows.as<int64_t>(), out_build_row, d_nout, out_cap, stream)) != PYST_OK)
-      return st;
-  }
+  if (nbcols > 1) return launch_gather_rows(ctx, ga[1], rows.as<int64_t>(), out_build_row, d_nout, out_cap, stream);
   return PYST_OK;
 }
 

@@ -3,6 +3,7 @@
 #include "ctx.hip"
 #include "ops.hip"
 #include "sort.hip"
+#include "join.hip"
 #include "agg.hip"
 #include "query.hip"
 #include "fast.hip"

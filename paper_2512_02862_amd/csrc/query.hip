@@ -410,7 +410,7 @@ pyst_status build_dimensions(pyst_ctx *ctx, const pyst_plan *plan, const QuerySh
       } else {
         k_join_build<256, kBuildItems><<<bblocks, 256, 0, stream>>>(static_cast<const int32_t *>(js.key.data),
                                                  static_cast<const int32_t *>(js.payload.data), sel, d_nsel, nb,
-                                                 d->t[j], 1, ctx_err_word(ctx));
+                                                 d->t[j], 1, ctx_err_word(ctx), nullptr);
         PYST_LAUNCH_CHECK("k_join_build");
       }
     }

@@ -22,33 +22,19 @@
 // groups 228 -> 94 us, 900k rows into 300k 348 -> 221 us, 60M rows into 10M
 // 2422 -> 2288 us with a key range pass of 125 us that it did not have.
 #include "pyst_internal.h"
+#include "ranges.h"
 #include "table.h"
 
 namespace pyst {
 
 constexpr int kSortBlock = 1024, kSortItems = 4, kSortTile = kSortBlock * kSortItems;
 constexpr int kSortWaves = kSortBlock / kWave;
-constexpr int kSortDigits = 256;
 constexpr int kSmallItems = 8, kSmallPairs = kSortBlock * kSmallItems;
-constexpr int kSortParts = 512;  // blocks: ranges of tiles
-constexpr int kSortGroup = 16, kSortGroups = kSortParts / kSortGroup;
 
 struct SortPlan {
   int64_t base;   // least key
   int32_t npass;  // 0: nothing to do here
   int32_t width;  // bits a pass
-};
-
-// Digit counts of a pass: per range (each pass writes its own over the last
-// one's) and per group of 16 ranges (a row set per pass, cleared up front).
-struct SortCounts {
-  uint32_t *part;
-  uint32_t *group;
-  int ngroups;
-  __device__ __forceinline__ uint32_t *of_part(int64_t p) const { return part + p * kSortDigits; }
-  __device__ __forceinline__ uint32_t *of_group(int pass, int64_t g) const {
-    return group + (int64_t{pass} * ngroups + g) * kSortDigits;
-  }
 };
 
 __device__ __forceinline__ int64_t sort_count(const int64_t *d_count, int64_t cap) {
@@ -81,12 +67,12 @@ __device__ __forceinline__ int range_bits(int64_t lo, int64_t hi) {
 
 // Per-block key range, and every pass's group counts cleared.
 __global__ __launch_bounds__(256) void k_sort_range(const int64_t *keys, const int64_t *d_count, int64_t cap, int64_t *lo_out,
-                                                    int64_t *hi_out, SortCounts counts, int passes) {
+                                                    int64_t *hi_out, RangeCounts counts, int passes) {
   __shared__ int64_t s_lo[4], s_hi[4];
   const int64_t n = sort_count(d_count, cap);
   if (n <= kSmallPairs) return;
   const int64_t gtid = int64_t{blockIdx.x} * 256 + threadIdx.x, step = int64_t{gridDim.x} * 256;
-  for (int64_t i = gtid; i < int64_t{passes} * counts.ngroups * kSortDigits; i += step) counts.group[i] = 0;
+  for (int64_t i = gtid; i < int64_t{passes} * counts.ngroups * kRangeDigits; i += step) counts.group[i] = 0;
   int64_t lo = INT64_MAX, hi = INT64_MIN;
   constexpr int U = 8;
   for (int64_t i0 = gtid; i0 < n; i0 += step * U) {
@@ -129,26 +115,16 @@ __device__ __forceinline__ uint32_t sort_digit(int64_t key, int64_t base, int sh
   return static_cast<uint32_t>((static_cast<uint64_t>(key) - static_cast<uint64_t>(base)) >> shift) & mask;
 }
 
-// The tiles of a block: range p of min(kSortParts, tiles) ranges, neighbours on one XCD.
-__device__ __forceinline__ bool sort_tiles(int64_t n, int64_t &part, int64_t &t0, int64_t &t1) {
-  const int64_t tiles = (n + kSortTile - 1) / kSortTile, parts = tiles < kSortParts ? tiles : kSortParts;
-  if (blockIdx.x >= parts) return false;
-  part = xcd_block(blockIdx.x, parts);
-  t0 = tiles * part / parts;
-  t1 = tiles * (part + 1) / parts;
-  return true;
-}
-
 __global__ __launch_bounds__(kSortBlock, 8) void k_sort_hist(const SortPlan *plan, int pass, const int64_t *keys,
-                                                            const int64_t *d_count, int64_t cap, SortCounts counts) {
-  __shared__ uint32_t s_h[kSortDigits];
+                                                            const int64_t *d_count, int64_t cap, RangeCounts counts) {
+  __shared__ uint32_t s_h[kRangeDigits];
   int64_t part, t0, t1;
   if (pass >= plan->npass) return;
   const int64_t n = sort_count(d_count, cap), base = plan->base;
-  if (!sort_tiles(n, part, t0, t1)) return;
+  if (!range_of_block(n, kSortTile, part, t0, t1)) return;
   const int tid = static_cast<int>(threadIdx.x), width = plan->width, shift = pass * width;
   const uint32_t mask = (1u << width) - 1;
-  if (tid < kSortDigits) s_h[tid] = 0;
+  if (tid < kRangeDigits) s_h[tid] = 0;
   __syncthreads();
   const int64_t hi = t1 * kSortTile < n ? t1 * kSortTile : n;
   constexpr int U = 8;
@@ -161,9 +137,9 @@ __global__ __launch_bounds__(kSortBlock, 8) void k_sort_hist(const SortPlan *pla
       if (i0 + u * kSortBlock < hi) atomicAdd(&s_h[sort_digit(k[u], base, shift, mask)], 1u);
   }
   __syncthreads();
-  if (tid < kSortDigits) {
+  if (tid < kRangeDigits) {
     counts.of_part(part)[tid] = s_h[tid];
-    if (s_h[tid]) atomicAdd(&counts.of_group(pass, part / kSortGroup)[tid], s_h[tid]);
+    if (s_h[tid]) atomicAdd(&counts.of_group(pass, part / kRangeGroup)[tid], s_h[tid]);
   }
 }
 
@@ -188,60 +164,23 @@ __device__ __forceinline__ void rank_digits(const uint32_t (&dig)[ITEMS], const 
 // One pass over a block's range of tiles.  Two blocks of 16 waves per CU.
 __global__ __launch_bounds__(kSortBlock, 8) void k_sort_move(const SortPlan *plan, int pass, const int64_t *skeys,
                                                             const int64_t *svals, int64_t *dkeys, int64_t *dvals,
-                                                            const int64_t *d_count, int64_t cap, SortCounts counts) {
-  constexpr int G = kSortBlock / kSortDigits;
-  __shared__ int32_t s_cnt[kSortWaves][kSortDigits];
-  __shared__ int64_t s_next[kSortDigits];  // where the range's next pair of each digit goes
-  __shared__ int32_t s_start[kSortDigits];
-  __shared__ uint32_t s_all[G][kSortDigits], s_before[G][kSortDigits];
+                                                            const int64_t *d_count, int64_t cap, RangeCounts counts) {
+  __shared__ int32_t s_cnt[kSortWaves][kRangeDigits];
+  __shared__ int64_t s_next[kRangeDigits];  // where the range's next pair of each digit goes
+  __shared__ int32_t s_start[kRangeDigits];
+  __shared__ RangeOffsets s_off;
   __shared__ uint8_t s_dig[kSortTile];
   __shared__ int64_t s_stage[kSortTile];
   int64_t part, t0, t1;
   if (pass >= plan->npass) return;
   const int64_t n = sort_count(d_count, cap), base = plan->base;
-  if (!sort_tiles(n, part, t0, t1)) return;
+  if (!range_of_block(n, kSortTile, part, t0, t1)) return;
   const int tid = static_cast<int>(threadIdx.x), w = tid / kWave, lane = lane_id();
-  {  // counts of all ranges, and of those before this one: four threads a digit
-    const int d = tid % kSortDigits, g = tid / kSortDigits, group = static_cast<int>(part) / kSortGroup;
-    uint32_t all = 0, before = 0;
-#pragma unroll
-    for (int j = 0; j < kSortGroups / G; ++j) {
-      const uint32_t c = j * G + g < counts.ngroups ? counts.of_group(pass, j * G + g)[d] : 0;
-      all += c;
-      before += j * G + g < group ? c : 0;
-    }
-#pragma unroll
-    for (int j = 0; j < kSortGroup / G; ++j) {
-      const int p = group * kSortGroup + j * G + g;
-      before += p < part ? counts.of_part(p)[d] : 0;
-    }
-    s_all[g][d] = all;
-    s_before[g][d] = before;
-  }
-  __syncthreads();
-  if (w == 0) {  // exclusive scan over the digits
-    int64_t a[4], la = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      a[j] = 0;
-#pragma unroll
-      for (int g = 0; g < G; ++g) a[j] += s_all[g][lane * 4 + j];
-      la += a[j];
-    }
-    int64_t ra = wave_inclusive_scan(la) - la;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int64_t before = ra;
-#pragma unroll
-      for (int g = 0; g < G; ++g) before += s_before[g][lane * 4 + j];
-      s_next[lane * 4 + j] = before;
-      ra += a[j];
-    }
-  }
+  range_offsets(counts, pass, static_cast<int>(part), s_off, s_next);
   const int width = plan->width, shift = pass * width;
   const uint32_t mask = (1u << width) - 1;
   for (int64_t t = t0; t < t1; ++t) {  // block-uniform
-    for (int i = tid; i < kSortWaves * kSortDigits; i += kSortBlock) s_cnt[i / kSortDigits][i % kSortDigits] = 0;
+    for (int i = tid; i < kSortWaves * kRangeDigits; i += kSortBlock) s_cnt[i / kRangeDigits][i % kRangeDigits] = 0;
     int64_t k[kSortItems], v[kSortItems];
     uint32_t dig[kSortItems];
     bool ok[kSortItems];
@@ -259,7 +198,7 @@ __global__ __launch_bounds__(kSortBlock, 8) void k_sort_move(const SortPlan *pla
     rank_digits<kSortItems>(dig, ok, width, s_cnt[w], pos);
     __syncthreads();
     int32_t total = 0;
-    if (tid < kSortDigits) {
+    if (tid < kRangeDigits) {
 #pragma unroll
       for (int q = 0; q < kSortWaves; ++q) {
         const int32_t c = s_cnt[q][tid];
@@ -299,15 +238,15 @@ __global__ __launch_bounds__(kSortBlock, 8) void k_sort_move(const SortPlan *pla
     __syncthreads();
     for (int i = tid; i < rows; i += kSortBlock) dvals[s_next[s_dig[i]] + i] = s_stage[i];
     __syncthreads();
-    if (tid < kSortDigits) s_next[tid] += s_start[tid] + total;
+    if (tid < kRangeDigits) s_next[tid] += s_start[tid] + total;
   }
 }
 
 // Up to kSmallPairs pairs in one block: keys and their 16-bit positions change
 // places in LDS, pass by pass; the values are read once at the end, in order.
 __global__ __launch_bounds__(kSortBlock) void k_sort_small(int64_t *keys, int64_t *vals, const int64_t *d_count, int64_t cap) {
-  __shared__ int32_t s_cnt[kSortWaves][kSortDigits];
-  __shared__ int32_t s_start[kSortDigits];
+  __shared__ int32_t s_cnt[kSortWaves][kRangeDigits];
+  __shared__ int32_t s_start[kRangeDigits];
   __shared__ int64_t s_key[kSmallPairs];
   __shared__ uint16_t s_idx[kSmallPairs];
   __shared__ int64_t s_lo[kSortWaves], s_hi[kSortWaves];
@@ -332,7 +271,7 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_small(int64_t *keys, int64_
   const int bits = range_bits(lo, hi), np = (bits + 7) / 8, width = (bits + np - 1) / np;
   const uint32_t mask = (1u << width) - 1;
   for (int p = 0; p < np; ++p) {
-    for (int i = tid; i < kSortWaves * kSortDigits; i += kSortBlock) s_cnt[i / kSortDigits][i % kSortDigits] = 0;
+    for (int i = tid; i < kSortWaves * kRangeDigits; i += kSortBlock) s_cnt[i / kRangeDigits][i % kRangeDigits] = 0;
     __syncthreads();  // also: the previous pass's exchange has been read
     uint32_t dig[kSmallItems];
     int32_t pos[kSmallItems];
@@ -340,7 +279,7 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_small(int64_t *keys, int64_
     for (int j = 0; j < kSmallItems; ++j) dig[j] = sort_digit(k[j], lo, p * width, mask);
     rank_digits<kSmallItems>(dig, ok, width, s_cnt[w], pos, per);
     __syncthreads();
-    if (tid < kSortDigits) {
+    if (tid < kRangeDigits) {
       int32_t total = 0;
 #pragma unroll
       for (int q = 0; q < kSortWaves; ++q) {
@@ -398,18 +337,14 @@ pyst_status sort_pairs_by_key(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const
                               int key_bits, hipStream_t stream) {
   if (cap <= 0) return PYST_OK;
   if (cap > kSmallPairs) {
-    const int parts = static_cast<int>(std::min<int64_t>(kSortParts, ceil_div(cap, kSortTile)));
+    const int parts = range_parts(cap, kSortTile);
     const int passes = (key_bits + 15) / 16 * 2;
     Scratch tmp(ctx, 2 * static_cast<size_t>(cap) * sizeof(int64_t), stream);
-    SortCounts counts;
-    counts.ngroups = static_cast<int>(ceil_div(parts, kSortGroup));
-    const size_t words = (static_cast<size_t>(parts) + static_cast<size_t>(passes) * counts.ngroups) * kSortDigits;
-    Scratch st(ctx, 256 + 2 * parts * sizeof(int64_t) + words * sizeof(uint32_t), stream);
+    Scratch st(ctx, 256 + 2 * parts * sizeof(int64_t) + range_count_words(parts, passes) * sizeof(uint32_t), stream);
     if (!tmp.p || !st.p) return set_error(PYST_ERR_NOMEM, "sort: arena exhausted");
     SortPlan *plan = st.as<SortPlan>();
     int64_t *lo = reinterpret_cast<int64_t *>(static_cast<char *>(st.p) + 256), *hi = lo + parts;
-    counts.part = reinterpret_cast<uint32_t *>(hi + parts);
-    counts.group = counts.part + int64_t{parts} * kSortDigits;
+    const RangeCounts counts = range_counts_at(hi + parts, parts);
     k_sort_range<<<parts, 256, 0, stream>>>(keys, d_count, cap, lo, hi, counts, passes);
     PYST_LAUNCH_CHECK("k_sort_range");
     k_sort_plan<<<1, kSortBlock, 0, stream>>>(plan, d_count, cap, lo, hi, parts);

@@ -52,6 +52,24 @@ struct GbPlan {
   unsigned long long ticket;
 };
 
+// How a materializing join of large sides looks its build rows up: chosen on the
+// device from the build keys' range (see join.hip).
+struct JoinPlan {
+  int64_t kmin;
+  uint64_t range;             // greatest - least build key + 1
+  int32_t direct;             // array indexed by key - kmin, else the hash table
+  int32_t shift;              // slice = (key - kmin) >> shift
+  int64_t moved[2];           // rows in their slices: build, probe
+  unsigned long long filled;  // entries of the array
+  unsigned long long ticket;
+};
+bool direct_join_wanted(const pyst_col *build_key, const pyst_col *probe_key, int unique);
+size_t direct_join_bytes(int64_t nb, int64_t np);
+pyst_status direct_join_build(pyst_ctx *ctx, const pyst_col *build_key, int64_t np, void *ws, int32_t *array,
+                              int64_t range_max, const JoinPlan **plan, hipStream_t stream);
+pyst_status direct_join_probe(pyst_ctx *ctx, int64_t nb, const pyst_col *probe_key, void *ws, int32_t *array,
+                              int32_t *out_row, int32_t *out_build, int64_t out_cap, int64_t *d_nout, hipStream_t stream);
+
 __device__ __forceinline__ int32_t plan_mode(const GbPlan *p) {
   return p->mode == kGbFew && p->few_failed ? p->otherwise : p->mode;
 }
@@ -130,7 +148,8 @@ __device__ __forceinline__ bool group_add(uint64_t *slots, int64_t mask, int64_t
 }
 
 // Host helpers implemented in ops.hip / sort.hip.
-pyst_status table_init(const TableDev &t, const int64_t *d_nsel, int64_t n, double max_load, hipStream_t stream);
+pyst_status table_init(const TableDev &t, const int64_t *d_nsel, int64_t n, double max_load, hipStream_t stream,
+                       const JoinPlan *plan = nullptr);
 pyst_status group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int64_t max_groups, double max_load,
                        hipStream_t stream);
 pyst_status group_insert(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val, const int32_t *sel,
