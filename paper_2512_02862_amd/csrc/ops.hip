@@ -797,12 +797,18 @@ __device__ __forceinline__ void probe_wide(const uint64_t *slots, int64_t mask, 
 }
 
 // Each lane probes ITEMS rows, one wave64 row apart: the keys, then the ITEMS
-// home groups (narrow table: two slots; wide: one) are loaded together, and
-// only rows whose run goes on past their home group walk on.  Keys compare by
-// value: an int64 probe key outside int32 range matches nothing in a narrow
-// table, and a probe key equal to its column's EMPTY sentinel matches nothing.
-// K64: the probe key column is int64.  PayT: int64 for stored payloads, int32
-// for the build rows of a materializing join.
+// home groups (narrow table: two slots; wide: one) are loaded together, and the
+// runs that go on past a group load their next groups together too, step by
+// step, so that a wave waits for as many round trips as its longest run has
+// groups (row by row it waited for the sum over its rows of the longest run
+// among 64 lanes).  A block of 16 waves with few rows a lane leaves registers for
+// eight waves per SIMD (eight rows took 136 registers, three waves): 20M probes of
+// a 1M-key wide table 844 -> 680 us, 15M of a 1M-key narrow one 430 -> 343 us.
+// Bound by the lines that miss the L2: one a probe, at 25 - 40e9/s.
+// Keys compare by value: an int64 probe key outside int32 range matches nothing
+// in a narrow table, and a probe key equal to its column's EMPTY sentinel
+// matches nothing.  K64: the probe key column is int64.  PayT: int64 for stored
+// payloads, int32 for the build rows of a materializing join.
 template <int BLOCK, int ITEMS, bool WIDE, bool K64, typename PayT>
 __global__ __launch_bounds__(BLOCK) void k_join_probe(const void *key, const int32_t *sel,
                                                      const int64_t *d_nsel, int64_t n, TableDev t, int unique,
@@ -826,52 +832,58 @@ __global__ __launch_bounds__(BLOCK) void k_join_probe(const void *key, const int
   using KeyT = std::conditional_t<K64, int64_t, int32_t>;              // probe column
   using CmpT = std::conditional_t<WIDE || K64, int64_t, int32_t>;      // key as held
   using StoredT = std::conditional_t<WIDE, int64_t, int32_t>;          // table payload
+  using SlotT = std::conditional_t<WIDE, uint64_t, uint32_t>;          // (a narrow table's home slots are 32-bit hashes)
   constexpr KeyT kColEmpty = K64 ? static_cast<KeyT>(kEmpty64) : static_cast<KeyT>(kEmpty32);
   CmpT kk[ITEMS];
   StoredT first_pay[ITEMS];
   int32_t c[ITEMS];
-  int64_t s[ITEMS];
+  SlotT s[ITEMS];
   ulonglong2 g[ITEMS];
-  bool live[ITEMS];
+  uint32_t on = 0;  // bit j: item j's run goes on
 #pragma unroll
   for (int j = 0; j < ITEMS; ++j) {
     const int64_t i = wbase + int64_t{j} * kWave + lane;
     const KeyT v = i < cnt ? static_cast<const KeyT *>(key)[row_of(sel, i)] : kColEmpty;
     kk[j] = v;
-    live[j] = v != kColEmpty;
-    if (!WIDE && K64) live[j] = live[j] && v > kEmpty32 && v <= INT32_MAX;  // fits the int32 table keys
-  }
-#pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    if (WIDE) {
-      s[j] = static_cast<int64_t>(table_hash64(static_cast<int64_t>(kk[j]))) & mask;
-      g[j] = live[j] ? *reinterpret_cast<const ulonglong2 *>(&slots[2 * s[j]])
-                     : ulonglong2{static_cast<uint64_t>(kEmpty64), 0};
-    } else {
-      s[j] = (table_hash32(static_cast<int32_t>(kk[j])) & mask) & ~int64_t{1};
-      g[j] = live[j] ? *reinterpret_cast<const ulonglong2 *>(&slots[s[j]]) : ulonglong2{kEmptySlot, kEmptySlot};
-    }
-  }
-  auto visit = [&](ulonglong2 x, int j) {
-    if constexpr (WIDE) return visit_wide(x, kk[j], unique, c[j], first_pay[j]);
-    else return visit_pair(x, static_cast<int32_t>(kk[j]), unique, c[j], first_pay[j]);
-  };
-  int64_t wave_total = 0;
-  int64_t lane_off[ITEMS];
-#pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
+    bool live = v != kColEmpty;
+    if (!WIDE && K64) live = live && v > kEmpty32 && v <= INT32_MAX;  // fits the int32 table keys
+    on |= live ? 1u << j : 0;
     c[j] = 0;
     first_pay[j] = 0;
-    if (live[j] && visit(g[j], j)) {
-      int64_t p = s[j];
-      for (int64_t step = GS; step <= mask; step += GS) {
-        p = (p + GS) & mask;
-        if (!visit(*reinterpret_cast<const ulonglong2 *>(&slots[WIDE ? 2 * p : p]), j)) break;
-      }
+    if (WIDE) s[j] = static_cast<SlotT>(table_hash64(static_cast<int64_t>(kk[j])) & static_cast<uint64_t>(mask));
+    else s[j] = static_cast<SlotT>(table_hash32(static_cast<int32_t>(kk[j])) & static_cast<uint64_t>(mask)) & ~SlotT{1};
+  }
+  for (int64_t step = 0; step <= mask && __any(on != 0); step += GS) {
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const int64_t p = (static_cast<int64_t>(s[j]) + step) & mask;
+      if ((on >> j) & 1) g[j] = *reinterpret_cast<const ulonglong2 *>(&slots[WIDE ? 2 * p : p]);
     }
-    const int64_t incl = wave_inclusive_scan<int64_t>(c[j]);
-    lane_off[j] = wave_total + incl - c[j];
-    wave_total += __shfl(incl, kWave - 1);
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      if (!((on >> j) & 1)) continue;
+      bool more;
+      if constexpr (WIDE) more = visit_wide(g[j], kk[j], unique, c[j], first_pay[j]);
+      else more = visit_pair(g[j], static_cast<int32_t>(kk[j]), unique, c[j], first_pay[j]);
+      if (!more) on &= ~(1u << j);
+    }
+  }
+  int64_t wave_total = 0;
+  int64_t lane_off[ITEMS];
+  if (unique) {  // at most one match a row
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const uint64_t m = __ballot(c[j] != 0);
+      lane_off[j] = wave_total + mbcnt(m);
+      wave_total += __popcll(m);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const int64_t incl = wave_inclusive_scan<int64_t>(c[j]);
+      lane_off[j] = wave_total + incl - c[j];
+      wave_total += __shfl(incl, kWave - 1);
+    }
   }
   if (lane == 0) s_w[w] = wave_total;
   __syncthreads();
@@ -1356,8 +1368,12 @@ template <typename PayT>
 pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, const pyst_col *key, const int32_t *sel,
                               const int64_t *d_nsel, int32_t *out_row, PayT *out_pay, int64_t out_cap,
                               int64_t *d_nout, hipStream_t stream, const JoinPlan *plan = nullptr) {
-  constexpr int BLOCK = 256, ITEMS = 8;
-  const int64_t ntiles = std::max<int64_t>(1, ceil_div(key->n, int64_t{BLOCK} * ITEMS));
+  // rows a lane: four of a narrow table's 8-byte slots, two of a wide one's 16 bytes (1M build and 15M
+  // probe rows, narrow: 343 us with four, 370 with two, 476 with one; lookup of 20M 64-bit ids,
+  // wide: 786, 680, 819)
+  constexpr int BLOCK = 1024, NARROW = 4, WIDE = 2;
+  const bool wide = t.slot_bytes == 16, k64 = key->dtype == PYST_I64;
+  const int64_t ntiles = std::max<int64_t>(1, ceil_div(key->n, int64_t{BLOCK} * (wide ? WIDE : NARROW)));
   Scratch sc(ctx, (ntiles + 1) * sizeof(uint64_t), stream);
   if (!sc.p) return set_error(PYST_ERR_NOMEM, "join probe: arena exhausted");
   pyst_status st = fill_u64(sc.p, ntiles + 1, 0, stream);
@@ -1366,21 +1382,20 @@ pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, cons
   auto *ticket = reinterpret_cast<unsigned long long *>(status + ntiles);
   const unsigned grid = static_cast<unsigned>(ntiles);
   uint32_t *err = ctx_err_word(ctx);
-  const bool wide = t.slot_bytes == 16, k64 = key->dtype == PYST_I64;
   if (wide && k64)
-    k_join_probe<BLOCK, ITEMS, true, true, PayT><<<grid, BLOCK, 0, stream>>>(
+    k_join_probe<BLOCK, WIDE, true, true, PayT><<<grid, BLOCK, 0, stream>>>(
         key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
         plan);
   else if (wide)
-    k_join_probe<BLOCK, ITEMS, true, false, PayT><<<grid, BLOCK, 0, stream>>>(
+    k_join_probe<BLOCK, WIDE, true, false, PayT><<<grid, BLOCK, 0, stream>>>(
         key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
         plan);
   else if (k64)
-    k_join_probe<BLOCK, ITEMS, false, true, PayT><<<grid, BLOCK, 0, stream>>>(
+    k_join_probe<BLOCK, NARROW, false, true, PayT><<<grid, BLOCK, 0, stream>>>(
         key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
         plan);
   else
-    k_join_probe<BLOCK, ITEMS, false, false, PayT><<<grid, BLOCK, 0, stream>>>(
+    k_join_probe<BLOCK, NARROW, false, false, PayT><<<grid, BLOCK, 0, stream>>>(
         key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
         plan);
   PYST_LAUNCH_CHECK("k_join_probe");
