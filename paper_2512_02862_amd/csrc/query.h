@@ -35,6 +35,7 @@ struct PairsOut {
 
 struct QueryShape {
   FactArgs fact;
+  uint32_t used_cols;  // bit c: the plan reads fact column c
   bool need_payload[2];
   bool slot_agg;   // group key is the key of the single join: sums live in its slots
   int agg_mode;    // 0 slot sums, 1 group table sized by max_groups, 2 pairs + group-by

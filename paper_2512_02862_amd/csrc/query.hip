@@ -293,6 +293,7 @@ pyst_status prepare_query(const pyst_plan *plan, const pyst_col *fact, int nfact
     if (slot_of[c] < 0) {
       if (a.ncol >= kMaxFactCols) return -2;
       slot_of[c] = a.ncol;
+      q->used_cols |= 1u << c;
       a.col[a.ncol] = fact[c].data;
       a.is64[a.ncol] = fact[c].dtype == PYST_I64;
       ++a.ncol;

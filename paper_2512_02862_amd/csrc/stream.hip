@@ -44,8 +44,10 @@ pyst_status streamed_query(pyst_ctx *ctx, const pyst_plan *plan, const pyst_col 
   // Per column and ring slot: the decoded chunk, and with packed input its block
   // headers and the most words any chunk of the column has.
   auto round = [](size_t x) { return (x + 255) / 256 * 256; };
-  std::vector<size_t> col_bytes(nfact), hdr_bytes(nfact, 0), word_bytes(nfact, 0);
+  std::vector<size_t> col_bytes(nfact, 0), hdr_bytes(nfact, 0), word_bytes(nfact, 0);
+  auto used = [&](int c) { return (q.used_cols >> c & 1) != 0; };
   for (int c = 0; c < nfact; ++c) {
+    if (!used(c)) continue;  // neither copied nor read: no room in the ring
     col_bytes[c] = round(static_cast<size_t>(chunk_rows) * (host_fact[c].dtype == PYST_I64 ? 8 : 4));
     if (!packed) continue;
     hdr_bytes[c] = round(static_cast<size_t>(chunk_rows / PYST_PACK_BLOCK + 1) * sizeof(pyst_pack_block));
@@ -77,6 +79,13 @@ pyst_status streamed_query(pyst_ctx *ctx, const pyst_plan *plan, const pyst_col 
       st = set_error(PYST_ERR_HIP, "pyst_query_streamed: hipEventCreate");
   }
 
+  // The copy stream must not overwrite ring memory before `stream` has reached this point.
+  hipEvent_t start = nullptr;
+  if (st == PYST_OK) {
+    if (hipEventCreateWithFlags(&start, hipEventDisableTiming) != hipSuccess || hipEventRecord(start, stream) != hipSuccess ||
+        hipStreamWaitEvent(cs, start, 0) != hipSuccess)
+      st = set_error(PYST_ERR_HIP, "pyst_query_streamed: ordering the copy stream");
+  }
   DimTables d;
   std::memset(&d, 0, sizeof(d));
   AggState s;
@@ -92,13 +101,6 @@ pyst_status streamed_query(pyst_ctx *ctx, const pyst_plan *plan, const pyst_col 
     }
   }
   if (st == PYST_OK) st = fast_build_dimensions(ctx, plan, q, &d, d_ngroups, nullptr, stream, false, nullptr);
-  // The copy stream must not overwrite ring memory before `stream` has reached this point.
-  hipEvent_t start = nullptr;
-  if (st == PYST_OK) {
-    if (hipEventCreateWithFlags(&start, hipEventDisableTiming) != hipSuccess || hipEventRecord(start, stream) != hipSuccess ||
-        hipStreamWaitEvent(cs, start, 0) != hipSuccess)
-      st = set_error(PYST_ERR_HIP, "pyst_query_streamed: ordering the copy stream");
-  }
   std::vector<pyst_col> dev_fact(host_fact, host_fact + nfact);
   for (int64_t ch = 0; ch < nchunks && st == PYST_OK; ++ch) {
     const int b = static_cast<int>(ch % nbuf);
@@ -114,6 +116,7 @@ pyst_status streamed_query(pyst_ctx *ctx, const pyst_plan *plan, const pyst_col 
         dev_fact[c].data = buf[b][c];
         dev_fact[c].n = rows;
         hipError_t e = hipSuccess;
+        if (!used(c)) continue;
         if (!packed) {
           const size_t w = host_fact[c].dtype == PYST_I64 ? 8 : 4;
           e = hipMemcpyAsync(buf[b][c], static_cast<const char *>(host_fact[c].data) + off * w,
@@ -139,6 +142,7 @@ pyst_status streamed_query(pyst_ctx *ctx, const pyst_plan *plan, const pyst_col 
     // the copy stream goes on with the next chunk meanwhile; the slot's packed
     // buffers are reused only after `consumed`, recorded after the fact pass.
     for (int c = 0; packed && c < nfact && st == PYST_OK; ++c) {
+      if (!used(c)) continue;
       const int64_t b0 = off / PYST_PACK_BLOCK, b1 = ceil_div(off + rows, PYST_PACK_BLOCK);
       const int64_t w0 = packed[c].blocks[b0].word_off, w1 = packed[c].blocks[b1].word_off;
       st = launch_unpack(ctx, reinterpret_cast<const pyst_pack_block *>(hdr[b][c]),

@@ -79,3 +79,26 @@ def test_streamed_rejects_pageable_and_bad_chunks(gpu, ctx):
         gpu.query_streamed(ctx, gpu.star_plan(bd), host, chunk_rows=1001)
     with pytest.raises(gpu.PystError):
         gpu.query_streamed(ctx, gpu.star_plan(bd), host, chunk_rows=1024, nbuf=1)
+
+
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("order", [(0, 1, 2, 3, 4), (3, 4, 0, 2, 1), (4, 2, 1, 0, 3)])
+def test_streamed_skips_columns_the_plan_does_not_read(gpu, ctx, order, packed):
+    # fk, date and price among two unread columns, at the front, the end and between
+    nb, n = 5_000, 300_007
+    b, p = gen.star_tables(nb, n)
+    bd = {k: dev(v) for k, v in b.items()}
+    data = [p["fk"], p["date"], p["price"], np.full(n, -7, np.int64), np.arange(n, dtype=np.int32)]
+    at = {c: i for i, c in enumerate(order)}
+    plan = gpu.star_plan(bd)
+    plan.joins[0]["probe_col"], plan.preds, plan.value = at[0], [(at[1], "<", 1200)], ("col", at[2])
+    cols = [pinned(data[c]) for c in order]
+    if packed:
+        got = gpu.query_streamed_packed(ctx, plan, [(*gpu.pack(t), n, t.dtype) for t in cols], chunk_rows=65536, nbuf=3)
+    else:
+        got = gpu.query_streamed(ctx, plan, cols, chunk_rows=65536, nbuf=3)
+    ctx.check()
+    got = sorted_out(*got)
+    wk, ws = oracle.star_query(b, p)
+    np.testing.assert_array_equal(got[0], wk)
+    np.testing.assert_array_equal(got[1], ws)
