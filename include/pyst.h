@@ -468,7 +468,9 @@ typedef struct pyst_fragment {
 /* Batch execution parameters.
    fanout   : the number of work units each fragment's fact table is split into
               (at least 4 * block rows per unit), i.e. how finely large
-              fragments spread over the chip next to small ones;
+              fragments spread over the chip next to small ones; with block
+              1024 a fragment so large that a unit would hold more than half of
+              a compute unit's share of the batch is split into more units;
    block    : threads per block of the fact pass (256, 512 or 1024);
    max_load : hash-table load bound of every fragment (0: the plan's). */
 typedef struct pyst_tuning {

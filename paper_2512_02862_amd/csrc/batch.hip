@@ -380,8 +380,21 @@ static bool batch_shape(const pyst_fragment &fg, QueryShape *q, FastArgs *fa) {
   return fast_shape(fg.plan, fg.fact, *q, fa);
 }
 
+// A staged batch runs one block per CU at a time, units largest first, so a unit
+// as long as a CU's whole share of the batch's fact rows leaves the other CUs
+// idle at the end: no unit holds more than half of a share (split_large),
+// whatever the tuned fanout, unless that is under 16384 rows.  64 fragments of
+// 10k to 20M rows at fanout 16 (a share is 658k rows, the largest units 1.25M):
+// fact pass 1354 -> 823 us, 819 with quarters of a share, 847 with whole shares;
+// 90 fragments of 15k to 5.3M rows 388 -> 389 us (quarters 400: each unit copies
+// its filter, 128 KiB, and leaves a chunk per bucket partly filled).  Without
+// staging several blocks share a CU and the pass is bound by its atomics: smaller
+// units measured 402 -> 411 us there, so those keep the fanout.
+constexpr int64_t kUnitsPerShare = 2;
+constexpr int64_t kUnitRowsMin = 16384;
+
 static pyst_status batch_layout(pyst_ctx *ctx, const pyst_fragment *fr, int nfrag, const pyst_tuning &tu, bool allow_staged,
-                                BatchPlan *bp) {
+                                bool split_large, BatchPlan *bp) {
   bp->frags.resize(nfrag);
   bp->pre.assign(static_cast<size_t>(kPreKinds) * (nfrag + 1), 0);
   const int64_t cus = ctx_num_cus(ctx);
@@ -394,6 +407,9 @@ static pyst_status batch_layout(pyst_ctx *ctx, const pyst_fragment *fr, int nfra
                                        tu.max_load > 0 ? tu.max_load : fr[f].plan->joins[0].max_load) <=
                    kBucketSlots * kMaxSumBuckets;
   bp->pool_chunks.assign(nfrag, 0);
+  int64_t rows = 0;
+  for (int f = 0; f < nfrag; ++f) rows += fr[f].nfact > 0 ? fr[f].fact[0].n : 0;
+  const int64_t most = std::max<int64_t>(kUnitRowsMin, ceil_div(rows, kUnitsPerShare * cus));
   for (int f = 0; f < nfrag; ++f) {
     QueryShape q;
     FastArgs fa;
@@ -416,7 +432,8 @@ static pyst_status batch_layout(pyst_ctx *ctx, const pyst_fragment *fr, int nfra
     }
     b.max_load = tu.max_load > 0 ? tu.max_load : js.max_load;
     b.fa = fa;
-    const int64_t units = std::max<int64_t>(1, std::min<int64_t>(tu.fanout, ceil_div(fa.n, int64_t{4} * tu.block)));
+    int64_t units = std::max<int64_t>(1, std::min<int64_t>(tu.fanout, ceil_div(fa.n, int64_t{4} * tu.block)));
+    if (split_large && bp->staged) units = std::max(units, ceil_div(fa.n, most));
     b.rows_per_unit = std::max<int64_t>(4, ceil_div(ceil_div(fa.n, units), 4) * 4);
     b.out_keys = fr[f].out_keys;
     b.out_sums = fr[f].out_sums;
@@ -484,7 +501,7 @@ struct BatchRun {
 static pyst_status batch_prepare(pyst_ctx *ctx, const pyst_fragment *fr, int nfrag, const pyst_tuning &tu,
                                  hipStream_t stream, BatchRun *run) {
   BatchPlan bp;
-  pyst_status st = batch_layout(ctx, fr, nfrag, tu, true, &bp);
+  pyst_status st = batch_layout(ctx, fr, nfrag, tu, true, true, &bp);
   if (st != PYST_OK) return st;
   const bool v64 = bp.frags[0].fa.v0_64 != 0;
   for (int f = 1; f < nfrag; ++f)
@@ -495,9 +512,15 @@ static pyst_status batch_prepare(pyst_ctx *ctx, const pyst_fragment *fr, int nfr
   const size_t meta = (desc_bytes + 255) / 256 * 256 + (pre_bytes + 255) / 256 * 256;
   char *mem = static_cast<char *>(
       ctx_alloc(ctx, meta + bp.table_bytes_total + bp.sel_bytes_total + bp.pool_bytes_total, stream));
-  if (!mem && bp.staged) {  // no room for the pair pools: per-row atomics instead
+  if (!mem && bp.staged) {  // no room for the pair pools: fewer units have smaller ones
     bp = BatchPlan();
-    if ((st = batch_layout(ctx, fr, nfrag, tu, false, &bp)) != PYST_OK) return st;
+    if ((st = batch_layout(ctx, fr, nfrag, tu, true, false, &bp)) != PYST_OK) return st;
+    mem = static_cast<char *>(
+        ctx_alloc(ctx, meta + bp.table_bytes_total + bp.sel_bytes_total + bp.pool_bytes_total, stream));
+  }
+  if (!mem && bp.staged) {  // per-row atomics instead
+    bp = BatchPlan();
+    if ((st = batch_layout(ctx, fr, nfrag, tu, false, true, &bp)) != PYST_OK) return st;
     mem = static_cast<char *>(ctx_alloc(ctx, meta + bp.table_bytes_total + bp.sel_bytes_total, stream));
   }
   if (!mem) return set_error(PYST_ERR_NOMEM, "pyst_query_batch: arena cannot hold the batch");

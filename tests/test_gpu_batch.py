@@ -226,3 +226,26 @@ def test_batch_duplicate_dimension_key(gpu, ctx, hash_only):
     finally:
         ctx.hash_join_only(False)
     assert e.value.status == gpu.ERR_DUP_KEY
+
+
+@pytest.mark.parametrize("budget", [4 << 30, 24 << 20])
+@pytest.mark.parametrize("spec", [[(16_384, 1_000), (16_385, 999)], [(32_769, 7), (5, 3), (1_000_003, 100_000)],
+                                  [(2_500_001, 50_000)], [(1_600_000, 90_000)] * 3 + [(40_000, 4_000)] * 9])
+def test_batch_splits_large_units(gpu, spec, budget):
+    # fanout 1: fragments above half of a compute unit's share are split further; a short arena
+    # keeps the fanout, or adds per row
+    c = gpu.Ctx(0, budget)
+    frags, host = [], []
+    for f, (p, b) in enumerate(spec):
+        bt, pt = gen.star_tables(b, p, workload=3, fragment=300 + f)
+        frags.append((gpu.star_plan({k: dev(v) for k, v in bt.items()}), [dev(pt[x]) for x in ("fk", "date", "price")]))
+        host.append((bt, pt))
+    batch = gpu.Batch(c, frags)
+    batch.run((1, 1024, 0.7))
+    c.check()
+    for (k, s), (bt, pt) in zip(batch.results(), host):
+        wk, ws = oracle.star_query(bt, pt)
+        gk, gs = sorted_np(k, s)
+        np.testing.assert_array_equal(gk, wk)
+        np.testing.assert_array_equal(gs, ws)
+    c.close()
