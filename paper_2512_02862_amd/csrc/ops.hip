@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "pyst_internal.h"
+#include "ranges.h"
 #include "table.h"
 
 // Scratch of pyst_partition_noalloc: every GPU the library runs on holds its
@@ -145,9 +146,109 @@ __global__ __launch_bounds__(BLOCK) void k_filter(PredSet ps, int64_t n, int32_t
   }
 }
 
+// The same in two kernels over up to 512 contiguous ranges of rows: the first
+// evaluates the predicates once, keeping one bit a row (the ballots) and the
+// range's count, the second adds up the counts before its range and writes the
+// row ids from the bits.  Nothing waits on another block: k_filter's tiles take
+// tickets from one word, one by one, and look back over each other.  Bound by
+// the predicate columns' read and the row ids' write: 20M rows, one int32
+// predicate, half selected, 90 -> 46 us (27 + 19; k_filter alone at 16384 rows a
+// tile 56 us).
+constexpr int kMaskItems = 8, kMaskTile = kRangeThreads * kMaskItems;
+__global__ __launch_bounds__(kRangeThreads, 8) void k_filter_masks(PredSet ps, int64_t n, uint64_t *masks, int32_t *counts) {
+  constexpr int NW = kRangeThreads / kWave;
+  __shared__ int32_t s_cnt[NW];
+  int64_t part, t0, t1;
+  if (!range_of_block(n, kMaskTile, part, t0, t1)) return;
+  const int w = threadIdx.x / kWave, lane = lane_id();
+  int32_t cnt = 0;
+  for (int64_t t = t0; t < t1; ++t) {
+    const int64_t wbase = t * kMaskTile + int64_t{w} * kWave * kMaskItems;
+    if (wbase >= n) break;  // wave-uniform
+    int64_t rows[kMaskItems];
+    bool keep[kMaskItems];
+#pragma unroll
+    for (int j = 0; j < kMaskItems; ++j) rows[j] = wbase + int64_t{j} * kWave + lane;
+    eval_preds_items<kMaskItems>(ps, rows, n, keep);
+    uint64_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kMaskItems; ++j) {
+      const uint64_t m = __ballot(keep[j]);
+      cnt += __popcll(m);
+      if (lane == j) mine = m;
+    }
+    if (lane < kMaskItems) masks[wbase / kWave + lane] = mine;
+  }
+  if (lane == 0) s_cnt[w] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t tot = 0;
+    for (int k = 0; k < NW; ++k) tot += s_cnt[k];
+    counts[part] = tot;
+  }
+}
+
+__global__ __launch_bounds__(kRangeThreads, 8) void k_filter_rows(const uint64_t *masks, const int32_t *counts, int64_t n,
+                                                                 int32_t *sel_out, int64_t *d_nsel) {
+  constexpr int NW = kRangeThreads / kWave;
+  __shared__ int64_t s_sum[NW];
+  __shared__ int32_t s_cnt[NW];
+  int64_t part, t0, t1;
+  if (!range_of_block(n, kMaskTile, part, t0, t1)) {
+    if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) *d_nsel = 0;
+    return;
+  }
+  const int tid = static_cast<int>(threadIdx.x), w = tid / kWave, lane = lane_id();
+  // every wave walks its own consecutive masks of the range
+  const int64_t m0 = t0 * (kMaskTile / kWave), m1 = t1 * (kMaskTile / kWave), words = (n + kWave - 1) / kWave;
+  const int64_t per = (m1 - m0) / NW, lo = m0 + w * per, end = lo + per < words ? lo + per : words;
+  const int64_t before = tid < part ? counts[tid] : 0;  // (at most 512 ranges)
+  int32_t cnt = 0;
+  for (int64_t i = lo + lane; i < end; i += kWave) cnt += __popcll(masks[i]);
+  cnt = wave_sum(cnt);
+  const int64_t sum = wave_sum(before);
+  if (lane == 0) {
+    s_cnt[w] = cnt;
+    s_sum[w] = sum;
+  }
+  __syncthreads();
+  int64_t base = 0;
+  for (int k = 0; k < NW; ++k) base += s_sum[k];
+  for (int k = 0; k < w; ++k) base += s_cnt[k];
+  if (t1 * kMaskTile >= n && w == NW - 1 && lane == 0) *d_nsel = base + cnt;  // the last range
+  for (int64_t i0 = lo; i0 < end; i0 += kWave) {  // wave-uniform: 64 masks, 4096 rows
+    const uint64_t m = i0 + lane < end ? masks[i0 + lane] : 0;
+    const int32_t c = __popcll(m), incl = wave_inclusive_scan(c);
+    const int32_t excl = incl - c;
+    const int used = static_cast<int>(end - i0 < kWave ? end - i0 : kWave);
+    for (int j = 0; j < used; ++j) {
+      const uint64_t mj = static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(m), j))) |
+                          static_cast<uint64_t>(static_cast<uint32_t>(
+                              __builtin_amdgcn_readlane(static_cast<int>(m >> 32), j))) << 32;
+      const int32_t at = __builtin_amdgcn_readlane(excl, j);
+      if ((mj >> lane) & 1ull) sel_out[base + at + mbcnt(mj)] = static_cast<int32_t>((i0 + j) * kWave + lane);
+    }
+    base += __builtin_amdgcn_readlane(incl, kWave - 1);
+  }
+}
+
 pyst_status filter_impl(pyst_ctx *ctx, const PredSet &ps, int64_t n, int32_t *sel_out, int64_t *d_nsel,
                         hipStream_t stream) {
-  constexpr int BLOCK = 256, ITEMS = 16;
+  {
+    const int64_t words = ceil_div(n, kMaskTile) * (kMaskTile / kWave);
+    Scratch masks(ctx, stream);
+    if (masks.try_alloc(words * sizeof(uint64_t) + kRangeParts * sizeof(int32_t))) {
+      int32_t *counts = reinterpret_cast<int32_t *>(masks.as<uint64_t>() + words);
+      const int parts = range_parts(n, kMaskTile);
+      k_filter_masks<<<parts, kRangeThreads, 0, stream>>>(ps, n, masks.as<uint64_t>(), counts);
+      PYST_LAUNCH_CHECK("k_filter_masks");
+      k_filter_rows<<<parts, kRangeThreads, 0, stream>>>(masks.as<uint64_t>(), counts, n, sel_out, d_nsel);
+      PYST_LAUNCH_CHECK("k_filter_rows");
+      return PYST_OK;
+    }
+  }
+  // an arena without a bit a row to spare: in one pass, with a word a tile
+  constexpr int BLOCK = 1024, ITEMS = 16;
   const int64_t ntiles = std::max<int64_t>(1, ceil_div(n, int64_t{BLOCK} * ITEMS));
   Scratch sc(ctx, (ntiles + 1) * sizeof(uint64_t), stream);
   if (!sc.p) return set_error(PYST_ERR_NOMEM, "pyst_filter: arena exhausted");
