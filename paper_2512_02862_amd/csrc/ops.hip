@@ -493,18 +493,17 @@ __global__ __launch_bounds__(BLOCK) void k_part_scatter(PartArgs a, const int32_
   int32_t pos[ITEMS];
   uint16_t dst[ITEMS];
   int64_t keyv[ITEMS];
-  // The first payload columns are loaded with the keys (one memory round
-  // trip per tile instead of one per column); later ones in the column loop.
-  // (Two with 512 threads; one with 1024, whose 4 rows per thread then fit in
-  // 56 registers: two blocks of 16 waves per CU.)
-  constexpr int PRE = BLOCK >= 1024 ? 1 : 2;
-  int64_t pre[PRE][ITEMS];
+  // The first payload column is loaded with the keys, each later one while the
+  // column before it is written out: one memory round trip per tile, and the
+  // registers of one column (44 at four rows a thread: two blocks of 16 waves).
+  // 60M rows to 64 destinations, two payload columns: 473 -> 458 us.  (One block per
+  // contiguous range of tiles instead, its counts added up as the sort's, measured
+  // 568: 512 ranges of open runs instead of the tiles in flight next to each other.)
+  int64_t x[ITEMS];
   {
     int64_t r64[ITEMS];
     part_load<ITEMS>(a, wbase, cnt, r64, keyv);
-#pragma unroll
-    for (int c = 0; c < PRE; ++c)
-      if (c < a.npay && wbase < cnt) load_items<ITEMS>(a.pay[c], a.pay64[c], r64, a.n, pre[c]);
+    if (a.npay > 0 && wbase < cnt) load_items<ITEMS>(a.pay[0], a.pay64[0], r64, a.n, x);
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) rowv[j] = static_cast<int32_t>(r64[j]);
   }
@@ -543,25 +542,14 @@ __global__ __launch_bounds__(BLOCK) void k_part_scatter(PartArgs a, const int32_
   const int tile_rows = static_cast<int>(std::min<int64_t>(TILE, std::max<int64_t>(0, cnt - t * TILE)));
   for (int c = 0; c <= a.npay; ++c) {
     const int is64 = c == 0 ? a.key64 : a.pay64[c - 1];
-    if (c == 0) {
 #pragma unroll
-      for (int j = 0; j < ITEMS; ++j)
-        if (pos[j] >= 0) s_stage[pos[j]] = keyv[j];
-    } else if (c <= PRE && wbase < cnt) {
-#pragma unroll
-      for (int q = 0; q < PRE; ++q)
-        if (q == c - 1)
-#pragma unroll
-          for (int j = 0; j < ITEMS; ++j)
-            if (pos[j] >= 0) s_stage[pos[j]] = pre[q][j];
-    } else if (wbase < cnt) {
-      int64_t rr[ITEMS], x[ITEMS];
+    for (int j = 0; j < ITEMS; ++j)
+      if (pos[j] >= 0) s_stage[pos[j]] = c == 0 ? keyv[j] : x[j];
+    if (c > 0 && c < a.npay && wbase < cnt) {
+      int64_t rr[ITEMS];
 #pragma unroll
       for (int j = 0; j < ITEMS; ++j) rr[j] = rowv[j];
-      load_items<ITEMS>(a.pay[c - 1], is64, rr, a.n, x);
-#pragma unroll
-      for (int j = 0; j < ITEMS; ++j)
-        if (pos[j] >= 0) s_stage[pos[j]] = x[j];
+      load_items<ITEMS>(a.pay[c], a.pay64[c], rr, a.n, x);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < tile_rows; i += BLOCK) {
