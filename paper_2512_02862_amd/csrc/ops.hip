@@ -318,14 +318,22 @@ __device__ __forceinline__ uint64_t match_peers(uint32_t d, uint64_t valid, int 
   return peers;
 }
 
+constexpr int kScanBlock = 256, kScanItems = 8;
 constexpr int kPartBlock = 256;
 constexpr int kPartItems = 16;
 constexpr int64_t kPartTile = int64_t{kPartBlock} * kPartItems;
 
+// The look-back words of the scan that follows, cleared on the way.
+__device__ __forceinline__ void clear_status(uint64_t *status, int64_t n) {
+  for (int64_t i = int64_t{blockIdx.x} * blockDim.x + threadIdx.x; i < n; i += int64_t{gridDim.x} * blockDim.x) status[i] = 0;
+}
+
 // Pass 1: per-tile destination histogram, stored destination-major so that one
 // exclusive scan of the flat array yields every (destination, tile) offset.
 template <int BLOCK, int ITEMS, int FMAX>
-__global__ __launch_bounds__(BLOCK) void k_part_hist(PartArgs a, int32_t *hist, int64_t ntiles) {
+__global__ __launch_bounds__(BLOCK) void k_part_hist(PartArgs a, int32_t *hist, int64_t ntiles, uint64_t *status,
+                                                    int64_t nstatus) {
+  clear_status(status, nstatus);
   constexpr int64_t TILE = int64_t{BLOCK} * ITEMS;
   __shared__ int32_t s_h[FMAX];
   for (int p = threadIdx.x; p < static_cast<int>(a.fanout); p += BLOCK) s_h[p] = 0;
@@ -349,11 +357,10 @@ __global__ __launch_bounds__(BLOCK) void k_part_hist(PartArgs a, int32_t *hist, 
   for (int p = threadIdx.x; p < static_cast<int>(a.fanout); p += BLOCK) hist[int64_t{p} * ntiles + t] = s_h[p];
 }
 
-// Exclusive scan of an int32 array (decoupled look-back); total -> *d_total.
+// Exclusive scan of an int32 array (decoupled look-back).
 template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void k_scan_excl_i32(const int32_t *in, int32_t *out, int64_t len,
-                                                        uint64_t *status, unsigned long long *ticket, int64_t ntiles,
-                                                        int64_t *d_total) {
+                                                        uint64_t *status, unsigned long long *ticket, int64_t ntiles) {
   constexpr int NW = BLOCK / kWave;
   constexpr int64_t TILE = int64_t{BLOCK} * ITEMS;
   __shared__ int64_t s_tile, s_prefix;
@@ -377,10 +384,7 @@ __global__ __launch_bounds__(BLOCK) void k_scan_excl_i32(const int32_t *in, int3
     const int64_t c = lane_id() < NW ? s_w[lane_id()] : 0;
     const int64_t agg = wave_sum(c);
     const int64_t ex = lookback_exclusive(status, t, agg);
-    if (lane_id() == 0) {
-      s_prefix = ex;
-      if (t == ntiles - 1 && d_total) *d_total = ex + agg;
-    }
+    if (lane_id() == 0) s_prefix = ex;
   }
   __syncthreads();
   int64_t run = s_prefix + incl - local;
@@ -392,13 +396,6 @@ __global__ __launch_bounds__(BLOCK) void k_scan_excl_i32(const int32_t *in, int3
   }
 }
 
-__global__ void k_part_offsets(const int32_t *scan, uint32_t fanout, int64_t ntiles, const int64_t *d_nsel, int64_t n,
-                               int64_t *d_offsets) {
-  const int64_t cnt = count_of(d_nsel, n);
-  for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p <= fanout; p += gridDim.x * blockDim.x)
-    d_offsets[p] = p < fanout ? static_cast<int64_t>(scan[int64_t{p} * ntiles]) : cnt;
-}
-
 // Pass 3: stable scatter.  Each wave ranks its rows per destination with
 // ballots; the block lays the tile out destination-major in LDS, then writes
 // every destination's run with consecutive threads on consecutive addresses
@@ -408,7 +405,9 @@ __global__ void k_part_offsets(const int32_t *scan, uint32_t fanout, int64_t nti
 // rows as four 16-byte loads.  Up to 8 destinations are counted in registers
 // and summed across the wave; more go to per-wave LDS counters.
 template <int FMAX>
-__global__ __launch_bounds__(256) void k_part_hist_i32(PartArgs a, int32_t *hist, int64_t ntiles) {
+__global__ __launch_bounds__(256) void k_part_hist_i32(PartArgs a, int32_t *hist, int64_t ntiles, uint64_t *status,
+                                                       int64_t nstatus) {
+  clear_status(status, nstatus);
   constexpr int BLOCK = 256, NW = BLOCK / kWave;
   constexpr int64_t TILE = 4096;
   __shared__ int32_t s_h[NW][FMAX];
@@ -468,7 +467,8 @@ __global__ __launch_bounds__(256) void k_part_hist_i32(PartArgs a, int32_t *hist
 }
 
 template <int BLOCK, int ITEMS, int FMAX>
-__global__ __launch_bounds__(BLOCK) void k_part_scatter(PartArgs a, const int32_t *scan, int64_t ntiles) {
+__global__ __launch_bounds__(BLOCK) void k_part_scatter(PartArgs a, const int32_t *scan, int64_t ntiles,
+                                                       int64_t *d_offsets) {
   constexpr int NW = BLOCK / kWave;
   constexpr int TILE = BLOCK * ITEMS;
   __shared__ int32_t s_cnt[NW][FMAX];
@@ -484,7 +484,9 @@ __global__ __launch_bounds__(BLOCK) void k_part_scatter(PartArgs a, const int32_
   for (int p = threadIdx.x; p < F; p += BLOCK) {
     for (int w = 0; w < NW; ++w) s_cnt[w][p] = 0;
     s_goff[p] = scan[int64_t{p} * ntiles + t];
+    if (t == 0) d_offsets[p] = s_goff[p];  // the first tile starts every destination
   }
+  if (t == 0 && threadIdx.x == 0) d_offsets[F] = cnt;
   __syncthreads();
 
   const int w = threadIdx.x / kWave, lane = lane_id();
@@ -563,28 +565,29 @@ __global__ __launch_bounds__(BLOCK) void k_part_scatter(PartArgs a, const int32_
 }
 
 template <int FMAX>
-static void launch_partition(const PartArgs &a, int32_t *hist, int32_t *scan, int64_t ntiles, hipStream_t stream,
-                             bool hist_phase) {
-  if (hist_phase && FMAX <= 64 && !a.sel && !a.key64 && !a.d_nsel && kPartTile == 4096 &&
-      (reinterpret_cast<uintptr_t>(a.key) & 15) == 0)
-    k_part_hist_i32<64><<<static_cast<unsigned>(ntiles), 256, 0, stream>>>(a, hist, ntiles);
-  else if (hist_phase)
-    k_part_hist<kPartBlock, kPartItems, FMAX><<<static_cast<unsigned>(ntiles), kPartBlock, 0, stream>>>(a, hist, ntiles);
-  else if (FMAX <= 256)
+static pyst_status launch_partition(pyst_ctx *ctx, const PartArgs &a, int32_t *hist, int32_t *scan, int64_t ntiles,
+                                    uint64_t *status, int64_t nstatus, int64_t *d_offsets, hipStream_t stream) {
+  const unsigned grid = static_cast<unsigned>(ntiles);
+  if (FMAX <= 64 && !a.sel && !a.key64 && !a.d_nsel && kPartTile == 4096 && (reinterpret_cast<uintptr_t>(a.key) & 15) == 0)
+    k_part_hist_i32<64><<<grid, 256, 0, stream>>>(a, hist, ntiles, status, nstatus);
+  else
+    k_part_hist<kPartBlock, kPartItems, FMAX><<<grid, kPartBlock, 0, stream>>>(a, hist, ntiles, status, nstatus);
+  PYST_LAUNCH_CHECK("k_part_hist");
+  k_scan_excl_i32<kScanBlock, kScanItems><<<static_cast<unsigned>(nstatus - 1), kScanBlock, 0, stream>>>(
+      hist, scan, ntiles * a.fanout, status, reinterpret_cast<unsigned long long *>(status + nstatus - 1), nstatus - 1);
+  PYST_LAUNCH_CHECK("k_scan_excl_i32");
+  TimedRegion timed(ctx, "part_scatter", stream);
+  if constexpr (FMAX <= 256)
     // the same 4096-row tiles as the histogram, as 1024 threads x 4 rows (few
     // registers per thread: 32 waves per CU; at fanout 64, 524 against 567 us
     // per 60M-row partition as 512 threads x 8 rows)
-    k_part_scatter<4 * kPartBlock, kPartItems / 4, FMAX><<<static_cast<unsigned>(ntiles), 4 * kPartBlock, 0, stream>>>(
-        a, scan, ntiles);
+    k_part_scatter<4 * kPartBlock, kPartItems / 4, FMAX><<<grid, 4 * kPartBlock, 0, stream>>>(a, scan, ntiles, d_offsets);
   else  // 1024 destinations: the per-wave counters of 16 waves would not leave LDS for two blocks
-    k_part_scatter<2 * kPartBlock, kPartItems / 2, FMAX><<<static_cast<unsigned>(ntiles), 2 * kPartBlock, 0, stream>>>(
-        a, scan, ntiles);
+    k_part_scatter<2 * kPartBlock, kPartItems / 2, FMAX><<<grid, 2 * kPartBlock, 0, stream>>>(a, scan, ntiles, d_offsets);
+  PYST_LAUNCH_CHECK("k_part_scatter");
+  return PYST_OK;
 }
 
-pyst_status scan_excl_i32(pyst_ctx *ctx, const int32_t *in, int32_t *out, int64_t len, int64_t *d_total,
-                          hipStream_t stream);
-
-constexpr int kScanBlock = 256, kScanItems = 8;
 
 // Scratch of one partition: per-tile destination counts, their exclusive scan
 // and the scan's look-back status words.
@@ -596,11 +599,11 @@ static size_t partition_scratch_bytes(int64_t n, uint32_t fanout) {
   return counts + static_cast<size_t>(stiles + 1) * sizeof(uint64_t);
 }
 
-pyst_status scan_excl_i32_ws(const int32_t *in, int32_t *out, int64_t len, int64_t *d_total, uint64_t *status,
-                             hipStream_t stream);
-
-// histogram -> scan -> (offsets) -> stable scatter, in `ws` of
+// histogram -> scan -> stable scatter, in `ws` of
 // partition_scratch_bytes(a.n, a.fanout) bytes; ctx (may be null) only for timing.
+// Three launches: the histogram clears the scan's look-back words and the scatter
+// writes the offsets (five took 37.6 us for 300k filtered rows to 9 destinations,
+// with the filter, 34.5).
 static pyst_status partition_run_ws(pyst_ctx *ctx, const PartArgs &a, int64_t *d_offsets, void *ws,
                                     hipStream_t stream) {
   const int64_t ntiles = std::max<int64_t>(1, ceil_div(a.n, kPartTile));
@@ -609,50 +612,16 @@ static pyst_status partition_run_ws(pyst_ctx *ctx, const PartArgs &a, int64_t *d
   int32_t *scan = hist + hlen + 64;
   uint64_t *status = reinterpret_cast<uint64_t *>(static_cast<char *>(ws) +
                                                   (static_cast<size_t>(2 * hlen) * sizeof(int32_t) + 256 + 255) / 256 * 256);
-  if (a.fanout <= 64) launch_partition<64>(a, hist, scan, ntiles, stream, true);
-  else if (a.fanout <= 256) launch_partition<256>(a, hist, scan, ntiles, stream, true);
-  else launch_partition<1024>(a, hist, scan, ntiles, stream, true);
-  PYST_LAUNCH_CHECK("k_part_hist");
-  pyst_status st = scan_excl_i32_ws(hist, scan, hlen, nullptr, status, stream);
-  if (st != PYST_OK) return st;
-  if (d_offsets) {
-    k_part_offsets<<<static_cast<unsigned>(ceil_div(a.fanout + 1, 256)), 256, 0, stream>>>(scan, a.fanout, ntiles,
-                                                                                          a.d_nsel, a.n, d_offsets);
-    PYST_LAUNCH_CHECK("k_part_offsets");
-  }
-  TimedRegion timed(ctx, "part_scatter", stream);
-  if (a.fanout <= 64) launch_partition<64>(a, hist, scan, ntiles, stream, false);
-  else if (a.fanout <= 256) launch_partition<256>(a, hist, scan, ntiles, stream, false);
-  else launch_partition<1024>(a, hist, scan, ntiles, stream, false);
-  PYST_LAUNCH_CHECK("k_part_scatter");
-  return PYST_OK;
+  const int64_t nstatus = std::max<int64_t>(1, ceil_div(hlen, int64_t{kScanBlock} * kScanItems)) + 1;
+  if (a.fanout <= 64) return launch_partition<64>(ctx, a, hist, scan, ntiles, status, nstatus, d_offsets, stream);
+  if (a.fanout <= 256) return launch_partition<256>(ctx, a, hist, scan, ntiles, status, nstatus, d_offsets, stream);
+  return launch_partition<1024>(ctx, a, hist, scan, ntiles, status, nstatus, d_offsets, stream);
 }
 
 static pyst_status partition_run(pyst_ctx *ctx, const PartArgs &a, int64_t *d_offsets, hipStream_t stream) {
   Scratch sc(ctx, partition_scratch_bytes(a.n, a.fanout), stream);
   if (!sc.p) return set_error(PYST_ERR_NOMEM, "partition: arena exhausted");
   return partition_run_ws(ctx, a, d_offsets, sc.p, stream);
-}
-
-// Exclusive scan with caller-provided look-back status: (tiles + 1) words,
-// cleared here by a kernel.
-pyst_status scan_excl_i32_ws(const int32_t *in, int32_t *out, int64_t len, int64_t *d_total, uint64_t *status,
-                             hipStream_t stream) {
-  const int64_t ntiles = std::max<int64_t>(1, ceil_div(len, int64_t{kScanBlock} * kScanItems));
-  pyst_status st = fill_u64(status, ntiles + 1, 0, stream);
-  if (st != PYST_OK) return st;
-  k_scan_excl_i32<kScanBlock, kScanItems><<<static_cast<unsigned>(ntiles), kScanBlock, 0, stream>>>(
-      in, out, len, status, reinterpret_cast<unsigned long long *>(status + ntiles), ntiles, d_total);
-  PYST_LAUNCH_CHECK("k_scan_excl_i32");
-  return PYST_OK;
-}
-
-pyst_status scan_excl_i32(pyst_ctx *ctx, const int32_t *in, int32_t *out, int64_t len, int64_t *d_total,
-                          hipStream_t stream) {
-  const int64_t ntiles = std::max<int64_t>(1, ceil_div(len, int64_t{kScanBlock} * kScanItems));
-  Scratch sc(ctx, (ntiles + 1) * sizeof(uint64_t), stream);
-  if (!sc.p) return set_error(PYST_ERR_NOMEM, "scan: arena exhausted");
-  return scan_excl_i32_ws(in, out, len, d_total, sc.as<uint64_t>(), stream);
 }
 
 // ============================================================== join build / probe

@@ -166,8 +166,6 @@ pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key,
                           int mode, uint64_t *few_status, hipStream_t stream);
 pyst_status filter_impl(pyst_ctx *ctx, const PredSet &ps, int64_t n, int32_t *sel_out, int64_t *d_nsel,
                         hipStream_t stream);
-pyst_status scan_excl_i32(pyst_ctx *ctx, const int32_t *in, int32_t *out, int64_t len, int64_t *d_total,
-                          hipStream_t stream);
 pyst_status sort_pairs_by_key(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const int64_t *d_count, int64_t cap,
                               int key_bits, hipStream_t stream);
 int grid_for(pyst_ctx *ctx, int64_t work, int block, int per_cu);
