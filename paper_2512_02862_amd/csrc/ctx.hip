@@ -12,7 +12,8 @@
 // earlier work), and an allocation on a stream first takes back the smallest
 // block that stream freed; no event is recorded for this, since each event
 // record is a packet of its own in the stream (a query that freed three blocks
-// ran 20 us slower per call for them).  Only when another stream needs the
+// ran 20 us slower per call for them).  Neighbouring blocks that one stream freed
+// are joined again.  Only when another stream needs the
 // memory is one event recorded per stream that holds pending blocks; those
 // blocks return to the shared free list once it has completed.
 #include <algorithm>
@@ -207,29 +208,46 @@ static void *arena_alloc(pyst_ctx *c, size_t bytes, hipStream_t stream, bool wai
 void *ctx_alloc(pyst_ctx *c, size_t bytes, hipStream_t stream) { return arena_alloc(c, bytes, stream, true); }
 void *ctx_try_alloc(pyst_ctx *c, size_t bytes, hipStream_t stream) { return arena_alloc(c, bytes, stream, false); }
 
-void ctx_free(pyst_ctx *c, void *p, hipStream_t stream) {
-  if (!p) return;
-  const size_t off = static_cast<size_t>(static_cast<char *>(p) - c->base);
-  auto it = c->live.find(off);
-  if (it == c->live.end()) return;
-  const size_t size = it->second;
+// Takes the live block at p off the books; false if there is none.
+static bool take_live(pyst_ctx *c, void *p, size_t *off, size_t *size) {
+  if (!p) return false;
+  *off = static_cast<size_t>(static_cast<char *>(p) - c->base);
+  auto it = c->live.find(*off);
+  if (it == c->live.end()) return false;
+  *size = it->second;
   c->live.erase(it);
-  c->used -= size;
+  c->used -= *size;
+  return true;
+}
+
+void ctx_free(pyst_ctx *c, void *p, hipStream_t stream) {
+  size_t off, size;
+  if (!take_live(c, p, &off, &size)) return;
+  // Neighbours that the same stream freed become one block again: what an
+  // allocation split off returns to it, so scratch of one size is found again
+  // however often blocks of other sizes were taken from it in between.
+  for (auto it = c->pending.begin(); it != c->pending.end();) {
+    if (it->stream == stream && !it->ev && (it->off + it->size == off || off + size == it->off)) {
+      off = std::min(off, it->off);
+      size += it->size;
+      it = c->pending.erase(it);
+    } else {
+      ++it;
+    }
+  }
   c->pending.push_back({off, size, stream, nullptr});
 }
 
 void ctx_free_eager(pyst_ctx *c, void *p, hipStream_t stream) {
-  if (!p) return;
-  ctx_free(c, p, stream);
+  size_t off, size;
+  if (!take_live(c, p, &off, &size)) return;
   hipEvent_t ev = take_event(c);
   if (ev && hipEventRecord(ev, stream) == hipSuccess) {
-    c->pending.back().ev = ev;
+    c->pending.push_back({off, size, stream, ev});
   } else {
     if (ev) c->events.push_back(ev);
     (void)hipStreamSynchronize(stream);
-    const auto blk = c->pending.back();
-    c->pending.pop_back();
-    insert_free(c, blk.off, blk.size);
+    insert_free(c, off, size);
   }
 }
 

@@ -16,7 +16,9 @@
 // compacts the matches.
 //
 // Bound by streams: 60M build rows 12 + 20 bytes a row, 160M probe rows about 24
-// bytes a row.  Measured: JOIN_FIGURES
+// bytes a row.  60M x 160M with 4 columns a side: build 2911 -> 880 us, probe 5064
+// -> 1585 us, the whole join 12.84 -> 7.10 ms (4.6 of them the gathers of the
+// columns, at 5.5 TB/s); 5M x 15M 834 -> 406 us.
 //
 // The choice is made on the device from the build keys' range: direct where the
 // keys span no more values than the hash table has slots, else the hash table's
@@ -33,18 +35,79 @@ constexpr int kSliceLg = 18;
 constexpr uint16_t kNoMatchPos = 0xffff;
 constexpr int kJoinRangeBlocks = 2048;
 
+// A move of rows to slices and, for probes, the way back.
+struct Slices {
+  RangeCounts counts;
+  int pass;             // row set of the counts
+  int64_t *moved;       // rows moved in all
+  void *items;          // moved items, then (probes) their results in place
+  // probes only:
+  uint64_t *status;     // look-back words of the emitting kernel, one per tile
+  unsigned long long *ticket;
+  int64_t ntiles;       // tiles of all n rows
+  uint64_t *found;      // bit per moved item (hash tables; a direct result is -1 for none)
+  uint16_t *pos;        // per row: its place among its tile's moved items
+  uint8_t *slice;       // per (tile, place): the slice
+  uint32_t *goff;       // per (tile, slice): where place 0 of the tile would lie
+  int32_t *live;        // per tile: moved items
+};
+
 struct DirectJoin {
   JoinPlan *plan;
   int32_t *array;       // row id by key - kmin, -1 for none
-  RangeCounts counts;   // pass 0: build, 1: probe
-  uint64_t *status;     // look-back words of the emitting kernel, one per probe tile
-  int64_t ntiles;       // probe tiles
-  uint64_t *pairs;      // moved build rows: offset | row << 32
-  uint32_t *moved;      // moved probe offsets, then their build rows (in place)
-  uint16_t *pos;        // per probe row: its place in its tile's moved keys
-  uint8_t *slice;       // per (tile, place): the slice
-  uint32_t *goff;       // per (tile, slice): where place 0 of the tile would lie
-  int32_t *live;        // per tile: moved keys
+  Slices build, probe;
+};
+
+template <bool K64>
+using ColumnKey = std::conditional_t<K64, int64_t, int32_t>;
+template <bool K64>
+constexpr ColumnKey<K64> kColumnEmpty = K64 ? static_cast<ColumnKey<K64>>(kEmpty64) : static_cast<ColumnKey<K64>>(kEmpty32);
+constexpr uint32_t kDead = 0xffffffffu;  // slice of a row that is not moved
+
+// What moves: the slice of a key and the item that travels for its row.
+template <bool K64, bool BUILD>
+struct DirectRows {
+  static constexpr bool kWide = K64, kProbe = !BUILD;
+  using Item = std::conditional_t<BUILD, uint64_t, uint32_t>;
+  const JoinPlan *plan;
+  int64_t kmin = 0;
+  uint64_t range = 0;
+  int shift = 0;
+  __device__ __forceinline__ bool open() {
+    kmin = plan->kmin;
+    range = plan->range;
+    shift = plan->shift;
+    return plan->direct != 0;
+  }
+  __device__ __forceinline__ uint64_t offset(int64_t k) const { return static_cast<uint64_t>(k) - static_cast<uint64_t>(kmin); }
+  __device__ __forceinline__ uint32_t slice(int64_t k) const {
+    return offset(k) < range ? static_cast<uint32_t>(offset(k) >> shift) : kDead;
+  }
+  __device__ __forceinline__ Item item(int64_t k, int32_t row) const {
+    if constexpr (BUILD) return static_cast<uint32_t>(offset(k)) | (static_cast<uint64_t>(static_cast<uint32_t>(row)) << 32);
+    else return static_cast<uint32_t>(offset(k));
+  }
+};
+
+// Probe keys of a hash table with 8-byte (int32 keys) or 16-byte slots, by home slot.
+template <bool WIDE, bool K64>
+struct HashRows {
+  static constexpr bool kWide = K64, kProbe = true;
+  using Item = std::conditional_t<WIDE, uint64_t, uint32_t>;
+  const JoinPlan *plan;  // may be null
+  const int64_t *hdr;
+  int shift;             // slots a slice
+  int64_t mask = 0;
+  __device__ __forceinline__ bool open() {
+    mask = hdr[0] - 1;
+    return !(plan && plan->direct);
+  }
+  __device__ __forceinline__ uint32_t slice(int64_t k) const {
+    if constexpr (WIDE) return static_cast<uint32_t>((table_hash64(k) & static_cast<uint64_t>(mask)) >> shift);
+    if (K64 && (k <= kEmpty32 || k > INT32_MAX)) return kDead;  // no int32 key of the table
+    return static_cast<uint32_t>((table_hash32(static_cast<int32_t>(k)) & static_cast<uint64_t>(mask)) >> shift);
+  }
+  __device__ __forceinline__ Item item(int64_t k, int32_t) const { return static_cast<Item>(k); }
 };
 
 template <bool K64>
@@ -118,82 +181,89 @@ __global__ __launch_bounds__(256) void k_direct_clear(DirectJoin d) {
   const int64_t quads = static_cast<int64_t>((d.plan->range + 3) / 4);  // the array has room for whole quads
   const v4i32 none = {-1, -1, -1, -1};
   for (int64_t i = i0; i < quads; i += step) reinterpret_cast<v4i32 *>(d.array)[i] = none;
-  for (int64_t i = i0; i < d.ntiles; i += step) d.status[i] = 0;
 }
 
-template <bool K64>
-__global__ __launch_bounds__(kRangeThreads, 8) void k_slice_hist(DirectJoin d, int pass, const void *key, int64_t n) {
+template <typename P>
+__global__ __launch_bounds__(kRangeThreads, 8) void k_slice_hist(P p, Slices d, const void *key, const int32_t *sel,
+                                                                const int64_t *d_nsel, int64_t n_all) {
+  using KeyT = ColumnKey<P::kWide>;
   __shared__ uint32_t s_h[kRangeDigits];
   int64_t part, t0, t1;
-  if (!d.plan->direct || !range_of_block(n, kSliceTile, part, t0, t1)) return;
-  const int tid = static_cast<int>(threadIdx.x), shift = d.plan->shift;
-  const int64_t kmin = d.plan->kmin;
-  const uint64_t range = d.plan->range;
+  const int64_t n = std::min(count_of(d_nsel, n_all), n_all);
+  if (!p.open()) return;
+  const int tid = static_cast<int>(threadIdx.x);
+  if (P::kProbe)
+    for (int64_t i = int64_t{blockIdx.x} * kRangeThreads + tid; i < d.ntiles; i += int64_t{gridDim.x} * kRangeThreads) d.status[i] = 0;
+  if (!range_of_block(n, kSliceTile, part, t0, t1)) return;
   if (tid < kRangeDigits) s_h[tid] = 0;
   __syncthreads();
   const int64_t hi = t1 * kSliceTile < n ? t1 * kSliceTile : n;
   for (int64_t i0 = t0 * kSliceTile + tid; i0 < hi; i0 += kSliceTile) {
-    int64_t k[kSliceItems];
-    bool ok[kSliceItems];
+    int64_t row[kSliceItems];
+    KeyT k[kSliceItems];
 #pragma unroll
-    for (int u = 0; u < kSliceItems; ++u) {
-      const int64_t i = i0 + u * kRangeThreads;
-      ok[u] = slice_key<K64>(key, i < hi ? i : i0, k[u]) && i < hi;
+    for (int u = 0; u < kSliceItems; ++u) row[u] = i0 + u * kRangeThreads < hi ? i0 + u * kRangeThreads : i0;
+    if (sel) {
+#pragma unroll
+      for (int u = 0; u < kSliceItems; ++u) row[u] = sel[row[u]];
     }
 #pragma unroll
+    for (int u = 0; u < kSliceItems; ++u) k[u] = static_cast<const KeyT *>(key)[row[u]];
+#pragma unroll
     for (int u = 0; u < kSliceItems; ++u) {
-      const uint64_t off = static_cast<uint64_t>(k[u]) - static_cast<uint64_t>(kmin);
-      if (ok[u] && off < range) atomicAdd(&s_h[off >> shift], 1u);
+      const uint32_t sl = p.slice(k[u]);
+      if (i0 + u * kRangeThreads < hi && k[u] != kColumnEmpty<P::kWide> && sl != kDead) atomicAdd(&s_h[sl], 1u);
     }
   }
   __syncthreads();
   if (tid < kRangeDigits) {
     d.counts.of_part(part)[tid] = s_h[tid];
-    if (s_h[tid]) atomicAdd(&d.counts.of_group(pass, part / kRangeGroup)[tid], s_h[tid]);
+    if (s_h[tid]) atomicAdd(&d.counts.of_group(d.pass, part / kRangeGroup)[tid], s_h[tid]);
   }
 }
 
-// Moves the offsets (BUILD: with their rows) of a block's range of tiles to
-// their slices.  A tile is laid out by slice in LDS and leaves as one run a
-// slice.  Two blocks of 16 waves per CU.
-template <bool K64, bool BUILD>
-__global__ __launch_bounds__(kRangeThreads, 8) void k_slice_move(DirectJoin d, const void *key, int64_t n) {
-  using Item = std::conditional_t<BUILD, uint64_t, uint32_t>;
-  using KeyT = std::conditional_t<K64, int64_t, int32_t>;
-  constexpr KeyT kColEmpty = K64 ? static_cast<KeyT>(kEmpty64) : static_cast<KeyT>(kEmpty32);
-  constexpr uint32_t kDead = 0xffffffffu;
+// Moves the items of a block's range of tiles to their slices.  A tile is laid
+// out by slice in LDS and leaves as one run a slice.  Two blocks of 16 waves per
+// CU.
+template <typename P>
+__global__ __launch_bounds__(kRangeThreads, 8) void k_slice_move(P p, Slices d, const void *key, const int32_t *sel,
+                                                                const int64_t *d_nsel, int64_t n_all) {
+  using Item = typename P::Item;
+  using KeyT = ColumnKey<P::kWide>;
   __shared__ __align__(16) Item s_stage[kSliceTile];
   __shared__ uint8_t s_dig[kSliceTile];
   __shared__ int32_t s_cnt[kRangeDigits], s_start[kRangeDigits];
   __shared__ int64_t s_next[kRangeDigits];
   __shared__ int32_t s_live;
   static_assert(sizeof(RangeOffsets) <= sizeof(s_stage), "the offsets are summed in the staging area");
+  static_assert(kSliceTile <= 1 << 16, "a slice and a rank share a word");
   int64_t part, t0, t1;
-  if (!d.plan->direct || !range_of_block(n, kSliceTile, part, t0, t1)) return;
-  const int tid = static_cast<int>(threadIdx.x), lane = lane_id(), shift = d.plan->shift;
-  const int64_t kmin = d.plan->kmin;
-  const uint64_t range = d.plan->range;
-  const int64_t total = range_offsets(d.counts, BUILD ? 0 : 1, static_cast<int>(part),
+  const int64_t n = std::min(count_of(d_nsel, n_all), n_all);
+  if (!p.open() || !range_of_block(n, kSliceTile, part, t0, t1)) return;
+  const int tid = static_cast<int>(threadIdx.x), lane = lane_id();
+  const int64_t total = range_offsets(d.counts, d.pass, static_cast<int>(part),
                                       *reinterpret_cast<RangeOffsets *>(s_stage), s_next);
-  if (part == 0 && tid == 0) d.plan->moved[BUILD ? 0 : 1] = total;
+  if (part == 0 && tid == 0) *d.moved = total;
+  const int32_t last = static_cast<int32_t>(n) - 1;
   for (int64_t t = t0; t < t1; ++t) {  // block-uniform
     if (tid < kRangeDigits) s_cnt[tid] = 0;
-    const int32_t base = static_cast<int32_t>(t) * kSliceTile + tid, last = static_cast<int32_t>(n) - 1;
+    const int32_t base = static_cast<int32_t>(t) * kSliceTile + tid;
     KeyT k[kSliceItems];
+    if (sel) {
 #pragma unroll
-    for (int u = 0; u < kSliceItems; ++u) {
-      const int32_t i = base + u * kRangeThreads;
-      k[u] = static_cast<const KeyT *>(key)[i < last ? i : last];
+      for (int u = 0; u < kSliceItems; ++u) k[u] = static_cast<const KeyT *>(key)[sel[std::min(base + u * kRangeThreads, last)]];
+    } else {
+#pragma unroll
+      for (int u = 0; u < kSliceItems; ++u) k[u] = static_cast<const KeyT *>(key)[std::min(base + u * kRangeThreads, last)];
     }
     __syncthreads();  // the counters are clear, the previous tile has left the staging area
-    uint32_t off[kSliceItems];  // kDead: no row, an EMPTY key, or one outside the build keys' range
-    int32_t rank[kSliceItems];
+    uint32_t at[kSliceItems];  // slice << 16 | rank among the tile's items of the slice; kDead: not moved
 #pragma unroll
     for (int u = 0; u < kSliceItems; ++u) {
-      const uint64_t o = static_cast<uint64_t>(static_cast<int64_t>(k[u])) - static_cast<uint64_t>(kmin);
-      const bool ok = k[u] != kColEmpty && base + u * kRangeThreads <= last && o < range;
-      off[u] = ok ? static_cast<uint32_t>(o) : kDead;
-      rank[u] = ok ? atomicAdd(&s_cnt[off[u] >> shift], 1) : 0;
+      const uint32_t sl = p.slice(k[u]);
+      at[u] = kDead;
+      if (k[u] != kColumnEmpty<P::kWide> && base + u * kRangeThreads <= last && sl != kDead)
+        at[u] = sl << 16 | static_cast<uint32_t>(atomicAdd(&s_cnt[sl], 1));
     }
     __syncthreads();
     if (tid < kWave) {
@@ -205,7 +275,7 @@ __global__ __launch_bounds__(kRangeThreads, 8) void k_slice_move(DirectJoin d, c
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         s_start[lane * 4 + j] = ra;
-        s_next[lane * 4 + j] -= ra;  // the key at place p goes to s_next + p
+        s_next[lane * 4 + j] -= ra;  // the item at place p goes to s_next + p
         ra += a[j];
       }
       if (lane == kWave - 1) s_live = incl;
@@ -214,27 +284,22 @@ __global__ __launch_bounds__(kRangeThreads, 8) void k_slice_move(DirectJoin d, c
 #pragma unroll
     for (int u = 0; u < kSliceItems; ++u) {
       const int32_t i = base + u * kRangeThreads;
-      int32_t p = kNoMatchPos;
-      if (off[u] != kDead) {
-        const uint32_t s = off[u] >> shift;
-        p = s_start[s] + rank[u];
-        s_dig[p] = static_cast<uint8_t>(s);
-        if constexpr (BUILD) s_stage[p] = off[u] | (static_cast<uint64_t>(static_cast<uint32_t>(i)) << 32);
-        else s_stage[p] = off[u];
+      int32_t place = kNoMatchPos;
+      if (at[u] != kDead) {
+        place = s_start[at[u] >> 16] + static_cast<int32_t>(at[u] & 0xffff);
+        s_dig[place] = static_cast<uint8_t>(at[u] >> 16);
+        s_stage[place] = p.item(k[u], i);
       }
-      if (!BUILD && i <= last) d.pos[i] = static_cast<uint16_t>(p);
+      if (P::kProbe && i <= last) d.pos[i] = static_cast<uint16_t>(place);
     }
     __syncthreads();
     const int live = s_live;
-    for (int p = tid; p < live; p += kRangeThreads) {
-      const int s = s_dig[p];
-      if constexpr (BUILD) d.pairs[s_next[s] + p] = s_stage[p];
-      else {
-        d.moved[s_next[s] + p] = s_stage[p];
-        d.slice[t * kSliceTile + p] = static_cast<uint8_t>(s);
-      }
+    for (int i = tid; i < live; i += kRangeThreads) {
+      const int sl = s_dig[i];
+      static_cast<Item *>(d.items)[s_next[sl] + i] = s_stage[i];
+      if (P::kProbe) d.slice[t * kSliceTile + i] = static_cast<uint8_t>(sl);
     }
-    if (!BUILD) {
+    if (P::kProbe) {
       if (tid < kRangeDigits) d.goff[t * kRangeDigits + tid] = static_cast<uint32_t>(s_next[tid]);
       if (tid == 0) d.live[t] = live;
     }
@@ -244,16 +309,18 @@ __global__ __launch_bounds__(kRangeThreads, 8) void k_slice_move(DirectJoin d, c
 }
 
 // Every moved build row into the array.  Blocks take consecutive pieces in
-// XCD-major order, so that a slice is written through one L2.
+// XCD-major order, so that a slice is written through one L2.  (As many blocks as
+// pieces: blocks that walk several drift apart, and with them the slices in use;
+// 8 a CU measured 1003 us against 452 for 60M rows, the lookup 649 against 401.)
 __global__ __launch_bounds__(256) void k_direct_store(DirectJoin d) {
   if (!d.plan->direct) return;
   constexpr int U = 8;
-  const int64_t n = d.plan->moved[0], blocks = (n + 256 * U - 1) / (256 * U);
+  const int64_t n = *d.build.moved, blocks = (n + 256 * U - 1) / (256 * U);
   if (blockIdx.x >= blocks) return;
   const int64_t i0 = xcd_block(blockIdx.x, blocks) * (256 * U) + threadIdx.x;
   uint64_t p[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) p[u] = i0 + u * 256 < n ? __builtin_nontemporal_load(&d.pairs[i0 + u * 256]) : 0;
+  for (int u = 0; u < U; ++u) p[u] = i0 + u * 256 < n ? __builtin_nontemporal_load(static_cast<const uint64_t *>(d.build.items) + i0 + u * 256) : 0;
 #pragma unroll
   for (int u = 0; u < U; ++u)
     if (i0 + u * 256 < n) d.array[static_cast<uint32_t>(p[u])] = static_cast<int32_t>(p[u] >> 32);
@@ -279,36 +346,100 @@ __global__ __launch_bounds__(256) void k_direct_filled(DirectJoin d) {
 __global__ __launch_bounds__(256) void k_direct_lookup(DirectJoin d) {
   if (!d.plan->direct) return;
   constexpr int U = 8;
-  const int64_t n = d.plan->moved[1], blocks = (n + 256 * U - 1) / (256 * U);  // the blocks that have rows
+  const int64_t n = *d.probe.moved, blocks = (n + 256 * U - 1) / (256 * U);  // the blocks that have rows
   if (blockIdx.x >= blocks) return;
   const int64_t i0 = xcd_block(blockIdx.x, blocks) * (256 * U) + threadIdx.x;
+  uint32_t *items = static_cast<uint32_t *>(d.probe.items);
   uint32_t o[U];
   int32_t r[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) o[u] = i0 + u * 256 < n ? __builtin_nontemporal_load(&d.moved[i0 + u * 256]) : 0;
+  for (int u = 0; u < U; ++u) o[u] = i0 + u * 256 < n ? __builtin_nontemporal_load(&items[i0 + u * 256]) : 0;
 #pragma unroll
   for (int u = 0; u < U; ++u) r[u] = d.array[o[u]];
 #pragma unroll
   for (int u = 0; u < U; ++u)
-    if (i0 + u * 256 < n) __builtin_nontemporal_store(static_cast<uint32_t>(r[u]), &d.moved[i0 + u * 256]);
+    if (i0 + u * 256 < n) __builtin_nontemporal_store(static_cast<uint32_t>(r[u]), &items[i0 + u * 256]);
+}
+
+// The payload of every moved probe key of a hash table with unique keys, in
+// place of the key, and a bit for those that have one.  A lane's keys walk their
+// runs together, in the L2's slice of the table.
+template <bool WIDE, bool K64>
+__global__ __launch_bounds__(256) void k_hash_lookup(HashRows<WIDE, K64> p, Slices d, const uint64_t *slots) {
+  using Item = typename HashRows<WIDE, K64>::Item;
+  using Stored = std::conditional_t<WIDE, int64_t, int32_t>;
+  constexpr int U = WIDE ? 4 : 8;
+  constexpr int64_t GS = WIDE ? 1 : 2;
+  if (!p.open()) return;
+  const int64_t n = *d.moved, blocks = (n + 256 * U - 1) / (256 * U), mask = p.mask;
+  if (blockIdx.x >= blocks) return;
+  const int64_t i0 = xcd_block(blockIdx.x, blocks) * (256 * U) + threadIdx.x;
+  Item *items = static_cast<Item *>(d.items);
+  Stored k[U], pay[U];
+  int32_t c[U];
+  uint32_t on = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    k[u] = static_cast<Stored>(i0 + u * 256 < n ? __builtin_nontemporal_load(&items[i0 + u * 256]) : 0);
+    on |= i0 + u * 256 < n ? 1u << u : 0;
+    c[u] = 0;
+    pay[u] = 0;
+  }
+  for (int64_t step = 0; step <= mask && __any(on != 0); step += GS) {
+    ulonglong2 g[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int64_t s;
+      if constexpr (WIDE) s = static_cast<int64_t>((table_hash64(k[u]) & static_cast<uint64_t>(mask)) + step) & mask;
+      else s = static_cast<int64_t>((table_hash32(k[u]) & static_cast<uint64_t>(mask) & ~uint64_t{1}) + step) & mask;
+      if ((on >> u) & 1) g[u] = *reinterpret_cast<const ulonglong2 *>(&slots[WIDE ? 2 * s : s]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!((on >> u) & 1)) continue;
+      bool more;
+      if constexpr (WIDE) more = visit_wide(g[u], k[u], 1, c[u], pay[u]);
+      else more = visit_pair(g[u], k[u], 1, c[u], pay[u]);
+      if (!more) on &= ~(1u << u);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint64_t m = __ballot(c[u] != 0);
+    const int64_t i = i0 + u * 256;
+    if (i < n) {
+      __builtin_nontemporal_store(static_cast<Item>(pay[u]), &items[i]);
+      if (lane_id() == 0) d.found[i / kWave] = m;  // i is a multiple of 64 in lane 0
+    }
+  }
 }
 
 // Matches in ascending probe row: a tile's results back in row order, compacted
-// by look-back over the tiles.
-__global__ __launch_bounds__(kRangeThreads, 8) void k_direct_emit(DirectJoin d, int64_t n, int32_t *out_row,
-                                                                 int32_t *out_build, int64_t out_cap, int64_t *d_nout,
-                                                                 uint32_t *err) {
+// by look-back over the tiles.  HASH: results are payloads with found bits, else
+// build rows, -1 for none.
+template <typename Item, bool HASH, typename PayT>
+__global__ __launch_bounds__(kRangeThreads, 8) void k_slice_emit(const JoinPlan *plan, Slices d, const int32_t *sel,
+                                                                const int64_t *d_nsel, int64_t n_all, int32_t *out_row,
+                                                                PayT *out_pay, int64_t out_cap, int64_t *d_nout,
+                                                                uint32_t *err) {
   constexpr int NW = kRangeThreads / kWave;
-  __shared__ int32_t s_res[kSliceTile];
+  using Res = std::make_signed_t<Item>;
+  __shared__ Res s_res[kSliceTile];
+  __shared__ uint8_t s_ok[HASH ? kSliceTile : 1];
   __shared__ uint32_t s_goff[kRangeDigits];
   __shared__ int32_t s_w[NW];
   __shared__ int64_t s_tile, s_prefix;
-  if (!d.plan->direct) return;
+  if (plan && (plan->direct != 0) == HASH) return;
+  const int64_t n = std::min(count_of(d_nsel, n_all), n_all), ntiles = (n + kSliceTile - 1) / kSliceTile;
   const int tid = static_cast<int>(threadIdx.x), w = tid / kWave, lane = lane_id();
-  if (tid == 0) s_tile = static_cast<int64_t>(atomicAdd(&d.plan->ticket, 1ull));
+  if (blockIdx.x >= ntiles) {
+    if (ntiles == 0 && blockIdx.x == 0 && tid == 0) *d_nout = 0;
+    return;
+  }
+  if (tid == 0) s_tile = static_cast<int64_t>(atomicAdd(d.ticket, 1ull));
   __syncthreads();
   const int64_t t = s_tile;
-  if (t == 0 && tid == 0 && d.plan->filled != static_cast<unsigned long long>(d.plan->moved[0])) latch(err, kErrDup);
+  if (!HASH && t == 0 && tid == 0 && plan->filled != static_cast<unsigned long long>(plan->moved[0])) latch(err, kErrDup);
   const int live = d.live[t];
   if (tid < kRangeDigits) s_goff[tid] = d.goff[t * kRangeDigits + tid];
   const int64_t base = t * kSliceTile + w * (kWave * kSliceItems) + lane;
@@ -320,21 +451,34 @@ __global__ __launch_bounds__(kRangeThreads, 8) void k_direct_emit(DirectJoin d, 
     sl[u] = d.slice[t * kSliceTile + u * kRangeThreads + tid];  // (undefined past the live ones: not used)
   }
   __syncthreads();
-  int32_t r[kSliceItems];
+  {
+    Res x[kSliceItems];
+    uint8_t f[kSliceItems];
 #pragma unroll
-  for (int u = 0; u < kSliceItems; ++u) {
-    const int p = u * kRangeThreads + tid;
-    r[u] = p < live ? static_cast<int32_t>(__builtin_nontemporal_load(&d.moved[int64_t{s_goff[sl[u]]} + p])) : -1;
+    for (int u = 0; u < kSliceItems; ++u) {
+      const int p = u * kRangeThreads + tid;
+      x[u] = -1;
+      f[u] = 0;
+      if (p < live) {
+        const int64_t g = int64_t{s_goff[sl[u]]} + p;
+        x[u] = static_cast<Res>(__builtin_nontemporal_load(static_cast<const Item *>(d.items) + g));
+        if (HASH) f[u] = reinterpret_cast<const uint8_t *>(d.found)[g >> 3] >> (g & 7) & 1;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kSliceItems; ++u) {
+      s_res[u * kRangeThreads + tid] = x[u];
+      if (HASH) s_ok[u * kRangeThreads + tid] = f[u];
+    }
   }
-#pragma unroll
-  for (int u = 0; u < kSliceItems; ++u) s_res[u * kRangeThreads + tid] = r[u];
   __syncthreads();
   uint64_t m[kSliceItems];
   int cnt = 0;
 #pragma unroll
   for (int u = 0; u < kSliceItems; ++u) {
-    r[u] = pos[u] != kNoMatchPos && base + u * kWave < n ? s_res[pos[u]] : -1;
-    m[u] = __ballot(r[u] >= 0);
+    const bool moved = pos[u] != kNoMatchPos && base + u * kWave < n;
+    const bool hit = moved && (HASH ? s_ok[pos[u]] != 0 : s_res[pos[u]] >= 0);
+    m[u] = __ballot(hit);
     cnt += __popcll(m[u]);
   }
   if (lane == 0) s_w[w] = cnt;
@@ -344,7 +488,7 @@ __global__ __launch_bounds__(kRangeThreads, 8) void k_direct_emit(DirectJoin d, 
     const int64_t agg = wave_sum(c), ex = lookback_exclusive(d.status, t, agg);
     if (lane == 0) {
       s_prefix = ex;
-      if (t == d.ntiles - 1) {
+      if (t == ntiles - 1) {
         *d_nout = ex + agg;
         if (ex + agg > out_cap) latch(err, kErrCapacity);
       }
@@ -356,9 +500,9 @@ __global__ __launch_bounds__(kRangeThreads, 8) void k_direct_emit(DirectJoin d, 
 #pragma unroll
   for (int u = 0; u < kSliceItems; ++u) {
     const int64_t p = at + mbcnt(m[u]);
-    if (r[u] >= 0 && p < out_cap) {
-      out_row[p] = static_cast<int32_t>(base + u * kWave);
-      out_build[p] = r[u];
+    if (((m[u] >> lane) & 1ull) && p < out_cap) {
+      out_row[p] = static_cast<int32_t>(row_of(sel, base + u * kWave));
+      out_pay[p] = static_cast<PayT>(s_res[pos[u]]);
     }
     at += __popcll(m[u]);
   }
@@ -375,45 +519,64 @@ bool direct_join_wanted(const pyst_col *build_key, const pyst_col *probe_key, in
 
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
-// Scratch beside the array, and its layout at `mem` (null: the size alone).
-static size_t direct_layout(char *mem, int64_t nb, int64_t np, DirectJoin *d, int64_t **lo) {
-  const int parts = std::max(range_parts(nb, kSliceTile), range_parts(np, kSliceTile));
-  const int64_t ntiles = ceil_div(np, kSliceTile);
+// A cursor over scratch memory (null: measures).
+struct Layout {
+  char *mem;
   size_t at = 0;
-  auto take = [&](size_t bytes) {
+  template <typename T>
+  T *take(size_t bytes) {
     char *p = mem ? mem + at : nullptr;
     at += align256(bytes);
-    return p;
-  };
-  char *plan = take(sizeof(JoinPlan)), *part = take(2 * kJoinRangeBlocks * sizeof(int64_t));
-  char *counts = take(range_count_words(parts, 2) * sizeof(uint32_t)), *status = take(ntiles * sizeof(uint64_t));
-  char *moved = take(std::max<size_t>(8 * static_cast<size_t>(nb), 4 * static_cast<size_t>(np)));
-  char *pos = take(2 * static_cast<size_t>(np)), *slice = take(static_cast<size_t>(ntiles) * kSliceTile);
-  char *goff = take(static_cast<size_t>(ntiles) * kRangeDigits * 4), *live = take(static_cast<size_t>(ntiles) * 4);
-  if (mem) {
-    *lo = reinterpret_cast<int64_t *>(part);
-    d->plan = reinterpret_cast<JoinPlan *>(plan);
-    d->counts = range_counts_at(counts, parts);
-    d->status = reinterpret_cast<uint64_t *>(status);
-    d->ntiles = ntiles;
-    d->pairs = reinterpret_cast<uint64_t *>(moved);
-    d->moved = reinterpret_cast<uint32_t *>(moved);
-    d->pos = reinterpret_cast<uint16_t *>(pos);
-    d->slice = reinterpret_cast<uint8_t *>(slice);
-    d->goff = reinterpret_cast<uint32_t *>(goff);
-    d->live = reinterpret_cast<int32_t *>(live);
+    return reinterpret_cast<T *>(p);
   }
-  return at;
+};
+
+// The way back of a probe of np rows whose items take `item` bytes.
+static void probe_layout(Layout &l, int64_t np, size_t item, bool found, Slices *s) {
+  s->ntiles = ceil_div(np, kSliceTile);
+  const size_t tiles = static_cast<size_t>(s->ntiles);
+  s->status = l.take<uint64_t>(tiles * 8);
+  if (item) s->items = l.take<void>(item * static_cast<size_t>(np));
+  s->found = found ? l.take<uint64_t>(static_cast<size_t>(ceil_div(np, kWave)) * 8) : nullptr;
+  s->pos = l.take<uint16_t>(2 * static_cast<size_t>(np));
+  s->slice = l.take<uint8_t>(tiles * kSliceTile);
+  s->goff = l.take<uint32_t>(tiles * kRangeDigits * 4);
+  s->live = l.take<int32_t>(tiles * 4);
 }
 
-size_t direct_join_bytes(int64_t nb, int64_t np) { return direct_layout(nullptr, nb, np, nullptr, nullptr); }
+// Scratch of a direct join beside its array, and its layout at `mem`.
+static size_t direct_layout(char *mem, int64_t nb, int64_t np, DirectJoin *d, int64_t **lo) {
+  const int parts = std::max(range_parts(nb, kSliceTile), range_parts(np, kSliceTile));
+  Layout l{mem};
+  d->plan = l.take<JoinPlan>(sizeof(JoinPlan));
+  *lo = l.take<int64_t>(2 * kJoinRangeBlocks * sizeof(int64_t));
+  void *counts = l.take<void>(range_count_words(parts, 2) * sizeof(uint32_t));
+  void *items = l.take<void>(std::max<size_t>(8 * static_cast<size_t>(nb), 4 * static_cast<size_t>(np)));
+  d->build = d->probe = Slices{};
+  probe_layout(l, np, 0, false, &d->probe);
+  if (mem) {
+    d->build.counts = d->probe.counts = range_counts_at(counts, parts);
+    d->build.items = d->probe.items = items;
+    d->build.moved = &d->plan->moved[0];
+    d->probe.moved = &d->plan->moved[1];
+    d->probe.pass = 1;
+    d->probe.ticket = &d->plan->ticket;
+  }
+  return l.at;
+}
 
-template <bool K64>
-static void launch_slices(const DirectJoin &d, const pyst_col *key, bool build, hipStream_t stream) {
+size_t direct_join_bytes(int64_t nb, int64_t np) {
+  DirectJoin d{};
+  int64_t *lo;
+  return direct_layout(nullptr, nb, np, &d, &lo);
+}
+
+template <typename P>
+static void launch_slices(const P &p, const Slices &d, const pyst_col *key, const int32_t *sel, const int64_t *d_nsel,
+                          hipStream_t stream) {
   const int parts = range_parts(key->n, kSliceTile);
-  k_slice_hist<K64><<<parts, kRangeThreads, 0, stream>>>(d, build ? 0 : 1, key->data, key->n);
-  if (build) k_slice_move<K64, true><<<parts, kRangeThreads, 0, stream>>>(d, key->data, key->n);
-  else k_slice_move<K64, false><<<parts, kRangeThreads, 0, stream>>>(d, key->data, key->n);
+  k_slice_hist<P><<<parts, kRangeThreads, 0, stream>>>(p, d, key->data, sel, d_nsel, key->n);
+  k_slice_move<P><<<parts, kRangeThreads, 0, stream>>>(p, d, key->data, sel, d_nsel, key->n);
 }
 
 // The build side's plan and, where it is direct, its array in `array` (room for
@@ -432,11 +595,12 @@ pyst_status direct_join_build(pyst_ctx *ctx, const pyst_col *build_key, int64_t 
       : k_join_range<false><<<rblocks, 256, 0, stream>>>(build_key->data, nb, lo, lo + kJoinRangeBlocks, ctx_err_word(ctx));
   PYST_LAUNCH_CHECK("k_join_range");
   k_join_plan<<<1, kRangeThreads, 0, stream>>>(d.plan, lo, lo + kJoinRangeBlocks, rblocks,
-                                              static_cast<uint64_t>(range_max), d.counts);
+                                              static_cast<uint64_t>(range_max), d.build.counts);
   PYST_LAUNCH_CHECK("k_join_plan");
   k_direct_clear<<<grid_for(ctx, range_max / 4, 256, 8), 256, 0, stream>>>(d);
   PYST_LAUNCH_CHECK("k_direct_clear");
-  k64 ? launch_slices<true>(d, build_key, true, stream) : launch_slices<false>(d, build_key, true, stream);
+  if (k64) launch_slices(DirectRows<true, true>{d.plan}, d.build, build_key, nullptr, nullptr, stream);
+  else launch_slices(DirectRows<false, true>{d.plan}, d.build, build_key, nullptr, nullptr, stream);
   PYST_LAUNCH_CHECK("k_slice_move");
   k_direct_store<<<static_cast<unsigned>(ceil_div(nb, 2048)), 256, 0, stream>>>(d);
   PYST_LAUNCH_CHECK("k_direct_store");
@@ -452,15 +616,104 @@ pyst_status direct_join_probe(pyst_ctx *ctx, int64_t nb, const pyst_col *probe_k
   const int64_t np = probe_key->n;
   direct_layout(static_cast<char *>(ws), nb, np, &d, &lo);
   d.array = array;
-  probe_key->dtype == PYST_I64 ? launch_slices<true>(d, probe_key, false, stream)
-                               : launch_slices<false>(d, probe_key, false, stream);
+  if (probe_key->dtype == PYST_I64) launch_slices(DirectRows<true, false>{d.plan}, d.probe, probe_key, nullptr, nullptr, stream);
+  else launch_slices(DirectRows<false, false>{d.plan}, d.probe, probe_key, nullptr, nullptr, stream);
   PYST_LAUNCH_CHECK("k_slice_move");
   k_direct_lookup<<<static_cast<unsigned>(ceil_div(np, 2048)), 256, 0, stream>>>(d);
   PYST_LAUNCH_CHECK("k_direct_lookup");
-  k_direct_emit<<<static_cast<unsigned>(d.ntiles), kRangeThreads, 0, stream>>>(d, np, out_row, out_build, out_cap, d_nout,
-                                                                              ctx_err_word(ctx));
-  PYST_LAUNCH_CHECK("k_direct_emit");
+  k_slice_emit<uint32_t, false, int32_t><<<static_cast<unsigned>(d.probe.ntiles), kRangeThreads, 0, stream>>>(
+      d.plan, d.probe, nullptr, nullptr, np, out_row, out_build, out_cap, d_nout, ctx_err_word(ctx));
+  PYST_LAUNCH_CHECK("k_slice_emit");
   return PYST_OK;
 }
+
+// ---------------------------------------------------------------- hash tables beyond the L2
+// Probes of a unique-key hash table far larger than the L2, by slices of 2 MiB of
+// its slots (or the table's 256th part), through the same moves and the same way
+// back.  From 16 MiB of slots (an XCD's L2 holds 4) and 2^21 probes: below, the
+// moves cost what the lines do (600k keys, 2.5M probes 179 -> 164 us; 400k 64-bit
+// keys, 8 MiB, stay as they were).  20M probes of a 1M-key table of 16-byte slots
+// 680 -> 465 us (counts 43, move 87, lookup 226, way back 109); 50M of 9M int32
+// keys with build 1625 -> 1339 us; a 20M x 60M join of sparse 64-bit keys 3993 ->
+// 3726 us.  Duplicate keys (any number of matches a row) and arenas without room
+// keep k_join_probe.
+constexpr int64_t kHashTableMin = int64_t{16} << 20;   // bytes
+constexpr int64_t kHashProbeMin = int64_t{1} << 21;    // rows
+constexpr int kHashSliceLg = 21;                       // bytes a slice
+
+bool sliced_probe_wanted(const TableDev &t, int unique, const pyst_col *key) {
+  return unique && key->n >= kHashProbeMin && t.cap_alloc * t.slot_bytes >= kHashTableMin;
+}
+
+struct HashProbe {
+  uint32_t *head;  // cleared: ticket, then the group counts
+  int64_t head_words;
+  int64_t *moved;
+  Slices s;
+};
+
+static size_t hash_probe_layout(char *mem, int64_t np, int slot_bytes, HashProbe *h) {
+  const int parts = range_parts(np, kSliceTile);
+  Layout l{mem};
+  const int64_t groups = ceil_div(parts, kRangeGroup) * kRangeDigits;
+  h->head_words = 64 + groups;
+  h->head = l.take<uint32_t>(static_cast<size_t>(h->head_words) * 4);
+  uint32_t *part = l.take<uint32_t>(static_cast<size_t>(parts) * kRangeDigits * 4);
+  h->moved = l.take<int64_t>(8);
+  h->s = Slices{};
+  probe_layout(l, np, slot_bytes == 16 ? 8 : 4, true, &h->s);
+  if (mem) {
+    h->s.counts.part = part;
+    h->s.counts.group = h->head + 64;
+    h->s.counts.ngroups = static_cast<int>(ceil_div(parts, kRangeGroup));
+    h->s.ticket = reinterpret_cast<unsigned long long *>(h->head);
+    h->s.moved = h->moved;
+  }
+  return l.at;
+}
+
+size_t sliced_probe_bytes(const TableDev &t, const pyst_col *key) {
+  HashProbe h{};
+  return hash_probe_layout(nullptr, key->n, t.slot_bytes, &h);
+}
+
+template <bool WIDE, bool K64, typename PayT>
+static pyst_status launch_sliced_probe(pyst_ctx *ctx, const TableDev &t, const pyst_col *key, const int32_t *sel,
+                                       const int64_t *d_nsel, const HashProbe &h, int32_t *out_row, PayT *out_pay,
+                                       int64_t out_cap, int64_t *d_nout, const JoinPlan *plan, hipStream_t stream) {
+  using P = HashRows<WIDE, K64>;
+  P p{plan, t.hdr, kHashSliceLg - (WIDE ? 4 : 3)};
+  while (((t.cap_alloc - 1) >> p.shift) >= kRangeDigits) ++p.shift;
+  launch_slices(p, h.s, key, sel, d_nsel, stream);
+  PYST_LAUNCH_CHECK("k_slice_move");
+  k_hash_lookup<WIDE, K64><<<static_cast<unsigned>(ceil_div(key->n, WIDE ? 1024 : 2048)), 256, 0, stream>>>(
+      p, h.s, static_cast<const uint64_t *>(t.slots));
+  PYST_LAUNCH_CHECK("k_hash_lookup");
+  k_slice_emit<typename P::Item, true, PayT><<<static_cast<unsigned>(h.s.ntiles), kRangeThreads, 0, stream>>>(
+      plan, h.s, sel, d_nsel, key->n, out_row, out_pay, out_cap, d_nout, ctx_err_word(ctx));
+  PYST_LAUNCH_CHECK("k_slice_emit");
+  return PYST_OK;
+}
+
+// launch_join_probe's results through slices, in `ws` of sliced_probe_bytes.
+template <typename PayT>
+pyst_status sliced_probe(pyst_ctx *ctx, const TableDev &t, const pyst_col *key, const int32_t *sel, const int64_t *d_nsel,
+                         void *ws, int32_t *out_row, PayT *out_pay, int64_t out_cap, int64_t *d_nout,
+                         const JoinPlan *plan, hipStream_t stream) {
+  HashProbe h{};
+  hash_probe_layout(static_cast<char *>(ws), key->n, t.slot_bytes, &h);
+  const pyst_status st = fill_u32(h.head, h.head_words, 0, stream);
+  if (st != PYST_OK) return st;
+  const bool k64 = key->dtype == PYST_I64;
+  if (t.slot_bytes == 16)
+    return k64 ? launch_sliced_probe<true, true>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, stream)
+               : launch_sliced_probe<true, false>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, stream);
+  return k64 ? launch_sliced_probe<false, true>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, stream)
+             : launch_sliced_probe<false, false>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, stream);
+}
+template pyst_status sliced_probe<int32_t>(pyst_ctx *, const TableDev &, const pyst_col *, const int32_t *, const int64_t *,
+                                           void *, int32_t *, int32_t *, int64_t, int64_t *, const JoinPlan *, hipStream_t);
+template pyst_status sliced_probe<int64_t>(pyst_ctx *, const TableDev &, const pyst_col *, const int32_t *, const int64_t *,
+                                           void *, int32_t *, int64_t *, int64_t, int64_t *, const JoinPlan *, hipStream_t);
 
 }  // namespace pyst

@@ -1422,10 +1422,23 @@ pyst_status launch_join_build(pyst_ctx *ctx, const TableDev &t, const pyst_col *
   return PYST_OK;
 }
 
+// Defined with the sliced joins.
+bool sliced_probe_wanted(const TableDev &t, int unique, const pyst_col *key);
+size_t sliced_probe_bytes(const TableDev &t, const pyst_col *key);
+template <typename PayT>
+pyst_status sliced_probe(pyst_ctx *ctx, const TableDev &t, const pyst_col *key, const int32_t *sel, const int64_t *d_nsel,
+                         void *ws, int32_t *out_row, PayT *out_pay, int64_t out_cap, int64_t *d_nout,
+                         const JoinPlan *plan, hipStream_t stream);
+
 template <typename PayT>
 pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, const pyst_col *key, const int32_t *sel,
                               const int64_t *d_nsel, int32_t *out_row, PayT *out_pay, int64_t out_cap,
                               int64_t *d_nout, hipStream_t stream, const JoinPlan *plan = nullptr) {
+  if (sliced_probe_wanted(t, unique, key)) {  // a table beyond the L2, many probes: by slices, where there is room
+    Scratch ws(ctx, stream);
+    if (ws.try_alloc(sliced_probe_bytes(t, key)))
+      return sliced_probe(ctx, t, key, sel, d_nsel, ws.p, out_row, out_pay, out_cap, d_nout, plan, stream);
+  }
   // rows a lane: four of a narrow table's 8-byte slots, two of a wide one's 16 bytes (1M build and 15M
   // probe rows, narrow: 343 us with four, 370 with two, 476 with one; lookup of 20M 64-bit ids,
   // wide: 786, 680, 819)
@@ -1770,7 +1783,7 @@ pyst_status pyst_table_info(const pyst_table *table, int64_t *d_out, hipStream_t
 
 void pyst_table_destroy(pyst_table *table, hipStream_t stream) {
   if (!table) return;
-  (void)hipStreamSynchronize(stream);
+  if (hipStreamSynchronize(stream) == hipSuccess) ctx_stream_idle(table->ctx, stream);
   if (table->stream && table->stream != stream) (void)hipStreamSynchronize(table->stream);
   ctx_free_eager(table->ctx, table->mem, stream);  // the caller's stream may go away after this
   delete table;
