@@ -43,6 +43,8 @@ __device__ __forceinline__ uint64_t agg_hash(int64_t key) { return fmix64(static
 //             kmin) >> shift instead of by hash bits, so that a bucket's LDS
 //             array is indexed directly (no probing, no compare-and-swap) and
 //             the groups come out in key order (no sort).
+//   kGbOnce   the same for int32 keys and values that span at most 1024 buckets of
+//             16384 values: one move, of 8-byte pairs, does (see k_once_move).
 //   kGbFew    the sample finds few different keys, over any range: a table in HBM
 //             behind an LDS table per block (k_gb_insert).  The sample promises
 //             nothing: a table that runs full sends the rows on to kGbHash.
@@ -57,6 +59,8 @@ __device__ __forceinline__ uint64_t agg_hash(int64_t key) { return fmix64(static
 constexpr int kDirectSlotsLg = 13;
 constexpr int kDirectSlots = 1 << kDirectSlotsLg;  // LDS sums of one direct-addressed table
 constexpr int kSamples = 16384;
+constexpr int kOnceBuckets = 1024;
+constexpr int kOnceShift = 14, kOnceSlots = 1 << kOnceShift;  // LDS sums of one bucket: 128 KiB and 16 KiB of flags
 constexpr int kFewKeys = 1500;                    // different keys of the sample, at most
 constexpr int64_t kFewSlots = int64_t{1} << 16;   // slots of the table in HBM
 
@@ -789,6 +793,9 @@ size_t narrow_groupby_bytes(int64_t cap) {
   return (counts * sizeof(int32_t) + 255) / 256 * 256 + static_cast<size_t>(cap) * 16 + 256;
 }
 
+static pyst_status launch_once(pyst_ctx *ctx, const NarrowArgs &a, void *ws, uint64_t *pairs, uint64_t *status,
+                               int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, hipStream_t stream);
+
 // GROUP BY key SUM(val) of the rows [0, *count) (of the selection sel) of int32
 // columns through narrow pairs, in scratch `ws` of narrow_groupby_bytes(cap).
 // *d_ngroups must be zero on entry.  Fewer than 2^31 rows.
@@ -805,6 +812,10 @@ pyst_status narrow_groupby(pyst_ctx *ctx, const int32_t *kcol, const int32_t *vc
   uint64_t *tmp = reinterpret_cast<uint64_t *>(static_cast<char *>(ws) + (cbytes + 255) / 256 * 256);
   uint64_t *pairs = tmp + cap;
   NarrowArgs a{kcol, vcol, sel, count, cap, plan};
+  if (plan) {
+    const pyst_status st = launch_once(ctx, a, ws, tmp, status, out_keys, out_sums, out_cap, d_ngroups, stream);
+    if (st != PYST_OK) return st;
+  }
   k_narrow_hist<<<kNB1, kAggBlock, 0, stream>>>(a, counts);
   PYST_LAUNCH_CHECK("k_narrow_hist");
   k_narrow_counts<<<static_cast<unsigned>(ceil_div(n1 + n2 + 1, 256)), 256, 0, stream>>>(counts, c1, c2, plan);
@@ -912,17 +923,17 @@ __global__ __launch_bounds__(256) void k_key_range(const void *key, int key64, c
 // wait for one block each; such keys take hash buckets.
 __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64_t *lo_in, const int64_t *hi_in,
                                                       int nblocks, const int64_t *samples, const int64_t *d_nsel,
-                                                      int64_t n, int64_t small_max, int allow_range, int allow_few,
-                                                      int otherwise, uint64_t *status, int64_t *d_ngroups) {
+                                                      int64_t n, int64_t small_max, int allow_range, int allow_once,
+                                                      int allow_few, int otherwise, uint64_t *status, int64_t *d_ngroups) {
   __shared__ int32_t s_c[kAggBuckets];
   __shared__ int64_t s_lo[kAggBlock / kWave], s_hi[kAggBlock / kWave];
-  __shared__ int32_t s_crowded, s_distinct;
+  __shared__ int32_t s_crowded, s_crowded_once, s_distinct;
   const int tid = static_cast<int>(threadIdx.x);
   for (int i = tid; i < kAggBuckets; i += kAggBlock) {
     s_c[i] = 0;
     status[i] = 0;
   }
-  if (tid == 0) s_crowded = s_distinct = 0;
+  if (tid == 0) s_crowded = s_crowded_once = s_distinct = 0;
   int64_t lo = INT64_MAX, hi = INT64_MIN;
   for (int i = tid; i < nblocks; i += kAggBlock) {
     lo = lo_in[i] < lo ? lo_in[i] : lo;
@@ -959,8 +970,22 @@ __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64
       const int c = s_c[b];
       if (c > kSamples / 256 || wave_sum(c) > kSamples / 12) s_crowded = 1;  // a wave holds one part's 64 buckets
     }
+    // kGbOnce: its 1024 buckets are whole groups of these; over 1/128 in one waits for a block
+    int once_shift = shift;
+    while (((range - 1) >> once_shift) >= kOnceBuckets) ++once_shift;
+    if (allow_once && once_shift <= kOnceShift) {  // block-uniform
+      const int per = 1 << (once_shift - shift);
+      int32_t c = 0;
+      for (int j = 0; j < per && tid * per + j < kAggBuckets; ++j) c += s_c[tid * per + j];
+      if (c > kSamples / 128) s_crowded_once = 1;
+    }
     __syncthreads();
-    if (s_crowded) mode = otherwise;
+    if (s_crowded) {
+      mode = otherwise;
+    } else if (allow_once && once_shift <= kOnceShift && !s_crowded_once) {
+      mode = kGbOnce;
+      shift = once_shift;
+    }
   }
   if (mode == otherwise && allow_few) {  // block-uniform: different keys of the sample, by their hash bits
     constexpr int kBits = kAggBuckets * 32;
@@ -1215,9 +1240,302 @@ pyst_status launch_direct_groups(pyst_ctx *ctx, GbPlan *plan, uint64_t *status, 
   return PYST_OK;
 }
 
+// ---------------------------------------------------------------- one move (kGbOnce)
+// int32 keys and values over at most 2^24 values: the pairs are moved once, into
+// up to 1024 buckets of the key range, and a bucket's sums fill the LDS of a CU.
+// Bound by memory: the rows read and the pairs written (16 bytes a row), the
+// pairs read and the groups written.  A move to so many places leaves lines
+// half written: 32 blocks of an XCD with 1024 runs each would hold its whole L2
+// in such lines, so the blocks of an XCD fill the same places (a cursor per XCD
+// and bucket, moved by atomics) and a line is whole before it leaves.  Tiles of
+// 16384 pairs (128 KiB of LDS, one block per CU) make runs of 16 pairs.
+// 60M pairs over 15M keys: count 34, move 258, sums 172 us, where two moves took
+// 40, 235 + 252 and 193; a cursor per block 304 and 198; tiles of 8192 pairs, two
+// blocks per CU, 276 and 194.  In all 890 -> 662 us; 20M over 9000 keys 379 ->
+// 262, 1.2M over 300K 136 -> 110, 30M over 16M 542 -> 432.
+constexpr int kOnceItems = 16, kOnceTile = kAggBlock * kOnceItems;
+constexpr int kOnceParts = 256;  // blocks: contiguous ranges of rows
+constexpr int kOnceShare = 32;   // neighbouring ranges (one XCD's) that fill places together
+
+struct OnceWork {
+  int32_t *counts;   // [kOnceParts][kOnceBuckets]; then the rows before each range, then cursors
+  int32_t *totals;   // [kOnceBuckets]
+  uint64_t *pairs;   // (key - kmin) << 32 | value
+};
+
+__global__ __launch_bounds__(kAggBlock) void k_once_hist(NarrowArgs a, OnceWork o) {
+  __shared__ int32_t s_c[kOnceBuckets];
+  if (a.plan->mode != kGbOnce) return;
+  const int tid = static_cast<int>(threadIdx.x), shift = a.plan->shift;
+  const int32_t kmin = static_cast<int32_t>(a.plan->kmin);
+  if (tid < kOnceBuckets) s_c[tid] = 0;
+  __syncthreads();
+  int64_t lo, hi;
+  const int blk = static_cast<int>(xcd_block(blockIdx.x, kOnceParts));
+  narrow_range(a, blk, kOnceParts, &lo, &hi);
+  constexpr int U = 8;
+  for (int64_t i0 = lo + tid; i0 < hi; i0 += int64_t{kAggBlock} * U) {
+    int32_t k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) k[u] = a.kcol[row_of(a.sel, i0 + u * kAggBlock < hi ? i0 + u * kAggBlock : i0)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * kAggBlock < hi) atomicAdd(&s_c[(static_cast<uint32_t>(k[u]) - static_cast<uint32_t>(kmin)) >> shift], 1);
+  }
+  __syncthreads();
+  if (tid < kOnceBuckets) o.counts[blk * kOnceBuckets + tid] = s_c[tid];
+}
+
+// Per bucket the exclusive prefix over the ranges, in place, and the total; 64
+// buckets a block, 16 ranges a wave.
+__global__ __launch_bounds__(kAggBlock) void k_once_counts(const GbPlan *plan, OnceWork o) {
+  constexpr int NW = kAggBlock / kWave, PER = kOnceParts / NW;
+  __shared__ int32_t s_w[NW][kWave];
+  if (plan->mode != kGbOnce) return;
+  const int w = threadIdx.x / kWave, lane = lane_id(), b = static_cast<int>(blockIdx.x) * kWave + lane;
+  int32_t c[PER], sum = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) c[j] = o.counts[(w * PER + j) * kOnceBuckets + b];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) sum += c[j];
+  s_w[w][lane] = sum;
+  __syncthreads();
+  int32_t run = 0;
+  for (int k = 0; k < w; ++k) run += s_w[k][lane];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    o.counts[(w * PER + j) * kOnceBuckets + b] = run;
+    run += c[j];
+  }
+  if (w == NW - 1) o.totals[b] = run;
+}
+
+// s[b]: the exclusive prefix of the bucket totals (all threads; synchronizes).
+__device__ __forceinline__ void once_offsets(const int32_t *totals, int32_t *s, int32_t *s_w) {
+  static_assert(kOnceBuckets == kAggBlock, "a thread per bucket");
+  const int tid = static_cast<int>(threadIdx.x), w = tid / kWave;
+  const int32_t c = totals[tid], incl = wave_inclusive_scan(c);
+  if (lane_id() == kWave - 1) s_w[w] = incl;
+  __syncthreads();
+  int32_t before = 0;
+  for (int k = 0; k < w; ++k) before += s_w[k];
+  s[tid] = before + incl - c;
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kAggBlock) void k_once_move(NarrowArgs a, OnceWork o) {
+  __shared__ uint64_t s_p[kOnceTile];
+  __shared__ int32_t s_cnt[kOnceBuckets], s_off[kOnceBuckets], s_to[kOnceBuckets];
+  __shared__ int32_t s_w[kAggBlock / kWave];
+  if (a.plan->mode != kGbOnce) return;
+  const int tid = static_cast<int>(threadIdx.x), w = tid / kWave, shift = a.plan->shift;
+  const uint32_t kmin = static_cast<uint32_t>(static_cast<int32_t>(a.plan->kmin));
+  int64_t lo, hi;
+  const int blk = static_cast<int>(xcd_block(blockIdx.x, kOnceParts));
+  narrow_range(a, blk, kOnceParts, &lo, &hi);
+  once_offsets(o.totals, s_to, s_w);
+  // thread b: bucket b's start, and the cursor of the places there that these blocks share
+  const int32_t start = s_to[tid];
+  int32_t *const cursor = o.counts + blk / kOnceShare * kOnceShare * kOnceBuckets + tid;
+  uint32_t key[kOnceItems];
+  int32_t val[kOnceItems];
+  auto load_tile = [&](int64_t t0) {
+    const uint32_t n = static_cast<uint32_t>(hi - t0 < kOnceTile ? hi - t0 : kOnceTile);
+    if (a.sel) {
+      const int32_t *sel = a.sel + t0;
+#pragma unroll
+      for (int u = 0; u < kOnceItems; ++u) {
+        const uint32_t i = static_cast<uint32_t>(u * kAggBlock + tid);
+        const int32_t r = sel[i < n ? i : 0];
+        key[u] = static_cast<uint32_t>(a.kcol[r]);
+        val[u] = a.vcol[r];
+      }
+    } else {
+      const int32_t *kc = a.kcol + t0, *vc = a.vcol + t0;
+#pragma unroll
+      for (int u = 0; u < kOnceItems; ++u) {
+        const uint32_t i = static_cast<uint32_t>(u * kAggBlock + tid);
+        if (i < n) key[u] = static_cast<uint32_t>(kc[i]);
+        if (i < n) val[u] = vc[i];
+      }
+    }
+  };
+  if (lo < hi) load_tile(lo);
+  for (int64_t t0 = lo; t0 < hi; t0 += kOnceTile) {  // block-uniform
+    s_cnt[tid] = 0;
+    uint32_t rk[kOnceItems / 2];  // ranks, two a register
+    const int n = static_cast<int>(hi - t0 < kOnceTile ? hi - t0 : kOnceTile);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kOnceItems; ++u) {
+      uint32_t r = 0;
+      if (u * kAggBlock + tid < n) r = static_cast<uint32_t>(atomicAdd(&s_cnt[(key[u] - kmin) >> shift], 1));
+      rk[u / 2] = u % 2 ? rk[u / 2] | r << 16 : r;
+    }
+    __syncthreads();
+    const int32_t c = s_cnt[tid], incl = wave_inclusive_scan(c);
+    const int32_t to = c ? atomicAdd(cursor, c) : 0;  // waited for after the pairs are in place
+    if (lane_id() == kWave - 1) s_w[w] = incl;
+    __syncthreads();
+    int32_t at = incl - c;  // bucket b's place in the tile
+    for (int k = 0; k < w; ++k) at += s_w[k];
+    s_off[tid] = at;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kOnceItems; ++u)
+      if (u * kAggBlock + tid < n) {
+        const uint32_t off = key[u] - kmin, r = u % 2 ? rk[u / 2] >> 16 : rk[u / 2] & 0xffff;
+        s_p[s_off[off >> shift] + r] = static_cast<uint64_t>(off) << 32 | static_cast<uint32_t>(val[u]);
+      }
+    s_to[tid] = start + to - at;  // the pair at place p goes to s_to + p
+    __syncthreads();
+    if (t0 + kOnceTile < hi) load_tile(t0 + kOnceTile);  // arrives while this tile leaves
+    for (int p = tid; p < n; p += kAggBlock) {
+      const uint64_t x = s_p[p];
+      o.pairs[s_to[static_cast<uint32_t>(x >> 32) >> shift] + p] = x;
+    }
+    __syncthreads();
+  }
+}
+
+// As k_direct_groups, with the whole LDS of a CU for a bucket.
+__global__ __launch_bounds__(kAggBlock) void k_once_groups(GbPlan *plan, OnceWork o, uint64_t *status, int64_t *out_keys,
+                                                          int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups,
+                                                          uint32_t *err) {
+  constexpr int NW = kAggBlock / kWave, U = 8, PER = kOnceSlots / kAggBlock;
+  __shared__ uint64_t s_sum[kOnceSlots];
+  __shared__ uint8_t s_flag[kOnceSlots];
+  __shared__ int32_t s_cnt[PER * NW];
+  __shared__ int32_t s_w[NW], s_lo[kOnceBuckets];
+  __shared__ int64_t s_base;
+  __shared__ int32_t s_b;
+  static_assert(PER * NW == 4 * kWave, "one wave scans the counts, four a lane");
+  if (plan->mode != kGbOnce) return;
+  const int tid = static_cast<int>(threadIdx.x), w = tid / kWave, lane = lane_id(), shift = plan->shift;
+  const int64_t kmin = plan->kmin;
+  const int nbuckets = static_cast<int>((plan->range - 1) >> shift) + 1;
+  const uint32_t mask = (1u << shift) - 1;
+  const int used = static_cast<int>((mask + kAggBlock) / kAggBlock);
+  once_offsets(o.totals, s_lo, s_w);
+  for (int i = tid; i < kOnceSlots; i += kAggBlock) {
+    s_sum[i] = 0;
+    s_flag[i] = 0;
+  }
+  // A round is 8 pairs a thread; the next round, of this bucket or of the next
+  // one, is loaded before this one is added.
+  uint64_t x[U];
+  int64_t i0 = 0, hi = 0;
+  auto load_round = [&]() {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * kAggBlock < hi) x[u] = o.pairs[i0 + u * kAggBlock];
+  };
+  if (tid == 0) s_b = static_cast<int32_t>(atomicAdd(&plan->ticket, 1ull));
+  __syncthreads();
+  int b = s_b;
+  if (b < nbuckets) {
+    i0 = s_lo[b] + tid;
+    hi = b + 1 < kOnceBuckets ? s_lo[b + 1] : plan->count;
+    load_round();
+  }
+  while (b < nbuckets) {  // block-uniform
+    __syncthreads();      // the table is clear; s_b, s_base and s_cnt are read
+    if (tid == 0) s_b = static_cast<int32_t>(atomicAdd(&plan->ticket, 1ull));
+    for (; i0 - tid < hi;) {  // block-uniform
+      uint64_t y[U];
+      const int64_t j0 = i0;
+      const int64_t jhi = hi;
+#pragma unroll
+      for (int u = 0; u < U; ++u) y[u] = x[u];
+      i0 += int64_t{kAggBlock} * U;
+      load_round();
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (j0 + u * kAggBlock >= jhi) continue;
+        const uint32_t s = static_cast<uint32_t>(y[u] >> 32) & mask;
+        atomicAdd(reinterpret_cast<unsigned long long *>(&s_sum[s]),
+                  static_cast<unsigned long long>(static_cast<int64_t>(static_cast<int32_t>(y[u] & 0xffffffffu))));
+        s_flag[s] = 1;
+      }
+    }
+    __syncthreads();
+    const int nb = s_b;
+    if (nb < nbuckets) {
+      i0 = s_lo[nb] + tid;
+      hi = nb + 1 < kOnceBuckets ? s_lo[nb + 1] : plan->count;
+      load_round();
+    }
+    uint64_t m[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      m[j] = j < used ? __ballot(s_flag[j * kAggBlock + tid] != 0) : 0;
+      if (lane == 0) s_cnt[j * NW + w] = __popcll(m[j]);
+    }
+    __syncthreads();
+    if (w == 0) {
+      int32_t c[4], sum = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sum += c[j] = s_cnt[4 * lane + j];
+      const int32_t incl = wave_inclusive_scan(sum);
+      int32_t run = incl - sum;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        s_cnt[4 * lane + j] = run;
+        run += c[j];
+      }
+      const int64_t agg = __shfl(incl, kWave - 1);
+      const int64_t ex = lookback_exclusive(status, b, agg);
+      if (lane == 0) {
+        s_base = ex;
+        if (b == nbuckets - 1) {
+          *d_ngroups = ex + agg;
+          if (ex + agg > out_cap) latch(err, kErrCapacity);
+        }
+      }
+    }
+    __syncthreads();
+    const int64_t base = s_base;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int s = j * kAggBlock + tid;
+      if (j < used && ((m[j] >> lane) & 1ull)) {
+        const int64_t p = base + s_cnt[j * NW + w] + mbcnt(m[j]);
+        if (p < out_cap) {
+          out_keys[p] = kmin + ((int64_t{b} << shift) | s);
+          out_sums[p] = static_cast<int64_t>(s_sum[s]);
+        }
+        s_sum[s] = 0;
+        s_flag[s] = 0;
+      }
+    }
+    b = nb;
+  }
+}
+
+// Scratch in the narrow moves' memory: the counts where theirs are, the pairs in
+// one of their two buffers.
+static pyst_status launch_once(pyst_ctx *ctx, const NarrowArgs &a, void *ws, uint64_t *pairs, uint64_t *status,
+                               int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, hipStream_t stream) {
+  static_assert((kOnceParts + 1) * kOnceBuckets <= kNB1 * kAggBuckets, "the counts of the narrow moves take more");
+  OnceWork o;
+  o.counts = static_cast<int32_t *>(ws);
+  o.totals = o.counts + kOnceParts * kOnceBuckets;
+  o.pairs = pairs;
+  k_once_hist<<<kOnceParts, kAggBlock, 0, stream>>>(a, o);
+  PYST_LAUNCH_CHECK("k_once_hist");
+  k_once_counts<<<kOnceBuckets / kWave, kAggBlock, 0, stream>>>(a.plan, o);
+  PYST_LAUNCH_CHECK("k_once_counts");
+  k_once_move<<<kOnceParts, kAggBlock, 0, stream>>>(a, o);
+  PYST_LAUNCH_CHECK("k_once_move");
+  k_once_groups<<<std::max(1, ctx_num_cus(ctx)), kAggBlock, 0, stream>>>(a.plan, o, status, out_keys, out_sums, out_cap,
+                                                                        d_ngroups, ctx_err_word(ctx));
+  PYST_LAUNCH_CHECK("k_once_groups");
+  return PYST_OK;
+}
+
 // The group count of the hash modes is what remains to be sorted.
 __global__ void k_gb_sort_count(GbPlan *plan, const int64_t *d_ngroups) {
-  plan->sort_count = plan_mode(plan) == kGbSmall || plan_mode(plan) == kGbRange ? 0 : *d_ngroups;
+  plan->sort_count = plan->mode == kGbSmall || plan->mode == kGbRange || plan->mode == kGbOnce ? 0 : *d_ngroups;
 }
 
 // Small scratch of a planned group-by: the plan, the look-back words, the
@@ -1270,7 +1588,7 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
       k_key_range<<<rblocks, 256, 0, stream>>>(key->data, k64, sel, d_nsel, n, lo, hi, samples, fg, few_status,
                                                few_words, err);
       PYST_LAUNCH_CHECK("k_key_range");
-      k_gb_plan<<<1, kAggBlock, 0, stream>>>(plan, lo, hi, rblocks, samples, d_nsel, n, small_max, moves,
+      k_gb_plan<<<1, kAggBlock, 0, stream>>>(plan, lo, hi, rblocks, samples, d_nsel, n, small_max, moves, narrow,
                                              few.p != nullptr, hash_buckets ? kGbHash : kGbTable, status, d_ngroups);
       PYST_LAUNCH_CHECK("k_gb_plan");
       uint64_t *psum = moves ? ws.as<uint64_t>() : table.as<uint64_t>();

@@ -39,7 +39,7 @@ struct GroupDev {
 
 // How the rows of a group-by are grouped: chosen on the device from the keys'
 // range (see the planned group-by).  Kernels of the other modes return at once.
-enum : int32_t { kGbHash = 0, kGbSmall = 1, kGbRange = 2, kGbTable = 3, kGbFew = 4 };
+enum : int32_t { kGbHash = 0, kGbSmall = 1, kGbRange = 2, kGbTable = 3, kGbFew = 4, kGbOnce = 5 };
 struct GbPlan {
   int64_t kmin;
   uint64_t range;      // greatest - least key + 1; 0 without rows

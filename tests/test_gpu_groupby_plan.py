@@ -142,3 +142,29 @@ def test_sample_promises_too_few_keys(gpu, ctx, unbounded):
     n = (1 << 24) + 7 if unbounded else 4_000_000
     k = np.where(rng.random(n) < 0.95, rng.integers(0, 100, n) << 50, rng.integers(-2**62, 2**62, n))
     check(gpu, ctx, k, rng.integers(-2**62, 2**62, n), max_groups=0 if unbounded else n)
+
+
+@pytest.mark.parametrize("n", [1 << 20, (1 << 22) + 12_345])
+@pytest.mark.parametrize("span", [1 << 14, 1_000_001, (1 << 24) - 1, 1 << 24, (1 << 24) + 1])
+@pytest.mark.parametrize("picked", [None, 0, 1, 16_385, 900_001])
+def test_one_move_of_int32_pairs(gpu, ctx, n, span, picked):
+    # spans of 2^24 values are moved once, wider ones twice; sums that cancel
+    # stay groups; the last tiles of the blocks' ranges are short
+    rng = np.random.default_rng(span + n)
+    k = keys_over(rng, n, span, -(span // 2), np.int32)
+    v = rng.integers(-2**31, 2**31, n).astype(np.int32)
+    v[k % 3 == 0] = 0
+    sel = None if picked is None else np.sort(rng.choice(n, picked, replace=False)).astype(np.int32)
+    check(gpu, ctx, k, v, sel)
+
+
+@pytest.mark.parametrize("share", [0.004, 0.01, 0.012, 0.1])
+def test_crowded_buckets_of_one_move(gpu, ctx, share):
+    # a run of 4096 neighbouring keys with that share of the rows: the buckets of
+    # one move, or those of two, or neither take them
+    rng = np.random.default_rng(7)
+    n, span = 3_000_017, 1 << 22
+    k = keys_over(rng, n, span, 0, np.int32)
+    many = rng.random(n) < share
+    k[many] = rng.integers(1 << 20, (1 << 20) + 4096, int(many.sum()))
+    check(gpu, ctx, k, rng.integers(-2**31, 2**31, n).astype(np.int32))
