@@ -849,8 +849,10 @@ pyst_status pair_groupby(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const int6
 
 // ---------------------------------------------------------------- planned group-by of columns
 // Least and greatest key of the rows (per-block partial results) and a sample
-// of the keys at jittered even steps.  One read of the keys, coalesced 4- or
-// 8-byte loads with eight in flight a thread.  An EMPTY int64 key is latched.
+// of the keys at jittered even steps.  One read of the keys bounds it: 16-byte
+// loads, four in flight a thread, where there is no selection and the column is
+// so aligned (60M int32 keys 49 us, 4.9 TB/s); else 4- or 8-byte loads, eight in
+// flight (61 us).  An EMPTY int64 key is latched.
 constexpr int kRangeBlocks = 2048, kRangeItems = 8;
 __global__ __launch_bounds__(256) void k_key_range(const void *key, int key64, const int32_t *sel, const int64_t *d_nsel,
                                                    int64_t n, int64_t *lo_out, int64_t *hi_out, int64_t *samples,
@@ -875,7 +877,45 @@ __global__ __launch_bounds__(256) void k_key_range(const void *key, int key64, c
   }
   int64_t lo = INT64_MAX, hi = INT64_MIN;
   bool bad = false;
-  for (int64_t i0 = gtid; i0 < cnt; i0 += int64_t{gridDim.x} * 256 * kRangeItems) {
+  int64_t first = 0;  // rows before it are done
+  if (!sel && reinterpret_cast<uintptr_t>(key) % 16 == 0) {
+    // whole 16-byte loads, kRangeItems / 2 in flight a thread
+    constexpr int V = kRangeItems / 2;
+    const int per = key64 ? 2 : 4;
+    const int64_t nv = cnt / per, step = int64_t{gridDim.x} * 256;
+    const int4 *kv = static_cast<const int4 *>(key);
+    first = nv * per;
+    int32_t lo32 = INT32_MAX, hi32 = INT32_MIN;
+    for (int64_t v0 = gtid; v0 < nv; v0 += step * V) {
+      int4 x[V];
+#pragma unroll
+      for (int u = 0; u < V; ++u) x[u] = kv[v0 + u * step < nv ? v0 + u * step : v0];
+#pragma unroll
+      for (int u = 0; u < V; ++u) {
+        if (key64) {
+          const longlong2 y = __builtin_bit_cast(longlong2, x[u]);
+          const int64_t k[2] = {y.x, y.y};
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            if (k[j] == kEmpty64) {
+              bad = true;
+              continue;
+            }
+            lo = k[j] < lo ? k[j] : lo;
+            hi = k[j] > hi ? k[j] : hi;
+          }
+        } else {
+          lo32 = min(lo32, min(min(x[u].x, x[u].y), min(x[u].z, x[u].w)));
+          hi32 = max(hi32, max(max(x[u].x, x[u].y), max(x[u].z, x[u].w)));
+        }
+      }
+    }
+    if (!key64 && gtid < nv) {
+      lo = lo32;
+      hi = hi32;
+    }
+  }
+  for (int64_t i0 = first + gtid; i0 < cnt; i0 += int64_t{gridDim.x} * 256 * kRangeItems) {
     int64_t k[kRangeItems], row[kRangeItems];
 #pragma unroll
     for (int u = 0; u < kRangeItems; ++u) {

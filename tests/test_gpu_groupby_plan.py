@@ -168,3 +168,22 @@ def test_crowded_buckets_of_one_move(gpu, ctx, share):
     many = rng.random(n) < share
     k[many] = rng.integers(1 << 20, (1 << 20) + 4096, int(many.sum()))
     check(gpu, ctx, k, rng.integers(-2**31, 2**31, n).astype(np.int32))
+
+
+@pytest.mark.parametrize("kt", [np.int32, np.int64])
+@pytest.mark.parametrize("skip", [0, 1, 2, 3])
+@pytest.mark.parametrize("extra", [0, 1, 2, 3])
+def test_key_columns_off_16_bytes(gpu, ctx, kt, skip, extra):
+    # the range is read in 16-byte words where the column allows it; the least
+    # and greatest keys are the first and last rows
+    rng = np.random.default_rng(skip)
+    n = (1 << 20) + extra
+    k = keys_over(rng, n, 50_000, -7, kt)
+    v = rng.integers(-100, 100, n).astype(np.int32)
+    d = dev(np.concatenate([np.full(skip, 10**9, kt), k]))[skip:]
+    gk, gs, ng = gpu.groupby_sum(ctx, d, dev(v), sort_by_key=True)
+    ctx.check()
+    wk, ws = oracle.groupby_sum(k, v)
+    m = int(ng.item())
+    np.testing.assert_array_equal(gk[:m].cpu().numpy(), wk)
+    np.testing.assert_array_equal(gs[:m].cpu().numpy(), ws)
