@@ -48,20 +48,27 @@ __device__ __forceinline__ uint64_t agg_hash(int64_t key) { return fmix64(static
 //   kGbFew    the sample finds few different keys, over any range: a table in HBM
 //             behind an LDS table per block (k_gb_insert).  The sample promises
 //             nothing: a table that runs full sends the rows on to kGbHash.
+//             Every block adds its own table's groups to the one in HBM, so this
+//             wants 2048 rows a group (2M rows, int64 keys, against hash buckets:
+//             300 groups 144 and 193 us, 900 189 and 200, 1400 224 and 199; 20M
+//             into 1400 419 and 770), and room in the blocks' 4096 LDS slots
+//             (20M into 2800: 2770 us, 748 hashed).
 //   kGbHash   otherwise: hash buckets, each summed in an LDS hash table.
 //   kGbTable  the same where hash buckets have no memory or too many groups: the
 //             table in HBM (k_gb_insert).
 // Measured at 60M rows, start to end, ordered by key: 2407 int32 keys with int64
-// values 1953 -> 362 us (kGbSmall: 138 us for the sums, 5.2 TB/s; hash buckets
+// values 1953 -> 218 us (kGbSmall: 135 us for the sums, 5.3 TB/s; hash buckets
 // left 2407 busy blocks of uneven size), 15M int32 keys with int32 values 2232
-// -> 1632 us (kGbRange: 193 us for the bucket sums against 376 with hash tables,
-// and nothing left to sort).  The range costs 60 - 68 us there.
+// -> 590 us (kGbOnce; 840 with the two moves of kGbRange, whose bucket sums take
+// 193 us against 376 with hash tables; nothing is left to sort).  The range costs
+// 49 - 66 us there.
 constexpr int kDirectSlotsLg = 13;
 constexpr int kDirectSlots = 1 << kDirectSlotsLg;  // LDS sums of one direct-addressed table
 constexpr int kSamples = 16384;
 constexpr int kOnceBuckets = 1024;
 constexpr int kOnceShift = 14, kOnceSlots = 1 << kOnceShift;  // LDS sums of one bucket: 128 KiB and 16 KiB of flags
 constexpr int kFewKeys = 1500;                    // different keys of the sample, at most
+constexpr int64_t kFewRows = 2048;                // rows per different key, at least
 constexpr int64_t kFewSlots = int64_t{1} << 16;   // slots of the table in HBM
 
 __device__ __forceinline__ bool plan_moves(const GbPlan *p) {
@@ -1040,7 +1047,8 @@ __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64
     news = wave_sum(news);
     if (lane_id() == 0) atomicAdd(&s_distinct, news);
     __syncthreads();
-    if (s_distinct <= kFewKeys) mode = kGbFew;
+    const int64_t cnt = count_of(d_nsel, n);
+    if (s_distinct <= kFewKeys && s_distinct <= cnt / kFewRows) mode = kGbFew;
   }
   if (tid == 0) {
     int64_t cnt = count_of(d_nsel, n);

@@ -1096,8 +1096,13 @@ __global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key6
     if (few && full) plan->few_failed = 1;
   }
   __syncthreads();
-  for (int i = tid; i < nslots; i += 1024)
-    if (s_key[i] != kE && !group_add(g.slots, mask, static_cast<int64_t>(s_key[i]), s_sum[i], probes)) full = true;
+  // each block starts elsewhere, or all would meet in the same words (2M rows into
+  // 1400 groups, 512 blocks: 176 -> 135 us)
+  const int first = static_cast<int>((blockIdx.x * 0x9e3779b1u) >> 16);
+  for (int i = tid; i < nslots; i += 1024) {
+    const int s = (i + first) & (nslots - 1);
+    if (s_key[s] != kE && !group_add(g.slots, mask, static_cast<int64_t>(s_key[s]), s_sum[s], probes)) full = true;
+  }
   if (full) {
     if (few) plan->few_failed = 1;  // more groups than the sample promised
     else latch(err, kErrTableFull);
