@@ -42,14 +42,14 @@ GROUP_OUT_BYTES = 16   # key int64 + sum int64
 KERNEL_SOURCES = {  # the files that define each profiled kernel (name patterns as rocprofv3 prints them)
     "k_fast_fact": ["fast.hip", "pyst_internal.h", "table.h", "query.h"],
     "k_fast_fact<2, 8, 2": ["fast.hip", "pyst_internal.h", "table.h", "query.h"],
-    "k_join_probe": ["ops.hip", "pyst_internal.h", "table.h"],
-    "k_join_build": ["ops.hip", "pyst_internal.h", "table.h"],
+    "k_direct_store": ["join.hip", "ranges.h", "pyst_internal.h", "table.h"],
+    "k_direct_lookup": ["join.hip", "ranges.h", "pyst_internal.h", "table.h"],
     "k_gather_rows<4": ["ops.hip", "pyst_internal.h"],
     "k_gather<": ["ops.hip", "pyst_internal.h"],
-    "k_narrow_hist": ["agg.hip", "pyst_internal.h"],
-    "k_narrow_move<true>": ["agg.hip", "pyst_internal.h"],
-    "k_narrow_move<false>": ["agg.hip", "pyst_internal.h"],
-    "k_narrow_groups": ["agg.hip", "pyst_internal.h"],
+    "k_key_range": ["agg.hip", "pyst_internal.h"],
+    "k_once_hist": ["agg.hip", "pyst_internal.h"],
+    "k_once_move": ["agg.hip", "pyst_internal.h"],
+    "k_once_groups": ["agg.hip", "pyst_internal.h"],
     "k_move_hist_both": ["agg.hip", "pyst_internal.h"],
     "k_move_scatter": ["agg.hip", "pyst_internal.h"],
     "k_bucket_groups": ["agg.hip", "pyst_internal.h"],
@@ -59,7 +59,7 @@ KERNEL_SOURCES = {  # the files that define each profiled kernel (name patterns 
 }
 Q18_WORKLOAD = "q18_n60000000_g15000000"
 BATCH_WORKLOAD = "batch_512"
-Q18_KERNELS = ("k_narrow_hist", "k_narrow_move<true>", "k_narrow_move<false>", "k_narrow_groups")
+Q18_KERNELS = ("k_key_range", "k_once_hist", "k_once_move", "k_once_groups")
 PAIR_KERNELS = ("k_move_hist_both", "k_move_scatter", "k_bucket_groups")
 CHAIN_WORKLOAD = "chain_a3000000_b300000_f120000000"  # fact-pass counters averaged over s = 0 and 1
 JOIN_WORKLOAD = "join_b60000000_p160000000_k4"  # counters of the k = 4 materializing join
@@ -589,7 +589,8 @@ def bench_join(ctx, pyst, gen, log, nb=60_000_000, npr=160_000_000, ks=(1, 4, 8)
     if "m2m" in legs:
         out["many_to_many"] = bench_many_to_many(ctx, pyst, gen, log, nb, npr)
     # HBM bytes per launch from committed counters of the k = 4 run (null once the kernels changed)
-    out["k4_counter_traffic"] = {"k_join_probe": counter_traffic("k_join_probe", JOIN_WORKLOAD),
+    out["k4_counter_traffic"] = {"k_direct_store": counter_traffic("k_direct_store", JOIN_WORKLOAD),
+                                 "k_direct_lookup": counter_traffic("k_direct_lookup", JOIN_WORKLOAD),
                                  "k_gather_rows": counter_traffic("k_gather_rows<4", JOIN_WORKLOAD),
                                  "k_gather": counter_traffic("k_gather<", JOIN_WORKLOAD)}
     return out
