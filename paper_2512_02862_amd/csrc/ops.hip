@@ -1807,8 +1807,8 @@ pyst_status pyst_groupby_sum(pyst_ctx *ctx, const pyst_col *key, const pyst_col 
   if (out_cap > 0 && (!out_keys || !out_sums)) return set_error(PYST_ERR_ARG, "pyst_groupby_sum: NULL outputs");
   if (!ctx_groupby_hash_only(ctx) && key->n >= kRadixRowsMin) {
     // By key range where that is small enough for LDS arrays, else radix-partitioned:
-    // the rows are moved twice into 4096 buckets and each bucket is summed in LDS,
-    // instead of two random L2 atomics per row.
+    // the rows are moved into buckets (once into 1024 or twice into 4096) and each
+    // bucket is summed in LDS, instead of two random L2 atomics per row.
     const bool radix = bound <= kRadixGroupsMax;
     TimedRegion timed(ctx, radix ? "groupby_radix" : "groupby_hash", stream);
     return planned_groupby(ctx, key, val, sel, d_nsel, max_groups, bound, max_load, radix, out_keys, out_sums, out_cap,
