@@ -647,9 +647,8 @@ bool sliced_probe_wanted(const TableDev &t, int unique, const pyst_col *key) {
 }
 
 struct HashProbe {
-  uint32_t *head;  // cleared: ticket, then the group counts
+  uint32_t *head;  // cleared: ticket, moved rows (nothing writes them where no row is selected), then the group counts
   int64_t head_words;
-  int64_t *moved;
   Slices s;
 };
 
@@ -660,7 +659,6 @@ static size_t hash_probe_layout(char *mem, int64_t np, int slot_bytes, HashProbe
   h->head_words = 64 + groups;
   h->head = l.take<uint32_t>(static_cast<size_t>(h->head_words) * 4);
   uint32_t *part = l.take<uint32_t>(static_cast<size_t>(parts) * kRangeDigits * 4);
-  h->moved = l.take<int64_t>(8);
   h->s = Slices{};
   probe_layout(l, np, slot_bytes == 16 ? 8 : 4, true, &h->s);
   if (mem) {
@@ -668,7 +666,7 @@ static size_t hash_probe_layout(char *mem, int64_t np, int slot_bytes, HashProbe
     h->s.counts.group = h->head + 64;
     h->s.counts.ngroups = static_cast<int>(ceil_div(parts, kRangeGroup));
     h->s.ticket = reinterpret_cast<unsigned long long *>(h->head);
-    h->s.moved = h->moved;
+    h->s.moved = reinterpret_cast<int64_t *>(h->head + 2);
   }
   return l.at;
 }

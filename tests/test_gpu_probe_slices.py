@@ -130,3 +130,27 @@ def test_duplicate_keys_and_short_arena_keep_the_other_path(gpu):
     assert int(ng.item()) == len(wr) + extra
     t.destroy()
     c.close()
+
+
+def fill_arena(gpu, c):
+    """Writes the word 2^31 (an EMPTY slot) all over a context's arena, and gives it back."""
+    t = gpu.join_build(c, dev(np.arange(3, dtype=np.int32)), max_load=3 / (c.budget // 2 // 8 - 2))
+    t.destroy()
+    c.check()
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("build_sel", [False, True])
+def test_empty_selection_first_in_a_used_arena(gpu, wide, build_sel):
+    # no row moves, so nothing but the clearing of the scratch says so to the later kernels
+    rng = np.random.default_rng(29)
+    kt = np.int64 if wide else np.int32
+    bk, pk = sides(rng, 1_100_000, ROWS + 77, kt, kt, False)
+    pay = rng.integers(-2**31, 2**31, len(bk)).astype(np.int32)
+    bsel = np.arange(1, len(bk), dtype=np.int32) if build_sel else None
+    c = gpu.Ctx(0, 512 << 20)
+    fill_arena(gpu, c)
+    check(gpu, c, bk, pay, pk, bsel, np.zeros(0, np.int32))
+    check(gpu, c, bk, pay, pk, bsel, np.array([len(pk) - 1], np.int32))
+    check(gpu, c, bk, pay, pk, bsel, np.zeros(0, np.int32))
+    c.close()
