@@ -1027,8 +1027,9 @@ __global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key6
   constexpr unsigned long long kE = static_cast<unsigned long long>(kEmpty64);
   __shared__ unsigned long long s_key[kPreSlots], s_sum[kPreSlots];
   __shared__ int32_t s_claimed;
-  __shared__ bool s_stop;
-  if (plan && plan_mode(plan) != mode) return;
+  __shared__ bool s_stop, s_late;
+  // (of the same launch, other blocks may set few_failed: one thread reads it for the block)
+  if (plan && (mode == kGbFew ? plan->mode : plan_mode(plan)) != mode) return;
   int64_t cnt = count_of(d_nsel, n);
   if (cnt > n) cnt = n;
   const int tid = static_cast<int>(threadIdx.x);
@@ -1044,8 +1045,12 @@ __global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key6
     s_key[i] = kE;
     s_sum[i] = 0;
   }
-  if (tid == 0) s_claimed = 0;
+  if (tid == 0) {
+    s_claimed = 0;
+    s_late = few && few_full(plan);
+  }
   __syncthreads();
+  if (s_late) return;  // block-uniform: the rows will be grouped another way
   bool direct = false, full = false;
   for (int64_t t0 = lo; t0 < hi; t0 += 1024 * U) {  // block-uniform
     int64_t row[U], k[U], v[U];
@@ -1089,7 +1094,7 @@ __global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key6
       direct = s_claimed > (t0 + 1024 * U - lo) / 2;
       const bool stop = s_stop;
       __syncthreads();
-      if (stop) break;  // block-uniform: the rows will be grouped another way
+      if (stop) return;  // block-uniform
     } else if (few && (full || few_full(plan))) {
       break;  // no barrier follows within the loop
     }

@@ -187,3 +187,32 @@ def test_key_columns_off_16_bytes(gpu, ctx, kt, skip, extra):
     m = int(ng.item())
     np.testing.assert_array_equal(gk[:m].cpu().numpy(), wk)
     np.testing.assert_array_equal(gs[:m].cpu().numpy(), ws)
+
+
+def test_few_table_full_while_blocks_still_start(gpu):
+    # two streams share the chip, so blocks start after others have found the table full
+    import torch
+    rng = np.random.default_rng(41)
+    n = 4_000_000
+    k = np.where(rng.random(n) < 0.95, rng.integers(0, 100, n) << 50, rng.integers(-2**62, 2**62, n))
+    v = rng.integers(-2**62, 2**62, n)
+    wk, ws = oracle.groupby_sum(k, v)
+    dk, dv = dev(k), dev(v)
+    ctxs = [gpu.Ctx(0, 1 << 30) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(3):
+        for c, s in zip(ctxs, streams):
+            with torch.cuda.stream(s):
+                got.append(gpu.groupby_sum(c, dk, dv, max_groups=n, sort_by_key=True, stream=s))
+    for c, s in zip(ctxs, streams):
+        c.check(s)
+    torch.cuda.synchronize()
+    for gk, gs, ng in got:
+        m = int(ng.item())
+        assert m == len(wk)
+        np.testing.assert_array_equal(gk[:m].cpu().numpy(), wk)
+        np.testing.assert_array_equal(gs[:m].cpu().numpy(), ws)
+    for c in ctxs:
+        c.close()
