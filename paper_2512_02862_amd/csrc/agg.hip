@@ -1607,13 +1607,17 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
   Scratch ps(ctx, stream);
   {
     const int64_t cap_alloc = hash_buckets ? 0 : table_capacity_host(bound, max_load);
-    Scratch table(ctx, stream), ws(ctx, stream), ws2(ctx, stream), few(ctx, stream);
-    if (!hash_buckets) table.alloc(group_bytes(cap_alloc));
+    Scratch table(ctx, stream), words(ctx, stream), ws(ctx, stream), ws2(ctx, stream), few(ctx, stream);
+    // what the call cannot do without comes first: what it can must not take its place
+    if (!hash_buckets) {
+      table.alloc(group_bytes(cap_alloc));
+      words.alloc(group_compact_words(cap_alloc) * sizeof(uint64_t));
+    }
     const size_t wsb = narrow ? narrow_groupby_bytes(n) : static_cast<size_t>(n) * 16;
     hash_buckets ? ws.alloc(wsb) : ws.try_alloc(wsb);
     if (!narrow && ws.p) hash_buckets ? ws2.alloc(wide_groupby_bytes(n)) : ws2.try_alloc(wide_groupby_bytes(n));
     const bool moves = ws.p && (narrow || ws2.p);
-    if (hash_buckets ? !moves : !table.p) return set_error(PYST_ERR_NOMEM, "pyst_groupby_sum: arena exhausted");
+    if (hash_buckets ? !moves : !table.p || !words.p) return set_error(PYST_ERR_NOMEM, "pyst_groupby_sum: arena exhausted");
     ps.try_alloc(kPlanBytes);
     const int64_t *count = d_nsel;
     uint64_t *status = nullptr;
@@ -1681,7 +1685,7 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
     if (!hash_buckets) {
       const GroupDev g = group_view(table.p, cap_alloc);
       st = table_groupby(ctx, g, key, val, sel, d_nsel, max_groups, max_load, out_keys, out_sums, out_cap, d_ngroups,
-                         plan, kGbTable, nullptr, stream);
+                         plan, kGbTable, words.as<uint64_t>(), stream);
       if (st != PYST_OK) return st;
     }
   }

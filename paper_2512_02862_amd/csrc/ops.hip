@@ -1231,14 +1231,13 @@ int64_t group_compact_words(int64_t cap_alloc) {
 pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val,
                           const int32_t *sel, const int64_t *d_nsel, int64_t max_groups, double max_load,
                           int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, GbPlan *plan,
-                          int mode, uint64_t *few_status, hipStream_t stream) {
+                          int mode, uint64_t *status, hipStream_t stream) {
   Scratch sc(ctx, stream);
-  uint64_t *status = few_status;
   pyst_status st = PYST_OK;
-  if (!status) {
+  if (mode != kGbFew) {
     const int64_t words = group_compact_words(g.cap_alloc);
-    if (!sc.alloc(words * sizeof(uint64_t))) return set_error(PYST_ERR_NOMEM, "group compaction: arena exhausted");
-    status = sc.as<uint64_t>();
+    if (!status && !sc.alloc(words * sizeof(uint64_t))) return set_error(PYST_ERR_NOMEM, "group compaction: arena exhausted");
+    if (!status) status = sc.as<uint64_t>();
     st = launch_group_init(g, d_nsel, key->n, max_groups, max_load, plan, mode, status, words, stream);
   }
   if (st == PYST_OK) st = group_insert(ctx, g, key, val, sel, d_nsel, 0, plan, mode, stream);

@@ -157,13 +157,13 @@ pyst_status group_insert(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, 
 pyst_status group_compact(pyst_ctx *ctx, const GroupDev &g, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
                           int64_t *d_ngroups, hipStream_t stream);
 // Group-by of columns through the table `g` in HBM (with a plan: only in `mode`).
-// few_status: in mode kGbFew, the table is empty and these group_compact_words
-// are cleared already.
+// status: group_compact_words of memory (null: taken from the arena).  In mode
+// kGbFew they are cleared, and the table empty, already.
 int64_t group_compact_words(int64_t cap_alloc);
 pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val,
                           const int32_t *sel, const int64_t *d_nsel, int64_t max_groups, double max_load,
                           int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, GbPlan *plan,
-                          int mode, uint64_t *few_status, hipStream_t stream);
+                          int mode, uint64_t *status, hipStream_t stream);
 pyst_status filter_impl(pyst_ctx *ctx, const PredSet &ps, int64_t n, int32_t *sel_out, int64_t *d_nsel,
                         hipStream_t stream);
 pyst_status sort_pairs_by_key(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const int64_t *d_count, int64_t cap,

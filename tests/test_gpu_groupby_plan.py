@@ -216,3 +216,36 @@ def test_few_table_full_while_blocks_still_start(gpu):
         np.testing.assert_array_equal(gs[:m].cpu().numpy(), ws)
     for c in ctxs:
         c.close()
+
+
+def rounded(b):
+    return (b + 255) // 256 * 256
+
+
+def test_table_comes_before_what_a_plan_takes(gpu):
+    # arenas that hold the table in HBM and its compaction words, and beside them any first part
+    # of the memory that a plan takes where there is room: the moves' two buffers, the plan, the
+    # few-keys table; each leaves 256 bytes less than the words would need after it
+    rng = np.random.default_rng(13)
+    n = (1 << 24) + 5
+    k = rng.integers(0, 100_000, n) * 1_000_003 - 2**40
+    v = rng.integers(-2**31, 2**31, n).astype(np.int32)
+    wk, ws = oracle.groupby_sum(k, v)
+    dk, dv = dev(k), dev(v)
+    slots = 1 << 25  # n rows at a load of 0.9
+    table, words = 1024 + 16 * slots, rounded(8 * (slots // 2048 + 1))
+    parts, buckets = 64 * 512, 4096 * 8
+    counts = rounded(4 * (512 * 4096 + 2 * (parts + 1 + buckets + 1)))
+    plan = rounded(256 + 8 * 4096 + 16 * 2048 + 8 * 16384)
+    few = rounded(1024 + 16 * 65536 + 8 * (65536 // 2048 + 1))
+    optional = [rounded(16 * n), rounded(counts + 16 * n), plan, few]
+    for held in range(len(optional) + 1):
+        c = gpu.Ctx(0, table + words + max(0, sum(optional[:held]) - 256))
+        gk, gs, ng = gpu.groupby_sum(c, dk, dv, max_load=0.9)
+        c.check()
+        m = int(ng.item())
+        assert m == len(wk), held
+        o = np.argsort(gk[:m].cpu().numpy())
+        np.testing.assert_array_equal(gk[:m].cpu().numpy()[o], wk)
+        np.testing.assert_array_equal(gs[:m].cpu().numpy()[o], ws)
+        c.close()
