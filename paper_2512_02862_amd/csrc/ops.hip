@@ -1439,26 +1439,37 @@ pyst_status sliced_probe(pyst_ctx *ctx, const TableDev &t, const pyst_col *key, 
                          void *ws, int32_t *out_row, PayT *out_pay, int64_t out_cap, int64_t *d_nout,
                          const JoinPlan *plan, hipStream_t stream);
 
+// rows a lane of k_join_probe: four of a narrow table's 8-byte slots, two of a wide one's 16 bytes (1M build
+// and 15M probe rows, narrow: 343 us with four, 370 with two, 476 with one; lookup of 20M 64-bit ids, wide:
+// 786, 680, 819)
+constexpr int kProbeBlock = 1024, kProbeNarrow = 4, kProbeWide = 2;
+static int64_t join_probe_tiles(const TableDev &t, int64_t n) {
+  return std::max<int64_t>(1, ceil_div(n, int64_t{kProbeBlock} * (t.slot_bytes == 16 ? kProbeWide : kProbeNarrow)));
+}
+// Look-back words and ticket of a probe of n rows.
+static size_t join_probe_bytes(const TableDev &t, int64_t n) {
+  return static_cast<size_t>(join_probe_tiles(t, n) + 1) * sizeof(uint64_t);
+}
+
+// words: join_probe_bytes of memory (null: taken from the arena where they are needed).
 template <typename PayT>
 pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, const pyst_col *key, const int32_t *sel,
                               const int64_t *d_nsel, int32_t *out_row, PayT *out_pay, int64_t out_cap,
-                              int64_t *d_nout, hipStream_t stream, const JoinPlan *plan = nullptr) {
+                              int64_t *d_nout, hipStream_t stream, const JoinPlan *plan = nullptr,
+                              uint64_t *words = nullptr) {
   if (sliced_probe_wanted(t, unique, key)) {  // a table beyond the L2, many probes: by slices, where there is room
     Scratch ws(ctx, stream);
     if (ws.try_alloc(sliced_probe_bytes(t, key)))
       return sliced_probe(ctx, t, key, sel, d_nsel, ws.p, out_row, out_pay, out_cap, d_nout, plan, stream);
   }
-  // rows a lane: four of a narrow table's 8-byte slots, two of a wide one's 16 bytes (1M build and 15M
-  // probe rows, narrow: 343 us with four, 370 with two, 476 with one; lookup of 20M 64-bit ids,
-  // wide: 786, 680, 819)
-  constexpr int BLOCK = 1024, NARROW = 4, WIDE = 2;
+  constexpr int BLOCK = kProbeBlock, NARROW = kProbeNarrow, WIDE = kProbeWide;
   const bool wide = t.slot_bytes == 16, k64 = key->dtype == PYST_I64;
-  const int64_t ntiles = std::max<int64_t>(1, ceil_div(key->n, int64_t{BLOCK} * (wide ? WIDE : NARROW)));
-  Scratch sc(ctx, (ntiles + 1) * sizeof(uint64_t), stream);
-  if (!sc.p) return set_error(PYST_ERR_NOMEM, "join probe: arena exhausted");
-  pyst_status st = fill_u64(sc.p, ntiles + 1, 0, stream);
+  const int64_t ntiles = join_probe_tiles(t, key->n);
+  Scratch sc(ctx, stream);
+  if (!words && !sc.alloc(join_probe_bytes(t, key->n))) return set_error(PYST_ERR_NOMEM, "join probe: arena exhausted");
+  uint64_t *status = words ? words : sc.as<uint64_t>();
+  pyst_status st = fill_u64(status, ntiles + 1, 0, stream);
   if (st != PYST_OK) return st;
-  uint64_t *status = sc.as<uint64_t>();
   auto *ticket = reinterpret_cast<unsigned long long *>(status + ntiles);
   const unsigned grid = static_cast<unsigned>(ntiles);
   uint32_t *err = ctx_err_word(ctx);
@@ -1749,10 +1760,12 @@ pyst_status pyst_join_materialize(pyst_ctx *ctx, const pyst_col *build_key, cons
   Scratch mem(ctx, table_bytes(cap_alloc, slot_bytes, false), stream);
   if (!mem.p) return set_error(PYST_ERR_NOMEM, "pyst_join_materialize: arena exhausted");
   const TableDev t = table_view(mem.p, cap_alloc, slot_bytes, false);
-  // several build columns: one random read of a packed row per match instead of one per column
-  Scratch rows(ctx, stream);
-  if (nbcols > 1 && !rows.alloc(static_cast<size_t>(build_key->n) * row_words(nbcols) * sizeof(int64_t)))
-    return set_error(PYST_ERR_NOMEM, "pyst_join_materialize: arena exhausted");
+  // One block of what the call cannot do without beside the table, before what it can: the probe's
+  // words, then in their place the packed build rows (several build columns: one random read of a
+  // packed row per match instead of one per column).
+  const size_t row_bytes = nbcols > 1 ? static_cast<size_t>(build_key->n) * row_words(nbcols) * sizeof(int64_t) : 0;
+  Scratch rest(ctx, std::max(join_probe_bytes(t, probe_key->n), row_bytes), stream);
+  if (!rest.p) return set_error(PYST_ERR_NOMEM, "pyst_join_materialize: arena exhausted");
   // large sides with unique build keys: an array over dense keys where the arena has room for the
   // moves beside the table's memory (which holds the array), decided on the device
   Scratch ws(ctx, stream);
@@ -1774,12 +1787,12 @@ pyst_status pyst_join_materialize(pyst_ctx *ctx, const pyst_col *build_key, cons
       st = direct_join_probe(ctx, build_key->n, probe_key, ws.p, array, out_probe_row, out_build_row, out_cap, d_nout, stream);
     if (st == PYST_OK)
       st = launch_join_probe(ctx, t, unique_keys != 0, probe_key, nullptr, nullptr, out_probe_row, out_build_row, out_cap,
-                             d_nout, stream, plan);
+                             d_nout, stream, plan, rest.as<uint64_t>());
   }
   if (st != PYST_OK) return st;
   if (npcols > 0 && (st = launch_gather(ctx, ga[0], out_probe_row, d_nout, out_cap, stream)) != PYST_OK) return st;
   if (nbcols == 1 && (st = launch_gather(ctx, ga[1], out_build_row, d_nout, out_cap, stream)) != PYST_OK) return st;
-  if (nbcols > 1) return launch_gather_rows(ctx, ga[1], rows.as<int64_t>(), out_build_row, d_nout, out_cap, stream);
+  if (nbcols > 1) return launch_gather_rows(ctx, ga[1], rest.as<int64_t>(), out_build_row, d_nout, out_cap, stream);
   return PYST_OK;
 }
 

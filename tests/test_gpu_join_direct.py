@@ -120,3 +120,32 @@ def test_arena_without_room_for_the_moves(gpu):
     rng = np.random.default_rng(10)
     check(gpu, c, *tables(rng, nb, MIN, nb, 0, np.int32, np.int32))
     c.close()
+
+
+@pytest.mark.parametrize("bcols", [1, 2])
+def test_arenas_from_the_least_to_room_for_the_moves(gpu, bcols):
+    # the least: the table and the larger of the probe's words and the packed rows, which are not
+    # needed at once; then up to where the optional moves (8 + 3 bytes a row and their counts) fit
+    # whole, some 256 bytes short of it, and past it
+    rng = np.random.default_rng(11)
+    nb = MIN + 9
+    bk, pk = tables(rng, nb, MIN + 5, nb, 0, np.int32, np.int32)
+    wp, wb = expect(bk, pk)
+    words = -(-(8 * (-(-len(pk) // 4096) + 1)) // 256) * 256
+    least = 1024 + capacity(nb) * 8 + max(words, -(-(nb * 16) // 256) * 256 if bcols > 1 else 0)
+    tiles, parts = -(-len(pk) // TILE), min(512, -(-nb // TILE))
+    r = lambda b: -(-b // 256) * 256  # noqa: E731
+    moves = (256 + 2 * 2048 * 8 + r((parts + 2 * -(-parts // 16)) * 256 * 4) + r(8 * nb) + r(tiles * 8) + r(2 * len(pk))
+             + r(tiles * TILE) + r(tiles * 1024) + r(tiles * 4))
+    dbk, dpk = dev(bk), dev(pk)
+    bc, pc = [dev(np.arange(nb) * 3 - 7)] * bcols, [dev(np.arange(len(pk)) * 5 + 1)]
+    for more in (0, 256, 1 << 20, moves - 256, moves, moves + words - 256, moves + words, moves + (1 << 20)):
+        c = gpu.Ctx(0, least + more)
+        prow, brow, cols, ng = gpu.join_materialize(c, dbk, bc, dpk, pc)
+        c.check()
+        m = int(ng.item())
+        assert m == len(wp), more
+        np.testing.assert_array_equal(prow[:m].cpu().numpy(), wp)
+        np.testing.assert_array_equal(brow[:m].cpu().numpy(), wb)
+        np.testing.assert_array_equal(cols[-1][:m].cpu().numpy(), wb * 3 - 7)
+        c.close()
