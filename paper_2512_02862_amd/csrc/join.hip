@@ -22,7 +22,8 @@
 // columns, at 5.5 TB/s); 5M x 15M 834 -> 406 us.
 //
 // The choice is made on the device from the build keys' range: direct where the
-// keys span no more values than the hash table has slots, else the hash table's
+// keys span no more values than the hash table has slots (and at most 2^32: a key
+// travels as its 32-bit offset), else the hash table's
 // kernels run and these return at once.  A duplicate key (the caller promised
 // none) leaves fewer filled entries than rows, which is reported.
 #include "pyst_internal.h"
@@ -513,6 +514,7 @@ __global__ __launch_bounds__(kRangeThreads, 8) void k_slice_emit(const JoinPlan 
 // build side lies mostly in the L2s, and fewer probes do not pay for the moves.
 constexpr int64_t kDirectBuildMin = int64_t{1} << 21;
 constexpr int64_t kDirectProbeMin = int64_t{1} << 21;
+constexpr int64_t kDirectRangeMax = int64_t{1} << 32;  // values of an item's offset
 
 bool direct_join_wanted(const pyst_col *build_key, const pyst_col *probe_key, int unique) {
   return unique && build_key->n >= kDirectBuildMin && probe_key->n >= kDirectProbeMin;
@@ -596,7 +598,7 @@ pyst_status direct_join_build(pyst_ctx *ctx, const pyst_col *build_key, int64_t 
       : k_join_range<false><<<rblocks, 256, 0, stream>>>(build_key->data, nb, lo, lo + kJoinRangeBlocks, ctx_err_word(ctx));
   PYST_LAUNCH_CHECK("k_join_range");
   k_join_plan<<<1, kRangeThreads, 0, stream>>>(d.plan, lo, lo + kJoinRangeBlocks, rblocks,
-                                              static_cast<uint64_t>(range_max), d.build.counts);
+                                              static_cast<uint64_t>(std::min(range_max, kDirectRangeMax)), d.build.counts);
   PYST_LAUNCH_CHECK("k_join_plan");
   k_direct_clear<<<grid_for(ctx, range_max / 4, 256, 8), 256, 0, stream>>>(d);
   PYST_LAUNCH_CHECK("k_direct_clear");

@@ -149,3 +149,49 @@ def test_arenas_from_the_least_to_room_for_the_moves(gpu, bcols):
         np.testing.assert_array_equal(brow[:m].cpu().numpy(), wb)
         np.testing.assert_array_equal(cols[-1][:m].cpu().numpy(), wb * 3 - 7)
         c.close()
+
+
+PIECE = 1 << 18  # least keys of a slice
+
+
+@pytest.mark.parametrize("span", [8 * PIECE - 1, 8 * PIECE, 8 * PIECE + 1, 12 * PIECE - 1, 12 * PIECE, 12 * PIECE + 1])
+def test_whole_slices(gpu, ctx, span):
+    rng = np.random.default_rng(span)
+    nb = MIN if span >= MIN else span
+    bk, pk = tables(rng, nb, MIN + 3, span, -5, np.int32, np.int64)
+    pk[:40] = -5 + np.clip(np.repeat(np.arange(20) * PIECE, 2) + np.tile([-1, 0], 20), 0, None)
+    check(gpu, ctx, bk, pk)
+
+
+def load_for(nb, slots):
+    """A load under which nb rows take that power of two of slots."""
+    load = nb / (slots * 0.9)
+    assert capacity(nb, load) == slots
+    return load
+
+
+@pytest.mark.parametrize("span", [(1 << 26) + 1, (1 << 27) - 1, 1 << 27, (1 << 27) + 1])
+@pytest.mark.parametrize("bt", [np.int32, np.int64])
+def test_ranges_of_larger_slices(gpu, ctx, span, bt):
+    # over 256 slices of 2^18 keys: twice as many keys a slice
+    rng = np.random.default_rng(span)
+    nb = MIN + 7
+    bk, pk = tables(rng, nb, MIN + 3, span, 11, bt, np.int32)
+    check(gpu, ctx, bk, pk, max_load=load_for(nb, 1 << 27))
+
+
+def test_range_beyond_32_bits(gpu):
+    # keys in pairs 2^32 apart, fewer values than the table has slots: their offsets do not fit 32 bits
+    import torch
+    slots = 1 << 33
+    budget = 16 * slots + (1 << 30)
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < budget + (8 << 30):
+        pytest.skip("a table of 2^33 16-byte slots does not fit the free memory")
+    rng = np.random.default_rng(12)
+    low = np.sort(rng.choice(1 << 24, MIN // 2 + 1, replace=False))
+    bk = rng.permutation(np.concatenate([low, low + (1 << 32)])) - 3
+    pk = rng.permutation(np.concatenate([bk[:MIN // 2], bk[:MIN] + 1, [2**33, -4, 2**63 - 1, -2**63]]))
+    c = gpu.Ctx(0, budget)
+    check(gpu, c, bk, pk, max_load=load_for(len(bk), slots))
+    c.close()

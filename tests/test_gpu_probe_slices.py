@@ -154,3 +154,21 @@ def test_empty_selection_first_in_a_used_arena(gpu, wide, build_sel):
     check(gpu, c, bk, pay, pk, bsel, np.array([len(pk) - 1], np.int32))
     check(gpu, c, bk, pay, pk, bsel, np.zeros(0, np.int32))
     c.close()
+
+
+@pytest.mark.parametrize("wide,slots", [(False, 1 << 26), (False, 1 << 27), (True, 1 << 25), (True, 1 << 26)])
+def test_slices_of_more_than_the_least_slots(gpu, ctx, wide, slots):
+    # from 2^27 slots of 8 bytes and 2^26 of 16, 256 slices take more than 2 MiB each
+    rng = np.random.default_rng(slots)
+    kt = np.int64 if wide else np.int32
+    bk, pk = sides(rng, 1_100_000, ROWS + 5, kt, kt, True)
+    t = gpu.join_build(ctx, dev(bk), max_load=len(bk) / (slots * 0.9))
+    assert t.info()[0] == slots
+    rows, vals, ng = gpu.join_probe(ctx, t, dev(pk))
+    ctx.check()
+    m = int(ng.item())
+    wr, wv = expect(bk, None, pk, None, None)
+    assert m == len(wr)
+    np.testing.assert_array_equal(rows[:m].cpu().numpy(), wr)
+    np.testing.assert_array_equal(vals[:m].cpu().numpy(), wv)
+    t.destroy()
