@@ -119,6 +119,18 @@ struct BucketPool {
 };
 constexpr size_t kPoolHeadBytes = kMaxSumBuckets * sizeof(uint32_t);  // the next[] counters ahead of the records
 
+// Where a single query's records start, whatever the arena's state: 1536 bytes
+// past a 2 KiB boundary.  The time of the fact pass and the sums follows the
+// address of the chunks modulo 2 KiB, whichever way the fact columns lie: 1.5M
+// dimension and 60M fact rows, a query 302, 303, 300, 300, 301, 300, 298, 298.5
+// us as the records start at 0, 256, ... 1792.  Left to the arena it was one of
+// these by what ran before.  The 1792 bytes are less than one chunk.
+constexpr size_t kPoolPeriod = 2048, kPoolPlace = 1536, kPoolSlack = kPoolPeriod - 256;
+inline uint64_t *pool_records(char *head) {
+  const uintptr_t p = reinterpret_cast<uintptr_t>(head) + kPoolHeadBytes;
+  return reinterpret_cast<uint64_t *>(p + (kPoolPlace + kPoolPeriod - p % kPoolPeriod) % kPoolPeriod);
+}
+
 __host__ __device__ inline uint32_t bucket_count(int64_t cap) {
   return cap > kBucketSlots ? static_cast<uint32_t>(cap >> kBucketLg) : 1u;
 }
@@ -2113,13 +2125,13 @@ pyst_status fast_query(pyst_ctx *ctx, const pyst_plan *plan, const QueryShape &q
     const int64_t cap_alloc = table_capacity_host(plan->joins[0].key.n, plan->joins[0].max_load);
     const int64_t grid = fast_grid(ctx, fa.n);
     const int64_t stride = std::min<int64_t>(kMaxBuckets, bucket_count(cap_alloc));
-    const int64_t nchunks = grid * stride + ceil_div(fa.n, int64_t{kChunk}) + 1;
+    const int64_t nchunks = grid * stride + ceil_div(fa.n, int64_t{kChunk});
     if (cap_alloc <= kBucketSlots * kMaxSumBuckets && nchunks < (int64_t{1} << 31))
-      pool = ctx_alloc(ctx, kPoolHeadBytes + static_cast<size_t>(nchunks) * (size_t{kChunk} * 8 + 4), stream);
+      pool = ctx_alloc(ctx, kPoolHeadBytes + kPoolSlack + static_cast<size_t>(nchunks) * (size_t{kChunk} * 8 + 4), stream);
     if (pool) {
       char *p = static_cast<char *>(pool);
       bp.next = reinterpret_cast<uint32_t *>(p);  // zeroed by the table initializer
-      bp.rec = reinterpret_cast<uint64_t *>(p + kPoolHeadBytes);
+      bp.rec = pool_records(p);
       bp.fill = reinterpret_cast<uint32_t *>(bp.rec + static_cast<size_t>(nchunks) * kChunk);
       bp.nchunks = static_cast<uint32_t>(nchunks);
       bp.chunk_lg = kChunkLg;

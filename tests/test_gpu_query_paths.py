@@ -483,3 +483,21 @@ def test_fast_query_capacity_error(gpu, ctx):
         ctx.check()
     assert e.value.status == gpu.ERR_CAPACITY
     assert int(ng.item()) == len(oracle.star_query(b, p)[0])
+
+
+@pytest.mark.parametrize("held", range(4))
+def test_star_wherever_the_arena_puts_its_records(gpu, held):
+    # each small table held takes 1536 bytes, so the pool starts at another place of its 2 KiB period
+    b, p = gen.star_tables(30_000, 300_001)
+    bd = {k: dev(v) for k, v in b.items()}
+    fact = [dev(p[c]) for c in FACT_STAR]
+    wk, ws = oracle.star_query(b, p)
+    for budget in (64 << 20, 2 << 20):  # (short: no room for a pool, the rows add in the table)
+        c = gpu.Ctx(0, budget)
+        tables = [gpu.join_build(c, dev(np.arange(3, dtype=np.int32))) for _ in range(held)]
+        k, s = run(gpu, c, gpu.star_plan(bd), fact, "fast")
+        np.testing.assert_array_equal(k, wk)
+        np.testing.assert_array_equal(s, ws)
+        for t in tables:
+            t.destroy()
+        c.close()
