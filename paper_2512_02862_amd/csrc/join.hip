@@ -99,10 +99,11 @@ struct HashRows {
   const JoinPlan *plan;  // may be null
   const int64_t *hdr;
   int shift;             // slots a slice
+  ProbeRule rule;
   int64_t mask = 0;
   __device__ __forceinline__ bool open() {
     mask = hdr[0] - 1;
-    return !(plan && plan->direct);
+    return !(plan && plan->direct) && !rule.not_by_slices();
   }
   __device__ __forceinline__ uint32_t slice(int64_t k) const {
     if constexpr (WIDE) return static_cast<uint32_t>((table_hash64(k) & static_cast<uint64_t>(mask)) >> shift);
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(256) void k_hash_lookup(HashRows<WIDE, K64> p, Slic
 // by look-back over the tiles.  HASH: results are payloads with found bits, else
 // build rows, -1 for none.
 template <typename Item, bool HASH, typename PayT>
-__global__ __launch_bounds__(kRangeThreads, 8) void k_slice_emit(const JoinPlan *plan, Slices d, const int32_t *sel,
+__global__ __launch_bounds__(kRangeThreads, 8) void k_slice_emit(const JoinPlan *plan, ProbeRule rule, Slices d, const int32_t *sel,
                                                                 const int64_t *d_nsel, int64_t n_all, int32_t *out_row,
                                                                 PayT *out_pay, int64_t out_cap, int64_t *d_nout,
                                                                 uint32_t *err) {
@@ -432,6 +433,7 @@ __global__ __launch_bounds__(kRangeThreads, 8) void k_slice_emit(const JoinPlan 
   __shared__ int32_t s_w[NW];
   __shared__ int64_t s_tile, s_prefix;
   if (plan && (plan->direct != 0) == HASH) return;
+  if (HASH && rule.not_by_slices()) return;
   const int64_t n = std::min(count_of(d_nsel, n_all), n_all), ntiles = (n + kSliceTile - 1) / kSliceTile;
   const int tid = static_cast<int>(threadIdx.x), w = tid / kWave, lane = lane_id();
   if (blockIdx.x >= ntiles) {
@@ -625,7 +627,7 @@ pyst_status direct_join_probe(pyst_ctx *ctx, int64_t nb, const pyst_col *probe_k
   k_direct_lookup<<<static_cast<unsigned>(ceil_div(np, 2048)), 256, 0, stream>>>(d);
   PYST_LAUNCH_CHECK("k_direct_lookup");
   k_slice_emit<uint32_t, false, int32_t><<<static_cast<unsigned>(d.probe.ntiles), kRangeThreads, 0, stream>>>(
-      d.plan, d.probe, nullptr, nullptr, np, out_row, out_build, out_cap, d_nout, ctx_err_word(ctx));
+      d.plan, ProbeRule{}, d.probe, nullptr, nullptr, np, out_row, out_build, out_cap, d_nout, ctx_err_word(ctx));
   PYST_LAUNCH_CHECK("k_slice_emit");
   return PYST_OK;
 }
@@ -639,7 +641,7 @@ pyst_status direct_join_probe(pyst_ctx *ctx, int64_t nb, const pyst_col *probe_k
 // 680 -> 465 us (counts 43, move 87, lookup 226, way back 109); 50M of 9M int32
 // keys with build 1625 -> 1339 us; a 20M x 60M join of sparse 64-bit keys 3993 ->
 // 3726 us.  Duplicate keys (any number of matches a row) and arenas without room
-// keep k_join_probe.
+// keep k_join_probe; for tables built from a selection the device chooses (ProbeRule).
 constexpr int64_t kHashTableMin = int64_t{16} << 20;   // bytes
 constexpr int64_t kHashProbeMin = int64_t{1} << 21;    // rows
 constexpr int kHashSliceLg = 21;                       // bytes a slice
@@ -681,9 +683,10 @@ size_t sliced_probe_bytes(const TableDev &t, const pyst_col *key) {
 template <bool WIDE, bool K64, typename PayT>
 static pyst_status launch_sliced_probe(pyst_ctx *ctx, const TableDev &t, const pyst_col *key, const int32_t *sel,
                                        const int64_t *d_nsel, const HashProbe &h, int32_t *out_row, PayT *out_pay,
-                                       int64_t out_cap, int64_t *d_nout, const JoinPlan *plan, hipStream_t stream) {
+                                       int64_t out_cap, int64_t *d_nout, const JoinPlan *plan, const ProbeRule &rule,
+                                       hipStream_t stream) {
   using P = HashRows<WIDE, K64>;
-  P p{plan, t.hdr, kHashSliceLg - (WIDE ? 4 : 3)};
+  P p{plan, t.hdr, kHashSliceLg - (WIDE ? 4 : 3), rule};
   while (((t.cap_alloc - 1) >> p.shift) >= kRangeDigits) ++p.shift;
   launch_slices(p, h.s, key, sel, d_nsel, stream);
   PYST_LAUNCH_CHECK("k_slice_move");
@@ -691,30 +694,42 @@ static pyst_status launch_sliced_probe(pyst_ctx *ctx, const TableDev &t, const p
       p, h.s, static_cast<const uint64_t *>(t.slots));
   PYST_LAUNCH_CHECK("k_hash_lookup");
   k_slice_emit<typename P::Item, true, PayT><<<static_cast<unsigned>(h.s.ntiles), kRangeThreads, 0, stream>>>(
-      plan, h.s, sel, d_nsel, key->n, out_row, out_pay, out_cap, d_nout, ctx_err_word(ctx));
+      plan, rule, h.s, sel, d_nsel, key->n, out_row, out_pay, out_cap, d_nout, ctx_err_word(ctx));
   PYST_LAUNCH_CHECK("k_slice_emit");
   return PYST_OK;
 }
 
-// launch_join_probe's results through slices, in `ws` of sliced_probe_bytes.
+ProbeRule sliced_probe_rule(const TableDev &t, const pyst_col *key, const int64_t *d_nsel) {
+  ProbeRule r;
+  r.hdr = t.hdr;
+  r.d_nsel = d_nsel;
+  r.n = key->n;
+  r.slots_min = kHashTableMin / t.slot_bytes;
+  return r;
+}
+
+// launch_join_probe's results through slices, in `ws` of `lead` bytes (a multiple
+// of 256, cleared with the scratch's head) and sliced_probe_bytes.
 template <typename PayT>
 pyst_status sliced_probe(pyst_ctx *ctx, const TableDev &t, const pyst_col *key, const int32_t *sel, const int64_t *d_nsel,
-                         void *ws, int32_t *out_row, PayT *out_pay, int64_t out_cap, int64_t *d_nout,
-                         const JoinPlan *plan, hipStream_t stream) {
+                         void *ws, size_t lead, int32_t *out_row, PayT *out_pay, int64_t out_cap, int64_t *d_nout,
+                         const JoinPlan *plan, const ProbeRule &rule, hipStream_t stream) {
   HashProbe h{};
-  hash_probe_layout(static_cast<char *>(ws), key->n, t.slot_bytes, &h);
-  const pyst_status st = fill_u32(h.head, h.head_words, 0, stream);
+  hash_probe_layout(static_cast<char *>(ws) + lead, key->n, t.slot_bytes, &h);
+  const pyst_status st = fill_u32(ws, static_cast<int64_t>(lead / 4) + h.head_words, 0, stream);
   if (st != PYST_OK) return st;
   const bool k64 = key->dtype == PYST_I64;
   if (t.slot_bytes == 16)
-    return k64 ? launch_sliced_probe<true, true>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, stream)
-               : launch_sliced_probe<true, false>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, stream);
-  return k64 ? launch_sliced_probe<false, true>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, stream)
-             : launch_sliced_probe<false, false>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, stream);
+    return k64 ? launch_sliced_probe<true, true>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, rule, stream)
+               : launch_sliced_probe<true, false>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, rule, stream);
+  return k64 ? launch_sliced_probe<false, true>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, rule, stream)
+             : launch_sliced_probe<false, false>(ctx, t, key, sel, d_nsel, h, out_row, out_pay, out_cap, d_nout, plan, rule, stream);
 }
 template pyst_status sliced_probe<int32_t>(pyst_ctx *, const TableDev &, const pyst_col *, const int32_t *, const int64_t *,
-                                           void *, int32_t *, int32_t *, int64_t, int64_t *, const JoinPlan *, hipStream_t);
+                                           void *, size_t, int32_t *, int32_t *, int64_t, int64_t *, const JoinPlan *,
+                                           const ProbeRule &, hipStream_t);
 template pyst_status sliced_probe<int64_t>(pyst_ctx *, const TableDev &, const pyst_col *, const int32_t *, const int64_t *,
-                                           void *, int32_t *, int64_t *, int64_t, int64_t *, const JoinPlan *, hipStream_t);
+                                           void *, size_t, int32_t *, int64_t *, int64_t, int64_t *, const JoinPlan *,
+                                           const ProbeRule &, hipStream_t);
 
 }  // namespace pyst

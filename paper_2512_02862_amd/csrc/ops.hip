@@ -872,8 +872,8 @@ __global__ __launch_bounds__(BLOCK) void k_join_probe(const void *key, const int
                                                      const int64_t *d_nsel, int64_t n, TableDev t, int unique,
                                                      int32_t *out_row, PayT *out_pay, int64_t out_cap, int64_t *d_nout,
                                                      uint64_t *status, unsigned long long *ticket, int64_t ntiles,
-                                                     uint32_t *err, const JoinPlan *plan) {
-  if (plan && plan->direct) return;
+                                                     uint32_t *err, const JoinPlan *plan, ProbeRule rule) {
+  if ((plan && plan->direct) || rule.not_in_one_pass()) return;
   constexpr int NW = BLOCK / kWave;
   constexpr int64_t TILE = int64_t{BLOCK} * ITEMS;
   __shared__ int64_t s_tile, s_prefix;
@@ -1434,10 +1434,11 @@ pyst_status launch_join_build(pyst_ctx *ctx, const TableDev &t, const pyst_col *
 // Defined with the sliced joins.
 bool sliced_probe_wanted(const TableDev &t, int unique, const pyst_col *key);
 size_t sliced_probe_bytes(const TableDev &t, const pyst_col *key);
+ProbeRule sliced_probe_rule(const TableDev &t, const pyst_col *key, const int64_t *d_nsel);
 template <typename PayT>
 pyst_status sliced_probe(pyst_ctx *ctx, const TableDev &t, const pyst_col *key, const int32_t *sel, const int64_t *d_nsel,
-                         void *ws, int32_t *out_row, PayT *out_pay, int64_t out_cap, int64_t *d_nout,
-                         const JoinPlan *plan, hipStream_t stream);
+                         void *ws, size_t lead, int32_t *out_row, PayT *out_pay, int64_t out_cap, int64_t *d_nout,
+                         const JoinPlan *plan, const ProbeRule &rule, hipStream_t stream);
 
 // rows a lane of k_join_probe: four of a narrow table's 8-byte slots, two of a wide one's 16 bytes (1M build
 // and 15M probe rows, narrow: 343 us with four, 370 with two, 476 with one; lookup of 20M 64-bit ids, wide:
@@ -1457,38 +1458,48 @@ pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, cons
                               const int64_t *d_nsel, int32_t *out_row, PayT *out_pay, int64_t out_cap,
                               int64_t *d_nout, hipStream_t stream, const JoinPlan *plan = nullptr,
                               uint64_t *words = nullptr) {
+  Scratch ws(ctx, stream);
+  ProbeRule rule;
   if (sliced_probe_wanted(t, unique, key)) {  // a table beyond the L2, many probes: by slices, where there is room
-    Scratch ws(ctx, stream);
-    if (ws.try_alloc(sliced_probe_bytes(t, key)))
-      return sliced_probe(ctx, t, key, sel, d_nsel, ws.p, out_row, out_pay, out_cap, d_nout, plan, stream);
+    // (where only the device knows the table's size, both ways are enqueued and one returns at once)
+    const size_t lead = t.selected ? (join_probe_bytes(t, key->n) + 255) / 256 * 256 : 0;
+    if (ws.try_alloc(lead + sliced_probe_bytes(t, key))) {
+      if (t.selected) rule = sliced_probe_rule(t, key, d_nsel);
+      const pyst_status st = sliced_probe(ctx, t, key, sel, d_nsel, ws.p, lead, out_row, out_pay, out_cap, d_nout, plan,
+                                          rule, stream);
+      if (st != PYST_OK || !t.selected) return st;
+    }
   }
   constexpr int BLOCK = kProbeBlock, NARROW = kProbeNarrow, WIDE = kProbeWide;
   const bool wide = t.slot_bytes == 16, k64 = key->dtype == PYST_I64;
   const int64_t ntiles = join_probe_tiles(t, key->n);
   Scratch sc(ctx, stream);
-  if (!words && !sc.alloc(join_probe_bytes(t, key->n))) return set_error(PYST_ERR_NOMEM, "join probe: arena exhausted");
-  uint64_t *status = words ? words : sc.as<uint64_t>();
-  pyst_status st = fill_u64(status, ntiles + 1, 0, stream);
-  if (st != PYST_OK) return st;
+  uint64_t *status = ws.as<uint64_t>();
+  if (!status) {
+    if (!words && !sc.alloc(join_probe_bytes(t, key->n))) return set_error(PYST_ERR_NOMEM, "join probe: arena exhausted");
+    status = words ? words : sc.as<uint64_t>();
+    const pyst_status st = fill_u64(status, ntiles + 1, 0, stream);
+    if (st != PYST_OK) return st;
+  }
   auto *ticket = reinterpret_cast<unsigned long long *>(status + ntiles);
   const unsigned grid = static_cast<unsigned>(ntiles);
   uint32_t *err = ctx_err_word(ctx);
   if (wide && k64)
     k_join_probe<BLOCK, WIDE, true, true, PayT><<<grid, BLOCK, 0, stream>>>(
         key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
-        plan);
+        plan, rule);
   else if (wide)
     k_join_probe<BLOCK, WIDE, true, false, PayT><<<grid, BLOCK, 0, stream>>>(
         key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
-        plan);
+        plan, rule);
   else if (k64)
     k_join_probe<BLOCK, NARROW, false, true, PayT><<<grid, BLOCK, 0, stream>>>(
         key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
-        plan);
+        plan, rule);
   else
     k_join_probe<BLOCK, NARROW, false, false, PayT><<<grid, BLOCK, 0, stream>>>(
         key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
-        plan);
+        plan, rule);
   PYST_LAUNCH_CHECK("k_join_probe");
   return PYST_OK;
 }
@@ -1694,6 +1705,7 @@ pyst_status pyst_join_build(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
   t->ctx = ctx;
   t->mem = mem;
   t->dev = table_view(mem, cap_alloc, slot_bytes, false);
+  t->dev.selected = sel != nullptr;
   t->unique = unique_keys != 0;
   t->stream = stream;
   pyst_status st = launch_join_build(ctx, t->dev, key, payload, sel, d_nsel, max_load, t->unique, stream);

@@ -28,7 +28,7 @@ struct TableDev {
   uint32_t *bloom; // optional blocked Bloom filter over the inserted keys (fast path)
   int64_t cap_alloc;
   int32_t slot_bytes;
-  int32_t reserved;
+  int32_t selected;  // built from a selection: only the device knows how many slots it uses
 };
 
 struct GroupDev {
@@ -69,6 +69,29 @@ pyst_status direct_join_build(pyst_ctx *ctx, const pyst_col *build_key, int64_t 
                               int64_t range_max, const JoinPlan **plan, hipStream_t stream);
 pyst_status direct_join_probe(pyst_ctx *ctx, int64_t nb, const pyst_col *probe_key, void *ws, int32_t *array,
                               int32_t *out_row, int32_t *out_build, int64_t out_cap, int64_t *d_nout, hipStream_t stream);
+
+// How a table that was built from a selection is probed, chosen on the device:
+// by slices where it is as large as the host asks of other tables, or half of
+// that if the probed column is long (8 MiB of slots, 20M probes 317 us by slices,
+// 330 in one pass; 2.5M 73 and 62), or where only a small part of a long column is
+// probed (the one-pass probe takes a ticket for every tile of the column, 14 ns
+// each: 1000 of 20M rows 140 us, by slices 29); else in one pass (five built rows,
+// all of 20M probed: 290 us by slices, 98 in one pass; of 2.5M 72 and 24).  The
+// launches that find nothing to do cost 3 to 12 us; a one-pass kernel of few
+// blocks that walk its tiles would spare 7 of them, and ran 20 % longer.
+struct ProbeRule {
+  const int64_t *hdr = nullptr;  // of the table; null: the host has chosen
+  const int64_t *d_nsel = nullptr;
+  int64_t n = 0, slots_min = 0;
+  static constexpr int64_t kLongColumn = int64_t{1} << 22;
+  __device__ __forceinline__ bool by_slices() const {
+    if (n < kLongColumn) return hdr[0] >= slots_min;
+    const int64_t rows = d_nsel ? *d_nsel : n;
+    return hdr[0] >= slots_min / 2 || rows < n / 4;
+  }
+  __device__ __forceinline__ bool not_by_slices() const { return hdr && !by_slices(); }
+  __device__ __forceinline__ bool not_in_one_pass() const { return hdr && by_slices(); }
+};
 
 __device__ __forceinline__ int32_t plan_mode(const GbPlan *p) {
   return p->mode == kGbFew && p->few_failed ? p->otherwise : p->mode;

@@ -172,3 +172,47 @@ def test_slices_of_more_than_the_least_slots(gpu, ctx, wide, slots):
     np.testing.assert_array_equal(rows[:m].cpu().numpy(), wr)
     np.testing.assert_array_equal(vals[:m].cpu().numpy(), wv)
     t.destroy()
+
+
+LONG = 1 << 22  # rows of a column of which a small part is probed by slices, whatever the table
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("npr", [LONG - 1, LONG])
+@pytest.mark.parametrize("built,probed", [(5, LONG // 4 - 2), (5, LONG // 4), (0, 0), (70_000, 1), (70_000, None),
+                                          (1_099_999, LONG // 4 + 1), (1_099_999, 1000)])
+def test_tables_built_from_a_selection(gpu, ctx, wide, npr, built, probed):
+    # the device chooses by the slots the table uses and the rows probed
+    rng = np.random.default_rng(npr + built)
+    kt = np.int64 if wide else np.int32
+    bk, pk = sides(rng, 1_100_000, npr, kt, kt, False)
+    bsel = np.sort(rng.choice(len(bk), built, replace=False)).astype(np.int32)
+    psel = None if probed is None else np.sort(rng.choice(npr, probed, replace=False)).astype(np.int32)
+    check(gpu, ctx, bk, rng.integers(-2**31, 2**31, len(bk)).astype(np.int32), pk, bsel, psel)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+def test_few_built_rows_cost_what_a_small_table_does(gpu, ctx, wide):
+    # all of 2^23 rows probed in a table of five rows: selected from a large column, or a column of five.
+    # By slices the first takes three (two) times as long as the second; the limit lies between that and one.
+    import torch
+    rng = np.random.default_rng(7)
+    kt = np.int64 if wide else np.int32
+    bk = rng.permutation(4_000_000).astype(kt)
+    pk = dev(rng.integers(0, 4_000_000, 1 << 23).astype(kt))
+    tables = [gpu.join_build(ctx, dev(bk), **sel_kw(np.arange(5, dtype=np.int32))), gpu.join_build(ctx, dev(bk[:5]))]
+    times = [[], []]
+    for _ in range(7):
+        for t, out in zip(tables, times):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            gpu.join_probe(ctx, t, pk)
+            a.record()
+            for _ in range(10):
+                gpu.join_probe(ctx, t, pk)
+            b.record()
+            b.synchronize()
+            out.append(a.elapsed_time(b))
+    ctx.check()
+    assert min(times[0]) < 1.6 * min(times[1])
+    for t in tables:
+        t.destroy()
