@@ -52,7 +52,13 @@ __device__ __forceinline__ uint64_t agg_hash(int64_t key) { return fmix64(static
 //             wants 2048 rows a group (2M rows, int64 keys, against hash buckets:
 //             300 groups 144 and 193 us, 900 189 and 200, 1400 224 and 199; 20M
 //             into 1400 419 and 770), and room in the blocks' 4096 LDS slots
-//             (20M into 2800: 2770 us, 748 hashed).
+//             (20M into 2800: 2770 us, 748 hashed).  The same for few rows, which only
+//             the device knows of a selection: up to half of the table's slots where
+//             nothing else but hash buckets is left (10000 of 20M rows, 64-bit keys
+//             over 2^40: 471 -> 64 us, 566 -> 160 ordered), and instead of the moves up
+//             to 8192 (whose groups one block sorts; 5000 of 1.1M, 64-bit keys over
+//             275000: 94 -> 48, 126 -> 104 ordered) or 1024 of one move (5000 ordered:
+//             89 by one move, 98 so).
 //   kGbHash   otherwise: hash buckets, each summed in an LDS hash table.
 //   kGbTable  the same where hash buckets have no memory or too many groups: the
 //             table in HBM (k_gb_insert).
@@ -70,6 +76,7 @@ constexpr int kOnceShift = 14, kOnceSlots = 1 << kOnceShift;  // LDS sums of one
 constexpr int kFewKeys = 1500;                    // different keys of the sample, at most
 constexpr int64_t kFewRows = 2048;                // rows per different key, at least
 constexpr int64_t kFewSlots = int64_t{1} << 16;   // slots of the table in HBM
+constexpr int64_t kFewRowsMoves = 8192, kFewRowsOnce = 1024;  // rows that take it instead of two moves, of one
 
 __device__ __forceinline__ bool plan_moves(const GbPlan *p) {
   return !p || plan_mode(p) == kGbHash || plan_mode(p) == kGbRange;
@@ -1002,9 +1009,12 @@ __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64
     hi = s_hi[w] > hi ? s_hi[w] : hi;
   }
   const uint64_t range = lo > hi ? 0 : static_cast<uint64_t>(hi) - static_cast<uint64_t>(lo) + 1;
+  const int64_t cnt = std::min(count_of(d_nsel, n), n);
   int32_t mode = otherwise, shift = 0;
   if (range <= static_cast<uint64_t>(small_max)) {
     mode = kGbSmall;
+  } else if (allow_few && cnt <= (allow_once ? kFewRowsOnce : kFewRowsMoves)) {  // block-uniform
+    mode = kGbFew;
   } else if (allow_range && range <= static_cast<uint64_t>(kAggBuckets) * kDirectSlots) {  // block-uniform
     mode = kGbRange;
     while (((range - 1) >> shift) >= kAggBuckets) ++shift;
@@ -1034,7 +1044,9 @@ __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64
       shift = once_shift;
     }
   }
-  if (mode == otherwise && allow_few) {  // block-uniform: different keys of the sample, by their hash bits
+  if (mode == otherwise && allow_few && cnt <= kFewSlots / 2) {  // no more groups than rows: the table holds any
+    mode = kGbFew;
+  } else if (mode == otherwise && allow_few) {  // block-uniform: different keys of the sample, by their hash bits
     constexpr int kBits = kAggBuckets * 32;
     __syncthreads();
     for (int i = tid; i < kAggBuckets; i += kAggBlock) s_c[i] = 0;
@@ -1047,14 +1059,12 @@ __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64
     news = wave_sum(news);
     if (lane_id() == 0) atomicAdd(&s_distinct, news);
     __syncthreads();
-    const int64_t cnt = count_of(d_nsel, n);
     if (s_distinct <= kFewKeys && s_distinct <= cnt / kFewRows) mode = kGbFew;
   }
   if (tid == 0) {
-    int64_t cnt = count_of(d_nsel, n);
     plan->kmin = lo;
     plan->range = range;
-    plan->count = cnt < n ? cnt : n;
+    plan->count = cnt;
     plan->mode = mode;
     plan->shift = shift;
     plan->sort_count = 0;

@@ -249,3 +249,45 @@ def test_table_comes_before_what_a_plan_takes(gpu):
         np.testing.assert_array_equal(gk[:m].cpu().numpy()[o], wk)
         np.testing.assert_array_equal(gs[:m].cpu().numpy()[o], ws)
         c.close()
+
+
+@pytest.mark.parametrize("kt,vt", [(np.int32, np.int32), (np.int64, np.int64)])
+@pytest.mark.parametrize("span", [SMALL + 1, 1 << 31])
+@pytest.mark.parametrize("picked", [0, 1, 1024, 1025, 8192, 8193, 32768, 32769])
+def test_few_selected_rows(gpu, ctx, kt, vt, span, picked):
+    # up to these numbers of rows the table takes them, whatever their keys
+    rng = np.random.default_rng(picked)
+    n = 1 << 20
+    k = keys_over(rng, n, span, -2**31, kt)
+    info = np.iinfo(vt)
+    v = rng.integers(info.min, info.max, n, dtype=vt, endpoint=True)
+    check(gpu, ctx, k, v, np.sort(rng.choice(n, picked, replace=False)).astype(np.int32))
+    check(gpu, ctx, np.full(n, k[1]), v, np.sort(rng.choice(n, picked, replace=False)).astype(np.int32))
+
+
+def time_groupby(gpu, ctx, *args, **kw):
+    import torch
+    best = []
+    for _ in range(7):
+        gpu.groupby_sum(ctx, *args, max_groups=1 << 20, **kw)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(10):
+            gpu.groupby_sum(ctx, *args, max_groups=1 << 20, **kw)
+        b.record()
+        b.synchronize()
+        best.append(a.elapsed_time(b))
+    return min(best)
+
+
+def test_few_selected_rows_cost_what_few_rows_do(gpu, ctx):
+    # 1000 of 8M rows, random 64-bit keys, against a column of 1000 rows.  By hash buckets the first takes
+    # over ten times as long; the limit lies between that and the launches that choose.
+    rng = np.random.default_rng(8)
+    n = 8_000_000
+    k, v = dev(rng.integers(0, 1 << 40, n)), dev(rng.integers(0, 99, n))
+    sel = np.sort(rng.choice(n, 1000, replace=False)).astype(np.int32)
+    few = time_groupby(gpu, ctx, k, v, sel=dev(sel), nsel=dev(np.array([1000], np.int64)))
+    column = time_groupby(gpu, ctx, k[:1000].contiguous(), v[:1000].contiguous())
+    ctx.check()
+    assert few < 5 * column, (few, column)
