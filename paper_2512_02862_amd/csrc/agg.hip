@@ -46,7 +46,7 @@ __device__ __forceinline__ uint64_t agg_hash(int64_t key) { return fmix64(static
 //   kGbOnce   the same for int32 keys and values that span at most 1024 buckets of
 //             16384 values: one move, of 8-byte pairs, does (see k_once_move).
 //   kGbFew    the sample finds few different keys, over any range: a table in HBM
-//             behind an LDS table per block (k_gb_insert).  The sample promises
+//             behind an LDS table per block (gb_insert_rows).  The sample promises
 //             nothing: a table that runs full sends the rows on to kGbHash.
 //             Every block adds its own table's groups to the one in HBM, so this
 //             wants 2048 rows a group (2M rows, int64 keys, against hash buckets:
@@ -375,6 +375,7 @@ __global__ __launch_bounds__(kAggBlock) void k_bucket_groups(const int64_t *keys
 // The moves and the bucket pass; the first move reads `first` (pairs or columns),
 // the second writes keys/vals (cap entries each).
 // With first.plan, `status` holds kAggBuckets look-back words (cleared by k_gb_plan).
+// Without hash_buckets the plan does not choose them.
 __global__ void k_narrow_counts(const int32_t *counts, int32_t *c1, int32_t *c2, const GbPlan *plan);
 __global__ void k_move_positions(const int32_t *c1, int32_t *p1, const int32_t *c2, int32_t *p2, const GbPlan *plan);
 template <bool NARROW>
@@ -392,7 +393,7 @@ static size_t wide_groupby_bytes(int64_t cap) { return wide_count_bytes() + stat
 
 pyst_status pair_groupby_from(pyst_ctx *ctx, MoveArgs first, int64_t *keys, int64_t *vals, const int64_t *count,
                               int64_t cap, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
-                              int64_t *d_ngroups, uint64_t *status, void *ws, hipStream_t stream) {
+                              int64_t *d_ngroups, uint64_t *status, void *ws, bool hash_buckets, hipStream_t stream) {
   if (cap >= (int64_t{1} << 31)) return set_error(PYST_ERR_ARG, "group-by: too many pairs");
   const int64_t n1 = int64_t{kRadix} * kAggBlocks1, n2 = int64_t{kAggBuckets} * kAggBlocks2;
   const size_t counts = wide_count_bytes();
@@ -430,9 +431,11 @@ pyst_status pair_groupby_from(pyst_ctx *ctx, MoveArgs first, int64_t *keys, int6
              : k_move_scatter<false><<<kRadix * kAggBlocks2, kAggBlock, 0, stream>>>(m2, p2, keys, vals);
   PYST_LAUNCH_CHECK("k_move_scatter");
   const int gblocks = static_cast<int>(std::min<int64_t>(kAggBuckets, std::max(1, ctx_num_cus(ctx))));
-  k_bucket_groups<<<gblocks, kAggBlock, 0, stream>>>(keys, vals, p2, kAggBlocks2, out_keys, out_sums, out_cap,
-                                                     d_ngroups, ctx_err_word(ctx), first.plan);
-  PYST_LAUNCH_CHECK("k_bucket_groups");
+  if (hash_buckets) {
+    k_bucket_groups<<<gblocks, kAggBlock, 0, stream>>>(keys, vals, p2, kAggBlocks2, out_keys, out_sums, out_cap,
+                                                       d_ngroups, ctx_err_word(ctx), first.plan);
+    PYST_LAUNCH_CHECK("k_bucket_groups");
+  }
   if (first.plan) return launch_direct_groups<false>(ctx, first.plan, status, keys, vals, p2, kAggBlocks2, out_keys,
                                                      out_sums, out_cap, d_ngroups, stream);
   return PYST_OK;
@@ -815,7 +818,8 @@ static pyst_status launch_once(pyst_ctx *ctx, const NarrowArgs &a, void *ws, uin
 // *d_ngroups must be zero on entry.  Fewer than 2^31 rows.
 pyst_status narrow_groupby(pyst_ctx *ctx, const int32_t *kcol, const int32_t *vcol, const int32_t *sel,
                            const int64_t *count, int64_t cap, void *ws, int64_t *out_keys, int64_t *out_sums,
-                           int64_t out_cap, int64_t *d_ngroups, GbPlan *plan, uint64_t *status, hipStream_t stream) {
+                           int64_t out_cap, int64_t *d_ngroups, GbPlan *plan, uint64_t *status, bool hash_buckets,
+                           hipStream_t stream) {
   if (cap >= (int64_t{1} << 31)) return set_error(PYST_ERR_ARG, "group-by: too many rows");
   const int64_t n1 = int64_t{kRadix} * kNB1, n2 = int64_t{kAggBuckets} * kNB2;
   int32_t *counts = static_cast<int32_t *>(ws);
@@ -841,9 +845,11 @@ pyst_status narrow_groupby(pyst_ctx *ctx, const int32_t *kcol, const int32_t *vc
   k_narrow_move<false><<<kRadix * kNB2, kAggBlock, 0, stream>>>(a, tmp, p1, p2, pairs);
   PYST_LAUNCH_CHECK("k_narrow_move<2>");
   const int gblocks = static_cast<int>(std::min<int64_t>(kAggBuckets, std::max(1, ctx_num_cus(ctx))));
-  k_narrow_groups<<<gblocks, kAggBlock, 0, stream>>>(pairs, p2, out_keys, out_sums, out_cap, d_ngroups,
-                                                     ctx_err_word(ctx), plan);
-  PYST_LAUNCH_CHECK("k_narrow_groups");
+  if (hash_buckets) {
+    k_narrow_groups<<<gblocks, kAggBlock, 0, stream>>>(pairs, p2, out_keys, out_sums, out_cap, d_ngroups,
+                                                       ctx_err_word(ctx), plan);
+    PYST_LAUNCH_CHECK("k_narrow_groups");
+  }
   if (!plan) return PYST_OK;
   return launch_direct_groups<true>(ctx, plan, status, pairs, nullptr, p2, kNB2, out_keys, out_sums, out_cap, d_ngroups,
                                     stream);
@@ -858,7 +864,7 @@ pyst_status pair_groupby(pyst_ctx *ctx, int64_t *keys, int64_t *vals, const int6
   Scratch ws(ctx, wide_groupby_bytes(cap), stream);
   if (!ws.p) return set_error(PYST_ERR_NOMEM, "group-by: arena exhausted");
   return pair_groupby_from(ctx, first, keys, vals, count, cap, out_keys, out_sums, out_cap, d_ngroups, nullptr, ws.p,
-                           stream);
+                           true, stream);
 }
 
 // ---------------------------------------------------------------- planned group-by of columns
@@ -1094,12 +1100,16 @@ __global__ __launch_bounds__(kAggBlock) void k_gb_plan(GbPlan *plan, const int64
 // `copies` interleaved tables, so that a wave's 64 adds do not all meet in a
 // few words.  Bound by the read of the rows (12 bytes each for int32 keys and
 // int64 values).
-__global__ __launch_bounds__(kAggBlock, 8) void k_small_sums(const void *key, int key64, const void *val, int val64,
-                                                            const int32_t *sel, int64_t rows, const GbPlan *plan,
-                                                            uint64_t *psum, uint8_t *pflag) {
-  __shared__ uint64_t s_sum[kDirectSlots];
-  __shared__ uint8_t s_flag[kDirectSlots];
-  if (plan->mode != kGbSmall || plan->range == 0) return;
+struct SmallLds {
+  uint64_t sum[kDirectSlots];
+  uint8_t flag[kDirectSlots];
+};
+__device__ __forceinline__ void small_sums(SmallLds &lds, const void *key, int key64, const void *val, int val64,
+                                           const int32_t *sel, int64_t rows, const GbPlan *plan, uint64_t *psum,
+                                           uint8_t *pflag) {
+  uint64_t *s_sum = lds.sum;
+  uint8_t *s_flag = lds.flag;
+  if (plan->range == 0) return;
   constexpr int U = 8;
   const int tid = static_cast<int>(threadIdx.x);
   const uint32_t range = static_cast<uint32_t>(plan->range);
@@ -1147,17 +1157,32 @@ __global__ __launch_bounds__(kAggBlock, 8) void k_small_sums(const void *key, in
   }
 }
 
+// The rows of the modes that read them where they are: kGbSmall, and kGbFew into
+// its table.  (One kernel, and one for their groups: each launch that finds
+// nothing to do costs the other modes 3 us.)
+__global__ __launch_bounds__(kAggBlock, 8) void k_gb_in_place(const void *key, int key64, const void *val, int val64,
+                                                             const int32_t *sel, const int64_t *d_nsel, int64_t rows,
+                                                             GbPlan *plan, uint64_t *psum, uint8_t *pflag, GroupDev few,
+                                                             uint32_t *err) {
+  static_assert(kAggBlock == 1024, "blocks of the insertion");
+  __shared__ union {
+    SmallLds small;
+    PreLds pre;
+  } lds;
+  const int32_t mode = plan->mode;  // (does not change during the launch)
+  if (mode == kGbSmall) small_sums(lds.small, key, key64, val, val64, sel, rows, plan, psum, pflag);
+  else if (mode == kGbFew) gb_insert_rows(lds.pre, key, key64, val, val64, sel, d_nsel, rows, few, err, 0, plan, true);
+}
+
 // Adds up the blocks' partial arrays, 64 keys per block, and writes the groups
 // that occur in key order (look-back over the blocks).
-__global__ __launch_bounds__(kAggBlock) void k_small_groups(GbPlan *plan, const uint64_t *psum, const uint8_t *pflag,
-                                                           int nparts, uint64_t *status, int64_t *out_keys,
-                                                           int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups,
-                                                           uint32_t *err) {
+__device__ __forceinline__ void small_groups(GbPlan *plan, const uint64_t *psum, const uint8_t *pflag, int nparts,
+                                             uint64_t *status, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
+                                             int64_t *d_ngroups, uint32_t *err) {
   constexpr int NW = kAggBlock / kWave, U = 4;
   __shared__ uint64_t s_sum[NW][kWave];
   __shared__ uint32_t s_flag[NW][kWave];
   __shared__ int64_t s_tile;
-  if (plan->mode != kGbSmall) return;
   const int64_t range = static_cast<int64_t>(plan->range), ntiles = (range + kWave - 1) / kWave;
   if (threadIdx.x == 0) s_tile = static_cast<int64_t>(atomicAdd(&plan->ticket, 1ull));
   __syncthreads();
@@ -1203,6 +1228,21 @@ __global__ __launch_bounds__(kAggBlock) void k_small_groups(GbPlan *plan, const 
     }
   }
   if (lane == 0 && t == ntiles - 1) *d_ngroups = ex + agg;
+}
+
+// The groups of k_gb_in_place.
+constexpr int kFewTileItems = 2;
+constexpr int64_t kFewTiles = kFewSlots / (kAggBlock * kFewTileItems);
+__global__ __launch_bounds__(kAggBlock) void k_gb_in_place_groups(GbPlan *plan, const uint64_t *psum, const uint8_t *pflag,
+                                                                 int nparts, uint64_t *status, GroupDev few,
+                                                                 uint64_t *few_status, int64_t *out_keys, int64_t *out_sums,
+                                                                 int64_t out_cap, int64_t *d_ngroups, uint32_t *err) {
+  const int32_t mode = plan_mode(plan);
+  if (mode == kGbSmall)
+    small_groups(plan, psum, pflag, nparts, status, out_keys, out_sums, out_cap, d_ngroups, err);
+  else if (mode == kGbFew)
+    gb_compact_tile<kAggBlock, kFewTileItems>(few, out_keys, out_sums, out_cap, d_ngroups, few_status,
+                                              reinterpret_cast<unsigned long long *>(few_status + kFewTiles), kFewTiles, err);
 }
 
 // kGbRange: the pairs of each bucket summed in an LDS array indexed by the low
@@ -1646,7 +1686,7 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
     const int64_t *count = d_nsel;
     uint64_t *status = nullptr;
     pyst_status st;
-    const int64_t few_words = group_compact_words(kFewSlots);
+    constexpr int64_t few_words = kFewTiles + 1;
     if (ps.p) few.try_alloc(group_bytes(kFewSlots) + few_words * sizeof(uint64_t));
     if (ps.p) {
       plan = ps.as<GbPlan>();
@@ -1669,16 +1709,13 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
       PYST_LAUNCH_CHECK("k_gb_plan");
       uint64_t *psum = moves ? ws.as<uint64_t>() : table.as<uint64_t>();
       uint8_t *pflag = reinterpret_cast<uint8_t *>(psum + parts * small_max);
-      k_small_sums<<<parts, kAggBlock, 0, stream>>>(key->data, k64, val->data, v64, sel, n, plan, psum, pflag);
-      PYST_LAUNCH_CHECK("k_small_sums");
-      k_small_groups<<<static_cast<unsigned>(ceil_div(std::max<int64_t>(small_max, 1), kWave)), kAggBlock, 0,
-                       stream>>>(plan, psum, pflag, parts, status, out_keys, out_sums, out_cap, d_ngroups, err);
-      PYST_LAUNCH_CHECK("k_small_groups");
-      if (few.p) {
-        st = table_groupby(ctx, fg, key, val, sel, d_nsel, 0, 0.5, out_keys, out_sums, out_cap, d_ngroups, plan, kGbFew,
-                           few_status, stream);
-        if (st != PYST_OK) return st;
-      }
+      k_gb_in_place<<<parts, kAggBlock, 0, stream>>>(key->data, k64, val->data, v64, sel, d_nsel, n, plan, psum, pflag,
+                                                    fg, err);
+      PYST_LAUNCH_CHECK("k_gb_in_place");
+      const int64_t gblocks = std::max(ceil_div(small_max, kWave), few.p ? kFewTiles : 1);
+      k_gb_in_place_groups<<<static_cast<unsigned>(gblocks), kAggBlock, 0, stream>>>(
+          plan, psum, pflag, parts, status, fg, few_status, out_keys, out_sums, out_cap, d_ngroups, err);
+      PYST_LAUNCH_CHECK("k_gb_in_place_groups");
     } else if (hash_buckets) {  // no room for a plan: hash buckets for any keys
       if ((st = fill_u64(d_ngroups, 1, 0, stream)) != PYST_OK) return st;
       if (!count) {
@@ -1690,7 +1727,7 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
     if (hash_buckets || (plan && moves)) {
       if (narrow) {
         st = narrow_groupby(ctx, static_cast<const int32_t *>(key->data), static_cast<const int32_t *>(val->data), sel,
-                            count, n, ws.p, out_keys, out_sums, out_cap, d_ngroups, plan, status, stream);
+                            count, n, ws.p, out_keys, out_sums, out_cap, d_ngroups, plan, status, hash_buckets, stream);
       } else {
         MoveArgs first{};
         first.kcol = key->data;
@@ -1702,7 +1739,7 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
         first.plan = plan;
         int64_t *pk = ws.as<int64_t>();
         st = pair_groupby_from(ctx, first, pk, pk + n, count, n, out_keys, out_sums, out_cap, d_ngroups, status, ws2.p,
-                               stream);
+                               hash_buckets, stream);
       }
       if (st != PYST_OK) return st;
     }

@@ -1019,17 +1019,19 @@ __device__ __forceinline__ bool few_full(GbPlan *plan) {
 }
 constexpr int kPreSlots = 4096, kPreProbes = 8, kPreItems = 4;
 constexpr int64_t kFewProbes = 256;  // a kGbFew table without a place this near counts as full
-__global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key64, const void *val, int val64,
-                                                       const int32_t *sel, const int64_t *d_nsel, int64_t n, GroupDev g,
-                                                       uint32_t *err, int skip_empty, GbPlan *plan, int mode) {
-  // skip_empty: the input is a pair buffer whose unused slots hold the EMPTY key
+struct PreLds {
+  unsigned long long key[kPreSlots], sum[kPreSlots];
+  int32_t claimed;
+  bool stop, late;
+};
+// One block's part.  few: the table of kGbFew, which may run full; skip_empty: the
+// input is a pair buffer whose unused slots hold the EMPTY key.
+__device__ __forceinline__ void gb_insert_rows(PreLds &lds, const void *key, int key64, const void *val, int val64,
+                                               const int32_t *sel, const int64_t *d_nsel, int64_t n, const GroupDev &g,
+                                               uint32_t *err, int skip_empty, GbPlan *plan, bool few) {
   constexpr int U = kPreItems;
   constexpr unsigned long long kE = static_cast<unsigned long long>(kEmpty64);
-  __shared__ unsigned long long s_key[kPreSlots], s_sum[kPreSlots];
-  __shared__ int32_t s_claimed;
-  __shared__ bool s_stop, s_late;
-  // (of the same launch, other blocks may set few_failed: one thread reads it for the block)
-  if (plan && (mode == kGbFew ? plan->mode : plan_mode(plan)) != mode) return;
+  unsigned long long *s_key = lds.key, *s_sum = lds.sum;
   int64_t cnt = count_of(d_nsel, n);
   if (cnt > n) cnt = n;
   const int tid = static_cast<int>(threadIdx.x);
@@ -1037,7 +1039,6 @@ __global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key6
   const int64_t lo = per * blockIdx.x, hi = lo + per < cnt ? lo + per : cnt;
   if (lo >= hi) return;  // block-uniform
   const int64_t mask = g.hdr[0] - 1;
-  const bool few = plan && mode == kGbFew;
   const int64_t probes = few ? kFewProbes : mask + 1;
   int nslots = 2048;  // at least two slots a row where a block has few rows
   while (nslots < kPreSlots && nslots < 2 * per) nslots *= 2;
@@ -1046,11 +1047,11 @@ __global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key6
     s_sum[i] = 0;
   }
   if (tid == 0) {
-    s_claimed = 0;
-    s_late = few && few_full(plan);
+    lds.claimed = 0;
+    lds.late = few && few_full(plan);  // (other blocks may set it: one thread reads it for the block)
   }
   __syncthreads();
-  if (s_late) return;  // block-uniform: the rows will be grouped another way
+  if (lds.late) return;  // block-uniform: the rows will be grouped another way
   bool direct = false, full = false;
   for (int64_t t0 = lo; t0 < hi; t0 += 1024 * U) {  // block-uniform
     int64_t row[U], k[U], v[U];
@@ -1088,11 +1089,11 @@ __global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key6
     }
     if (!direct && t0 + 1024 * U < hi) {  // another tile follows
       claimed = wave_sum(claimed);
-      if (lane_id() == 0 && claimed) atomicAdd(&s_claimed, claimed);
-      if (tid == 0) s_stop = few && few_full(plan);
+      if (lane_id() == 0 && claimed) atomicAdd(&lds.claimed, claimed);
+      if (tid == 0) lds.stop = few && few_full(plan);
       __syncthreads();
-      direct = s_claimed > (t0 + 1024 * U - lo) / 2;
-      const bool stop = s_stop;
+      direct = lds.claimed > (t0 + 1024 * U - lo) / 2;
+      const bool stop = lds.stop;
       __syncthreads();
       if (stop) return;  // block-uniform
     } else if (few && (full || few_full(plan))) {
@@ -1114,19 +1115,27 @@ __global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key6
   }
 }
 
+__global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key64, const void *val, int val64,
+                                                       const int32_t *sel, const int64_t *d_nsel, int64_t n, GroupDev g,
+                                                       uint32_t *err, int skip_empty, GbPlan *plan, int mode) {
+  __shared__ PreLds lds;
+  if (plan && plan_mode(plan) != mode) return;
+  gb_insert_rows(lds, key, key64, val, val64, sel, d_nsel, n, g, err, skip_empty, plan, false);
+}
+
+// One tile of a table's slots, by ticket: its groups after those of the tiles before.
 template <int BLOCK, int ITEMS>
-__global__ __launch_bounds__(BLOCK) void k_gb_compact(GroupDev g, int64_t *out_keys, int64_t *out_sums,
-                                                     int64_t out_cap, int64_t *d_ngroups, uint64_t *status,
-                                                     unsigned long long *ticket, int64_t ntiles, uint32_t *err,
-                                                     const GbPlan *plan, int mode) {
+__device__ __forceinline__ void gb_compact_tile(const GroupDev &g, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
+                                                int64_t *d_ngroups, uint64_t *status, unsigned long long *ticket,
+                                                int64_t ntiles, uint32_t *err) {
   constexpr int NW = BLOCK / kWave;
   constexpr int64_t TILE = int64_t{BLOCK} * ITEMS;
-  if (plan && plan_mode(plan) != mode) return;
   __shared__ int64_t s_tile, s_prefix;
   __shared__ int32_t s_cnt[NW];
   if (threadIdx.x == 0) s_tile = static_cast<int64_t>(atomicAdd(ticket, 1ull));
   __syncthreads();
   const int64_t t = s_tile;
+  if (t >= ntiles) return;  // block-uniform
   const int64_t cap = g.hdr[0];
   const int w = threadIdx.x / kWave, lane = lane_id();
   const int64_t wbase = t * TILE + int64_t{w} * kWave * ITEMS;
@@ -1168,6 +1177,15 @@ __global__ __launch_bounds__(BLOCK) void k_gb_compact(GroupDev g, int64_t *out_k
     }
     pos += __popcll(m[j]);
   }
+}
+
+template <int BLOCK, int ITEMS>
+__global__ __launch_bounds__(BLOCK) void k_gb_compact(GroupDev g, int64_t *out_keys, int64_t *out_sums,
+                                                     int64_t out_cap, int64_t *d_ngroups, uint64_t *status,
+                                                     unsigned long long *ticket, int64_t ntiles, uint32_t *err,
+                                                     const GbPlan *plan, int mode) {
+  if (plan && plan_mode(plan) != mode) return;
+  gb_compact_tile<BLOCK, ITEMS>(g, out_keys, out_sums, out_cap, d_ngroups, status, ticket, ntiles, err);
 }
 
 constexpr int kCompactBlock = 256, kCompactItems = 8;
@@ -1233,13 +1251,10 @@ pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key,
                           int64_t *out_keys, int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, GbPlan *plan,
                           int mode, uint64_t *status, hipStream_t stream) {
   Scratch sc(ctx, stream);
-  pyst_status st = PYST_OK;
-  if (mode != kGbFew) {
-    const int64_t words = group_compact_words(g.cap_alloc);
-    if (!status && !sc.alloc(words * sizeof(uint64_t))) return set_error(PYST_ERR_NOMEM, "group compaction: arena exhausted");
-    if (!status) status = sc.as<uint64_t>();
-    st = launch_group_init(g, d_nsel, key->n, max_groups, max_load, plan, mode, status, words, stream);
-  }
+  const int64_t words = group_compact_words(g.cap_alloc);
+  if (!status && !sc.alloc(words * sizeof(uint64_t))) return set_error(PYST_ERR_NOMEM, "group compaction: arena exhausted");
+  if (!status) status = sc.as<uint64_t>();
+  pyst_status st = launch_group_init(g, d_nsel, key->n, max_groups, max_load, plan, mode, status, words, stream);
   if (st == PYST_OK) st = group_insert(ctx, g, key, val, sel, d_nsel, 0, plan, mode, stream);
   if (st != PYST_OK) return st;
   return launch_compact(ctx, g, status, out_keys, out_sums, out_cap, d_ngroups, plan, mode, stream);

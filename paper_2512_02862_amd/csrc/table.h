@@ -180,8 +180,7 @@ pyst_status group_insert(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, 
 pyst_status group_compact(pyst_ctx *ctx, const GroupDev &g, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
                           int64_t *d_ngroups, hipStream_t stream);
 // Group-by of columns through the table `g` in HBM (with a plan: only in `mode`).
-// status: group_compact_words of memory (null: taken from the arena).  In mode
-// kGbFew they are cleared, and the table empty, already.
+// status: group_compact_words of memory (null: taken from the arena).
 int64_t group_compact_words(int64_t cap_alloc);
 pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val,
                           const int32_t *sel, const int64_t *d_nsel, int64_t max_groups, double max_load,
