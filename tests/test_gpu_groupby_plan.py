@@ -291,3 +291,37 @@ def test_few_selected_rows_cost_what_few_rows_do(gpu, ctx):
     column = time_groupby(gpu, ctx, k[:1000].contiguous(), v[:1000].contiguous())
     ctx.check()
     assert few < 5 * column, (few, column)
+
+
+@pytest.mark.parametrize("kt", [np.int32, np.int64])
+@pytest.mark.parametrize("picked", [(1 << 19) - 1, 1 << 19, 700_001])
+@pytest.mark.parametrize("case", ["narrow", "outlier read first", "outlier between", "wide", "few and wide"])
+def test_large_selections_are_judged_by_some_of_their_keys(gpu, ctx, kt, picked, case):
+    # from 2^19 selected rows on, 256 of them (the first among them) may already span more than any range mode takes
+    rng = np.random.default_rng(picked)
+    n = (1 << 20) + 3
+    k = keys_over(rng, n, 60_000, -30_000, kt)
+    sel = np.sort(rng.choice(n, picked, replace=False)).astype(np.int32)
+    if case == "outlier read first":
+        k[sel[0]] = 2**31 - 1
+    elif case == "outlier between":
+        k[sel[1]] = 2**31 - 1
+    elif case == "wide":
+        k = keys_over(rng, n, 1 << 32, -2**31, kt)
+    elif case == "few and wide":
+        k = rng.choice(keys_over(rng, 9, 1 << 32, -2**31, kt), n)
+    check(gpu, ctx, k, rng.integers(-1000, 1000, n), sel)
+
+
+@pytest.mark.parametrize("at", [0, 1])
+@pytest.mark.parametrize("keys", [9, 1 << 40])
+def test_empty_key_of_a_large_selection(gpu, ctx, at, keys):
+    rng = np.random.default_rng(at)
+    n = 1 << 20
+    k = rng.choice(rng.integers(-2**62, 2**62, 9), n) if keys == 9 else rng.integers(0, keys, n)
+    sel = np.arange(0, n, 2, dtype=np.int32)
+    k[sel[at]] = np.iinfo(np.int64).min
+    gpu.groupby_sum(ctx, dev(k), dev(k), sel=dev(sel), nsel=dev(np.array([len(sel)], np.int64)))
+    with pytest.raises(gpu.PystError) as e:
+        ctx.check()
+    assert e.value.status == gpu.ERR_KEY
