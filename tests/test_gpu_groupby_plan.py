@@ -325,3 +325,12 @@ def test_empty_key_of_a_large_selection(gpu, ctx, at, keys):
     with pytest.raises(gpu.PystError) as e:
         ctx.check()
     assert e.value.status == gpu.ERR_KEY
+
+
+@pytest.mark.parametrize("picked", [0, 1, 1000, 1023, 1024, 2047, 2048, 20_001, 300_000])
+def test_tables_that_use_a_part_of_their_slots(gpu, ctx, picked):
+    # the compaction's tiles (2048 slots) end with the slots in use: 64 at least, twice the selected rows
+    rng = np.random.default_rng(picked)
+    n = 300_000
+    k = rng.integers(-2**62, 2**62, n)
+    check(gpu, ctx, k, rng.integers(-9, 9, n), np.sort(rng.choice(n, picked, replace=False)).astype(np.int32))
