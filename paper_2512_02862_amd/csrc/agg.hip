@@ -1768,7 +1768,7 @@ pyst_status planned_groupby(pyst_ctx *ctx, const pyst_col *key, const pyst_col *
     PYST_LAUNCH_CHECK("k_gb_sort_count");
     sort_count = &plan->sort_count;
   }
-  return sort_pairs_by_key(ctx, out_keys, out_sums, sort_count, out_cap, k64 ? 64 : 32, stream);
+  return sort_pairs_by_key(ctx, out_keys, out_sums, sort_count, bound, k64 ? 64 : 32, stream);
 }
 
 }  // namespace pyst

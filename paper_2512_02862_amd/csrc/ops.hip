@@ -1869,7 +1869,7 @@ pyst_status pyst_groupby_sum(pyst_ctx *ctx, const pyst_col *key, const pyst_col 
                                    out_keys, out_sums, out_cap, d_ngroups, nullptr, kGbTable, nullptr, stream);
     if (st != PYST_OK || !sort_by_key) return st;
   }
-  return sort_pairs_by_key(ctx, out_keys, out_sums, d_ngroups, out_cap, key->dtype == PYST_I64 ? 64 : 32, stream);
+  return sort_pairs_by_key(ctx, out_keys, out_sums, d_ngroups, bound, key->dtype == PYST_I64 ? 64 : 32, stream);
 }
 
 }  // extern "C"

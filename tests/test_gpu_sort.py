@@ -74,3 +74,18 @@ def test_few_groups_in_a_large_output(gpu, ctx):
     for groups in (3, 20_000):
         k = rng.integers(0, groups, 700_000) * (1 << 33) - (1 << 60)
         check(gpu, ctx, k, rng.integers(-2**62, 2**62, len(k)))
+
+
+@pytest.mark.parametrize("n,max_groups", [(50, 10_000), (50, 3_000_000), (9_000, 20_000)])
+def test_output_larger_than_the_rows(gpu, n, max_groups):
+    # the arena holds what a sort of eight byte passes over max_groups pairs takes beside the table:
+    # the pairs again, and 256 counts and their sums per 4096 of them
+    rng = np.random.default_rng(n)
+    slots = 1 << (2 * n).bit_length()
+    table = 1024 + 16 * slots
+    tiles = (max_groups + TILE - 1) // TILE
+    counts = (2 * tiles * 256 * 4 + 256 + 255) // 256 * 256 + 8 * (tiles * 256 // 2048 + 2)
+    c = gpu.Ctx(0, sum((b + 255) // 256 * 256 for b in (table, 16 * max_groups, counts)))
+    k = rng.permutation(distinct(rng, n, 40, np.int64))
+    check(gpu, c, k, rng.integers(-9, 9, len(k)), max_groups=max_groups)
+    c.close()
