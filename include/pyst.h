@@ -470,7 +470,8 @@ typedef struct pyst_fragment {
               (at least 4 * block rows per unit), i.e. how finely large
               fragments spread over the chip next to small ones; with block
               1024 a fragment so large that a unit would hold more than half of
-              a compute unit's share of the batch is split into more units;
+              a compute unit's share of the batch is split into more units,
+              except in a captured graph, which holds its units' memory;
    block    : threads per block of the fact pass (256, 512 or 1024);
    max_load : hash-table load bound of every fragment (0: the plan's). */
 typedef struct pyst_tuning {

@@ -387,9 +387,12 @@ static bool batch_shape(const pyst_fragment &fg, QueryShape *q, FastArgs *fa) {
 // 10k to 20M rows at fanout 16 (a share is 658k rows, the largest units 1.25M):
 // fact pass 1354 -> 823 us, 819 with quarters of a share, 847 with whole shares;
 // 90 fragments of 15k to 5.3M rows 388 -> 389 us (quarters 400: each unit copies
-// its filter, 128 KiB, and leaves a chunk per bucket partly filled).  Without
-// staging several blocks share a CU and the pass is bound by its atomics: smaller
-// units measured 402 -> 411 us there, so those keep the fanout.
+// its filter, 128 KiB, and leaves a chunk per bucket partly filled).  More units
+// take larger pools (their first chunks), which a batch gives back when it has run
+// but a captured graph holds: graphs keep the fanout, so that as many fit an arena
+// as their fanouts ask for.  Without staging several blocks share a CU and the pass
+// is bound by its atomics: smaller units measured 402 -> 411 us there, so those keep
+// the fanout too.
 constexpr int64_t kUnitsPerShare = 2;
 constexpr int64_t kUnitRowsMin = 16384;
 
@@ -499,9 +502,9 @@ struct BatchRun {
 // Lays the fragments out, allocates their device memory and uploads the
 // descriptors on `stream`.
 static pyst_status batch_prepare(pyst_ctx *ctx, const pyst_fragment *fr, int nfrag, const pyst_tuning &tu,
-                                 hipStream_t stream, BatchRun *run) {
+                                 bool split_large, hipStream_t stream, BatchRun *run) {
   BatchPlan bp;
-  pyst_status st = batch_layout(ctx, fr, nfrag, tu, true, true, &bp);
+  pyst_status st = batch_layout(ctx, fr, nfrag, tu, true, split_large, &bp);
   if (st != PYST_OK) return st;
   const bool v64 = bp.frags[0].fa.v0_64 != 0;
   for (int f = 1; f < nfrag; ++f)
@@ -512,7 +515,7 @@ static pyst_status batch_prepare(pyst_ctx *ctx, const pyst_fragment *fr, int nfr
   const size_t meta = (desc_bytes + 255) / 256 * 256 + (pre_bytes + 255) / 256 * 256;
   char *mem = static_cast<char *>(
       ctx_alloc(ctx, meta + bp.table_bytes_total + bp.sel_bytes_total + bp.pool_bytes_total, stream));
-  if (!mem && bp.staged) {  // no room for the pair pools: fewer units have smaller ones
+  if (!mem && bp.staged && split_large) {  // no room for the pair pools: fewer units have smaller ones
     bp = BatchPlan();
     if ((st = batch_layout(ctx, fr, nfrag, tu, true, false, &bp)) != PYST_OK) return st;
     mem = static_cast<char *>(
@@ -520,7 +523,7 @@ static pyst_status batch_prepare(pyst_ctx *ctx, const pyst_fragment *fr, int nfr
   }
   if (!mem && bp.staged) {  // per-row atomics instead
     bp = BatchPlan();
-    if ((st = batch_layout(ctx, fr, nfrag, tu, false, true, &bp)) != PYST_OK) return st;
+    if ((st = batch_layout(ctx, fr, nfrag, tu, false, false, &bp)) != PYST_OK) return st;
     mem = static_cast<char *>(ctx_alloc(ctx, meta + bp.table_bytes_total + bp.sel_bytes_total, stream));
   }
   if (!mem) return set_error(PYST_ERR_NOMEM, "pyst_query_batch: arena cannot hold the batch");
@@ -608,7 +611,7 @@ static hipError_t batch_enqueue(const BatchRun &r, uint32_t *err, hipStream_t st
 static pyst_status batch_run(pyst_ctx *ctx, const pyst_fragment *fr, int nfrag, const pyst_tuning &tu,
                              hipStream_t stream) {
   BatchRun r;
-  pyst_status st = batch_prepare(ctx, fr, nfrag, tu, stream, &r);
+  pyst_status st = batch_prepare(ctx, fr, nfrag, tu, true, stream, &r);
   if (st != PYST_OK) return st;
   hipError_t e;
   {
@@ -670,7 +673,7 @@ pyst_status pyst_batch_graph_create(pyst_ctx *ctx, const pyst_fragment *frags, i
   pyst_status st = check_fragments(frags, nfrag, "pyst_batch_graph_create: bad fragment");
   if (st != PYST_OK) return st;
   BatchRun r;
-  st = batch_prepare(ctx, frags, nfrag, tu, stream, &r);
+  st = batch_prepare(ctx, frags, nfrag, tu, false, stream, &r);
   if (st != PYST_OK) return st;
   auto fail = [&](hipError_t e, const char *what, hipStream_t cs, hipGraph_t g) {
     if (g) (void)hipGraphDestroy(g);

@@ -249,3 +249,46 @@ def test_batch_splits_large_units(gpu, spec, budget):
         np.testing.assert_array_equal(gk, wk)
         np.testing.assert_array_equal(gs, ws)
     c.close()
+
+
+def test_batch_graph_holds_what_its_fanout_asks_for(gpu):
+    # beside what a batch without staging takes (block 512): one pool of pair chunks per fragment, with
+    # one first chunk per unit and bucket; the second of two graphs has the room the first leaves
+    spec = [(2_500_001, 200_000), (1_000_003, 100_000)]
+    frags, host = [], []
+    for f, (p, b) in enumerate(spec):
+        bt, pt = gen.star_tables(b, p, workload=3, fragment=700 + f)
+        frags.append((gpu.star_plan({k: dev(v) for k, v in bt.items()}), [dev(pt[x]) for x in ("fk", "date", "price")]))
+        host.append((bt, pt))
+    c = gpu.Ctx(0, 1 << 30)
+    batch = gpu.Batch(c, frags)
+    g = batch.graph((2, 512, 0.5))
+    plain = c.used
+    g.close()
+    pools = 0
+    for p, b in spec:
+        buckets = max(1, (1 << (2 * b).bit_length()) >> 13)
+        chunks = 2 * buckets + ((p + 7) // 8 + 127) // 128 + 1
+        pools += 2048 + (chunks * (8 * 128 + 4) + 255) // 256 * 256
+    g = batch.graph((2, 1024, 0.5))
+    one = c.used
+    assert one <= plain + pools + 1024
+    g.close()
+    c.close()
+    c = gpu.Ctx(0, plain + pools + 1024 + plain + 1024)  # a staged graph and one without staging
+    batch = gpu.Batch(c, frags)
+    graphs = [batch.graph((2, 1024, 0.5)) for _ in range(2)]
+    for g in graphs:
+        for ok, osum, ng in batch.outs:
+            ok.fill_(-7)
+            osum.fill_(-7)
+        g.launch()
+        c.check()
+        for (k, s), (bt, pt) in zip(batch.results(), host):
+            wk, ws = oracle.star_query(bt, pt)
+            gk, gs = sorted_np(k, s)
+            np.testing.assert_array_equal(gk, wk)
+            np.testing.assert_array_equal(gs, ws)
+    for g in graphs:
+        g.close()
+    c.close()
