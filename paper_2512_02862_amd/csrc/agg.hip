@@ -1253,7 +1253,7 @@ __global__ __launch_bounds__(kAggBlock) void k_gb_in_place_groups(GbPlan *plan, 
     small_groups(plan, psum, pflag, nparts, status, out_keys, out_sums, out_cap, d_ngroups, err);
   else if (mode == kGbFew)
     gb_compact_tile<kAggBlock, kFewTileItems>(few, out_keys, out_sums, out_cap, d_ngroups, few_status,
-                                              reinterpret_cast<unsigned long long *>(few_status + kFewTiles), err);
+                                              reinterpret_cast<unsigned long long *>(few_status + kFewTiles), kFewTiles, err);
 }
 
 // kGbRange: the pairs of each bucket summed in an LDS array indexed by the low

@@ -1017,7 +1017,7 @@ __global__ void k_gb_init(GroupDev g, const int64_t *d_nsel, int64_t n, int64_t 
 __device__ __forceinline__ bool few_full(GbPlan *plan) {
   return __hip_atomic_load(&plan->few_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }
-constexpr int kPreSlots = 4096, kPreProbes = 8, kPreItems = 4;
+constexpr int kPreSlots = 4096, kPreProbes = 8, kPreItems = 4, kPreUnitLg = 7, kPreUnit = 1 << kPreUnitLg;
 constexpr int64_t kFewProbes = 256;  // a kGbFew table without a place this near counts as full
 struct PreLds {
   unsigned long long key[kPreSlots], sum[kPreSlots];
@@ -1035,12 +1035,14 @@ __device__ __forceinline__ void gb_insert_rows(PreLds &lds, const void *key, int
   int64_t cnt = count_of(d_nsel, n);
   if (cnt > n) cnt = n;
   const int tid = static_cast<int>(threadIdx.x);
-  const int64_t tiles = (cnt + 1023) / 1024, per = (tiles + gridDim.x - 1) / gridDim.x * 1024;
+  const int lg = cnt < int64_t{1024} * gridDim.x ? kPreUnitLg : 10;  // a block's rows are whole units of 1 << lg
+  const uint32_t units = static_cast<uint32_t>((cnt + (1 << lg) - 1) >> lg);
+  const int64_t per = static_cast<int64_t>((units + gridDim.x - 1) / gridDim.x) << lg;
   const int64_t lo = per * blockIdx.x, hi = lo + per < cnt ? lo + per : cnt;
   if (lo >= hi) return;  // block-uniform
   const int64_t mask = g.hdr[0] - 1;
   const int64_t probes = few ? kFewProbes : mask + 1;
-  int nslots = 2048;  // at least two slots a row where a block has few rows
+  int nslots = 2 * kPreUnit;  // at least two slots a row where a block has few rows
   while (nslots < kPreSlots && nslots < 2 * per) nslots *= 2;
   for (int i = tid; i < nslots; i += 1024) {
     s_key[i] = kE;
@@ -1123,18 +1125,20 @@ __global__ __launch_bounds__(1024, 8) void k_gb_insert(const void *key, int key6
   gb_insert_rows(lds, key, key64, val, val64, sel, d_nsel, n, g, err, skip_empty, plan, false);
 }
 
-// One tile of the slots in use, by ticket: its groups after those of the tiles
-// before.  The grid has a block for every tile of the memory; those past the slots
-// in use take no ticket (a table for 20M groups that holds 40000: 412 us of tickets).
+// One tile of a table's slots, by ticket: its groups after those of the tiles before.
+// ntiles 0: the grid has a block for every tile of the memory, and those past the
+// slots in use take no ticket (a table for 20M groups that holds 40000: 412 us of
+// tickets); the header is waited for first (1M rows, all slots in use: 4 us).
 template <int BLOCK, int ITEMS>
 __device__ __forceinline__ void gb_compact_tile(const GroupDev &g, int64_t *out_keys, int64_t *out_sums, int64_t out_cap,
                                                 int64_t *d_ngroups, uint64_t *status, unsigned long long *ticket,
-                                                uint32_t *err) {
+                                                int64_t ntiles, uint32_t *err) {
   constexpr int NW = BLOCK / kWave;
   constexpr int64_t TILE = int64_t{BLOCK} * ITEMS;
   __shared__ int64_t s_tile, s_prefix;
   __shared__ int32_t s_cnt[NW];
-  const int64_t cap = g.hdr[0], ntiles = (cap + TILE - 1) / TILE;
+  const int64_t cap = g.hdr[0];
+  if (ntiles == 0) ntiles = (cap + TILE - 1) / TILE;
   if (blockIdx.x >= ntiles) return;
   if (threadIdx.x == 0) s_tile = static_cast<int64_t>(atomicAdd(ticket, 1ull));
   __syncthreads();
@@ -1184,10 +1188,10 @@ __device__ __forceinline__ void gb_compact_tile(const GroupDev &g, int64_t *out_
 template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void k_gb_compact(GroupDev g, int64_t *out_keys, int64_t *out_sums,
                                                      int64_t out_cap, int64_t *d_ngroups, uint64_t *status,
-                                                     unsigned long long *ticket, uint32_t *err, const GbPlan *plan,
-                                                     int mode) {
+                                                     unsigned long long *ticket, int64_t ntiles, uint32_t *err,
+                                                     const GbPlan *plan, int mode) {
   if (plan && plan_mode(plan) != mode) return;
-  gb_compact_tile<BLOCK, ITEMS>(g, out_keys, out_sums, out_cap, d_ngroups, status, ticket, err);
+  gb_compact_tile<BLOCK, ITEMS>(g, out_keys, out_sums, out_cap, d_ngroups, status, ticket, ntiles, err);
 }
 
 constexpr int kCompactBlock = 256, kCompactItems = 8;
@@ -1195,14 +1199,14 @@ static int64_t compact_tiles(const GroupDev &g) {
   return std::max<int64_t>(1, ceil_div(g.cap_alloc, int64_t{kCompactBlock} * kCompactItems));
 }
 
-// status: compact_tiles + 1 cleared words.
+// status: compact_tiles + 1 cleared words.  whole: every slot of the memory is in use.
 static pyst_status launch_compact(pyst_ctx *ctx, const GroupDev &g, uint64_t *status, int64_t *out_keys,
-                                  int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, const GbPlan *plan, int mode,
-                                  hipStream_t stream) {
+                                  int64_t *out_sums, int64_t out_cap, int64_t *d_ngroups, bool whole,
+                                  const GbPlan *plan, int mode, hipStream_t stream) {
   const int64_t ntiles = compact_tiles(g);
   k_gb_compact<kCompactBlock, kCompactItems><<<static_cast<unsigned>(ntiles), kCompactBlock, 0, stream>>>(
       g, out_keys, out_sums, out_cap, d_ngroups, status, reinterpret_cast<unsigned long long *>(status + ntiles),
-      ctx_err_word(ctx), plan, mode);
+      whole ? ntiles : 0, ctx_err_word(ctx), plan, mode);
   PYST_LAUNCH_CHECK("k_gb_compact");
   return PYST_OK;
 }
@@ -1214,7 +1218,7 @@ pyst_status group_compact(pyst_ctx *ctx, const GroupDev &g, int64_t *out_keys, i
   if (!sc.p) return set_error(PYST_ERR_NOMEM, "group compaction: arena exhausted");
   pyst_status st = fill_u64(sc.p, ntiles + 1, 0, stream);
   if (st != PYST_OK) return st;
-  return launch_compact(ctx, g, sc.as<uint64_t>(), out_keys, out_sums, out_cap, d_ngroups, nullptr, 0, stream);
+  return launch_compact(ctx, g, sc.as<uint64_t>(), out_keys, out_sums, out_cap, d_ngroups, false, nullptr, 0, stream);
 }
 
 static pyst_status launch_group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int64_t max_groups,
@@ -1231,11 +1235,15 @@ pyst_status group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int6
   return launch_group_init(g, d_nsel, n, max_groups, max_load, nullptr, 0, nullptr, 0, stream);
 }
 
-// Up to two blocks of 1024 threads per CU, at least a row a thread.
+// Up to two blocks of 1024 threads per CU, a row a thread or more; few rows take
+// more blocks, up to half as many as CUs, down to 128 rows each: what a block's
+// groups cost is its CU's requests to the table, a few ns each (3000 different
+// keys: in 3 blocks 21 us, in 24 13.6; 30000: 24 in 30, 17 in 128).
 pyst_status group_insert(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val, const int32_t *sel,
                          const int64_t *d_nsel, int skip_empty, GbPlan *plan, int mode, hipStream_t stream) {
   if (key->n == 0) return PYST_OK;
-  const int blocks = grid_for(ctx, key->n, 1024, 2);
+  const int64_t few = std::min<int64_t>(ceil_div(key->n, kPreUnit), std::max(1, ctx_num_cus(ctx) / 2));
+  const int blocks = static_cast<int>(std::max<int64_t>(grid_for(ctx, key->n, 1024, 2), few));
   k_gb_insert<<<blocks, 1024, 0, stream>>>(key->data, key->dtype == PYST_I64, val->data, val->dtype == PYST_I64, sel,
                                           d_nsel, key->n, g, ctx_err_word(ctx), skip_empty, plan, mode);
   PYST_LAUNCH_CHECK("k_gb_insert");
@@ -1259,7 +1267,7 @@ pyst_status table_groupby(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key,
   pyst_status st = launch_group_init(g, d_nsel, key->n, max_groups, max_load, plan, mode, status, words, stream);
   if (st == PYST_OK) st = group_insert(ctx, g, key, val, sel, d_nsel, 0, plan, mode, stream);
   if (st != PYST_OK) return st;
-  return launch_compact(ctx, g, status, out_keys, out_sums, out_cap, d_ngroups, plan, mode, stream);
+  return launch_compact(ctx, g, status, out_keys, out_sums, out_cap, d_ngroups, d_nsel == nullptr, plan, mode, stream);
 }
 
 // ============================================================== gather (materialize)

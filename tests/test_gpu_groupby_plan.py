@@ -334,3 +334,14 @@ def test_tables_that_use_a_part_of_their_slots(gpu, ctx, picked):
     n = 300_000
     k = rng.integers(-2**62, 2**62, n)
     check(gpu, ctx, k, rng.integers(-9, 9, n), np.sort(rng.choice(n, picked, replace=False)).astype(np.int32))
+
+
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 1023, 1025, 16_383, 16_384, 16_385, 131_071, 131_073, 262_143, 524_289])
+@pytest.mark.parametrize("groups", [1, 1 << 40])
+def test_blocks_of_few_rows(gpu, ctx, n, groups):
+    # units of 128 rows while a block has fewer than 1024, units of 1024 from there
+    rng = np.random.default_rng(n)
+    k = rng.integers(0, groups, n)
+    check(gpu, ctx, k, rng.integers(-2**62, 2**62, n))
+    sel = np.sort(rng.choice(n, n // 3 + 1, replace=False)).astype(np.int32)
+    check(gpu, ctx, k, rng.integers(-2**62, 2**62, n), sel)
