@@ -84,3 +84,11 @@ def test_partition_one_hot_destination_and_payload_counts(gpu, ctx, npay):
     key = np.where(rng.random(n) < 0.95, 42, rng.integers(0, 1000, n)).astype(np.int32)
     pays = [rng.integers(-2**31, 2**31, n).astype(np.int32 if j % 3 else np.int64) for j in range(npay)]
     check_partition(gpu, ctx, key, pays, 128, None)
+
+
+@pytest.mark.parametrize("n", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1, (1 << 18) + 63, (1 << 18) + 8191, (1 << 18) + 8192,
+                               (1 << 18) + 8193, 300_001])
+@pytest.mark.parametrize("bound", [-1, 500, 1000])
+def test_filter_where_two_kernels_take_over(gpu, ctx, n, bound):
+    rng = np.random.default_rng(n)
+    check_filter(gpu, ctx, [rng.integers(0, 1000, n).astype(np.int32)], [(0, "<", bound)])
