@@ -1475,25 +1475,30 @@ pyst_status sliced_probe(pyst_ctx *ctx, const TableDev &t, const pyst_col *key, 
 // and 15M probe rows, narrow: 343 us with four, 370 with two, 476 with one; lookup of 20M 64-bit ids, wide:
 // 786, 680, 819)
 constexpr int kProbeBlock = 1024, kProbeNarrow = 4, kProbeWide = 2;
-static int64_t join_probe_tiles(const TableDev &t, int64_t n) {
-  return std::max<int64_t>(1, ceil_div(n, int64_t{kProbeBlock} * (t.slot_bytes == 16 ? kProbeWide : kProbeNarrow)));
-}
+static int64_t join_probe_tiles(int64_t n, int rows) { return std::max<int64_t>(1, ceil_div(n, int64_t{kProbeBlock} * rows)); }
+static int join_probe_rows(const TableDev &t) { return t.slot_bytes == 16 ? kProbeWide : kProbeNarrow; }
 // Look-back words and ticket of a probe of n rows.
-static size_t join_probe_bytes(const TableDev &t, int64_t n) {
-  return static_cast<size_t>(join_probe_tiles(t, n) + 1) * sizeof(uint64_t);
+static size_t join_probe_bytes(int64_t n, int rows) { return static_cast<size_t>(join_probe_tiles(n, rows) + 1) * sizeof(uint64_t); }
+// One row a lane where the runs are walked to their end (duplicate keys) in a wide table beyond the L2 and
+// the rows are few: 1.5M rows, 900k different keys 92 us with two, 76 with one, 300k keys three times each
+// 247 and 225; 20M rows, 3M keys 880 and 802, 1M three times each 1975 and 2195.
+constexpr int64_t kProbeLongWalks = int64_t{1} << 22;
+static bool join_probe_one_row(const TableDev &t, int unique, int64_t n) {
+  return !unique && t.slot_bytes == 16 && t.cap_alloc >= (int64_t{1} << 20) && n < kProbeLongWalks;
 }
 
-// words: join_probe_bytes of memory (null: taken from the arena where they are needed).
+// words: nwords bytes of memory, at least join_probe_bytes of join_probe_rows (null: taken from the arena
+// where they are needed).
 template <typename PayT>
 pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, const pyst_col *key, const int32_t *sel,
                               const int64_t *d_nsel, int32_t *out_row, PayT *out_pay, int64_t out_cap,
                               int64_t *d_nout, hipStream_t stream, const JoinPlan *plan = nullptr,
-                              uint64_t *words = nullptr) {
+                              uint64_t *words = nullptr, size_t nwords = 0) {
   Scratch ws(ctx, stream);
   ProbeRule rule;
   if (sliced_probe_wanted(t, unique, key)) {  // a table beyond the L2, many probes: by slices, where there is room
     // (where only the device knows the table's size, both ways are enqueued and one returns at once)
-    const size_t lead = t.selected ? (join_probe_bytes(t, key->n) + 255) / 256 * 256 : 0;
+    const size_t lead = t.selected ? (join_probe_bytes(key->n, join_probe_rows(t)) + 255) / 256 * 256 : 0;
     if (ws.try_alloc(lead + sliced_probe_bytes(t, key))) {
       if (t.selected) rule = sliced_probe_rule(t, key, d_nsel);
       const pyst_status st = sliced_probe(ctx, t, key, sel, d_nsel, ws.p, lead, out_row, out_pay, out_cap, d_nout, plan,
@@ -1503,11 +1508,17 @@ pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, cons
   }
   constexpr int BLOCK = kProbeBlock, NARROW = kProbeNarrow, WIDE = kProbeWide;
   const bool wide = t.slot_bytes == 16, k64 = key->dtype == PYST_I64;
-  const int64_t ntiles = join_probe_tiles(t, key->n);
+  int rows = join_probe_rows(t);
   Scratch sc(ctx, stream);
+  if (!ws.p && join_probe_one_row(t, unique, key->n)) {  // (twice the words: where there is room)
+    const size_t bytes = join_probe_bytes(key->n, 1);
+    if (words ? bytes <= nwords : sc.try_alloc(bytes) != nullptr) rows = 1;
+  }
+  const int64_t ntiles = join_probe_tiles(key->n, rows);
   uint64_t *status = ws.as<uint64_t>();
   if (!status) {
-    if (!words && !sc.alloc(join_probe_bytes(t, key->n))) return set_error(PYST_ERR_NOMEM, "join probe: arena exhausted");
+    if (!words && !sc.p && !sc.alloc(join_probe_bytes(key->n, rows)))
+      return set_error(PYST_ERR_NOMEM, "join probe: arena exhausted");
     status = words ? words : sc.as<uint64_t>();
     const pyst_status st = fill_u64(status, ntiles + 1, 0, stream);
     if (st != PYST_OK) return st;
@@ -1515,7 +1526,15 @@ pyst_status launch_join_probe(pyst_ctx *ctx, const TableDev &t, int unique, cons
   auto *ticket = reinterpret_cast<unsigned long long *>(status + ntiles);
   const unsigned grid = static_cast<unsigned>(ntiles);
   uint32_t *err = ctx_err_word(ctx);
-  if (wide && k64)
+  if (rows == 1 && k64)
+    k_join_probe<BLOCK, 1, true, true, PayT><<<grid, BLOCK, 0, stream>>>(
+        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
+        plan, rule);
+  else if (rows == 1)
+    k_join_probe<BLOCK, 1, true, false, PayT><<<grid, BLOCK, 0, stream>>>(
+        key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
+        plan, rule);
+  else if (wide && k64)
     k_join_probe<BLOCK, WIDE, true, true, PayT><<<grid, BLOCK, 0, stream>>>(
         key->data, sel, d_nsel, key->n, t, unique, out_row, out_pay, out_cap, d_nout, status, ticket, ntiles, err,
         plan, rule);
@@ -1807,7 +1826,8 @@ pyst_status pyst_join_materialize(pyst_ctx *ctx, const pyst_col *build_key, cons
   // words, then in their place the packed build rows (several build columns: one random read of a
   // packed row per match instead of one per column).
   const size_t row_bytes = nbcols > 1 ? static_cast<size_t>(build_key->n) * row_words(nbcols) * sizeof(int64_t) : 0;
-  Scratch rest(ctx, std::max(join_probe_bytes(t, probe_key->n), row_bytes), stream);
+  const size_t rest_bytes = std::max(join_probe_bytes(probe_key->n, join_probe_rows(t)), row_bytes);
+  Scratch rest(ctx, rest_bytes, stream);
   if (!rest.p) return set_error(PYST_ERR_NOMEM, "pyst_join_materialize: arena exhausted");
   // large sides with unique build keys: an array over dense keys where the arena has room for the
   // moves beside the table's memory (which holds the array), decided on the device
@@ -1830,7 +1850,7 @@ pyst_status pyst_join_materialize(pyst_ctx *ctx, const pyst_col *build_key, cons
       st = direct_join_probe(ctx, build_key->n, probe_key, ws.p, array, out_probe_row, out_build_row, out_cap, d_nout, stream);
     if (st == PYST_OK)
       st = launch_join_probe(ctx, t, unique_keys != 0, probe_key, nullptr, nullptr, out_probe_row, out_build_row, out_cap,
-                             d_nout, stream, plan, rest.as<uint64_t>());
+                             d_nout, stream, plan, rest.as<uint64_t>(), rest_bytes);
   }
   if (st != PYST_OK) return st;
   if (npcols > 0 && (st = launch_gather(ctx, ga[0], out_probe_row, d_nout, out_cap, stream)) != PYST_OK) return st;

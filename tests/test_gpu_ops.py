@@ -386,3 +386,34 @@ def test_query_is_deterministic(gpu, ctx):
     k2, s2 = _sorted_pair(r2[0], r2[1], m)
     np.testing.assert_array_equal(k1, k2)
     np.testing.assert_array_equal(s1, s2)
+
+
+@pytest.mark.parametrize("room", [True, False])
+@pytest.mark.parametrize("pt", [np.int32, np.int64])
+@pytest.mark.parametrize("npr", [1, 1023, 1024, 1025, 2049, 300_001])
+def test_probe_of_duplicate_wide_keys_beyond_the_l2(gpu, npr, pt, room):
+    # a table of 16-byte slots with 2^20 slots or more takes one row a lane, two where the arena is short of its words
+    rng = np.random.default_rng(npr)
+    nb = 600_000
+    bk = rng.integers(0, 250_000, nb)
+    pay = rng.integers(-2**62, 2**62, nb)
+    pk = rng.integers(0, 300_000, npr).astype(pt)
+    words = 256 * -(-8 * (-(-npr // 2048) + 1) // 256)  # two rows a lane
+    c = gpu.Ctx(0, 64 << 20 if room else 1024 + (16 << 21) + words)
+    t = gpu.join_build(c, dev(bk), dev(pay), unique_keys=False)
+    assert t.info()[0] == 1 << 21
+    rows, vals, ng = gpu.join_probe(c, t, dev(pk), out_cap=12 * npr + 100)
+    c.check()
+    m = int(ng.item())
+    order = np.argsort(bk, kind="stable")
+    lo, hi = np.searchsorted(bk[order], pk, "left"), np.searchsorted(bk[order], pk, "right")
+    assert m == int((hi - lo).sum())
+    np.testing.assert_array_equal(rows[:m].cpu().numpy(), np.repeat(np.arange(npr), hi - lo))
+    got = vals[:m].cpu().numpy()
+    at = np.concatenate([[0], np.cumsum(hi - lo)])
+    want = np.concatenate([np.sort(pay[order[a:b]]) for a, b in zip(lo, hi)] or [np.zeros(0, np.int64)])
+    seg = np.repeat(np.arange(npr), hi - lo)
+    np.testing.assert_array_equal(got[np.lexsort((got, seg))], want)
+    assert at[-1] == m
+    t.destroy()
+    c.close()
