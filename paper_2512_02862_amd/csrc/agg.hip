@@ -63,9 +63,9 @@ __device__ __forceinline__ uint64_t agg_hash(int64_t key) { return fmix64(static
 //   kGbTable  the same where hash buckets have no memory or too many groups: the
 //             table in HBM (k_gb_insert).
 // Measured at 60M rows, start to end, ordered by key: 2407 int32 keys with int64
-// values 1953 -> 218 us (kGbSmall: 135 us for the sums, 5.3 TB/s; hash buckets
+// values 1953 -> 216 us (kGbSmall: 135 us for the sums, 5.3 TB/s; hash buckets
 // left 2407 busy blocks of uneven size), 15M int32 keys with int32 values 2232
-// -> 590 us (kGbOnce; 840 with the two moves of kGbRange, whose bucket sums take
+// -> 580 us (kGbOnce; 840 with the two moves of kGbRange, whose bucket sums take
 // 193 us against 376 with hash tables; nothing is left to sort).  The range costs
 // 49 - 66 us there.
 constexpr int kDirectSlotsLg = 13;
@@ -1374,8 +1374,8 @@ pyst_status launch_direct_groups(pyst_ctx *ctx, GbPlan *plan, uint64_t *status, 
 // 16384 pairs (128 KiB of LDS, one block per CU) make runs of 16 pairs.
 // 60M pairs over 15M keys: count 34, move 258, sums 172 us, where two moves took
 // 40, 235 + 252 and 193; a cursor per block 304 and 198; tiles of 8192 pairs, two
-// blocks per CU, 276 and 194.  In all 890 -> 662 us; 20M over 9000 keys 379 ->
-// 262, 1.2M over 300K 136 -> 110, 30M over 16M 542 -> 432.
+// blocks per CU, 276 and 194.  The call, ordered by key: 840 -> 585 us; 20M over
+// 9000 keys 331 -> 211, 1.2M over 300K 123 -> 91, 30M over 16M 490 -> 350.
 constexpr int kOnceItems = 16, kOnceTile = kAggBlock * kOnceItems;
 constexpr int kOnceParts = 256;  // blocks: contiguous ranges of rows
 constexpr int kOnceShare = 32;   // neighbouring ranges (one XCD's) that fill places together
