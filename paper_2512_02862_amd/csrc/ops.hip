@@ -1244,11 +1244,15 @@ pyst_status group_init(const GroupDev &g, const int64_t *d_nsel, int64_t n, int6
 // Up to two blocks of 1024 threads per CU, a row a thread or more; few rows take
 // more blocks, up to half as many as CUs, down to 128 rows each: what a block's
 // groups cost is its CU's requests to the table, a few ns each (3000 different
-// keys: in 3 blocks 21 us, in 24 13.6; 30000: 24 in 30, 17 in 128).
+// keys: in 3 blocks 21 us, in 24 13.6; 30000: 24 in 30, 17 in 128).  Not where the
+// table's slots say that rows repeat: a block has fewer groups than rows then, and
+// the blocks meet in the table's lines (55000 rows, room for 95 groups: the call 36
+// us in 54 blocks, 45 in 128; 30000 for 376 29 in 30, 37 in 128).
 pyst_status group_insert(pyst_ctx *ctx, const GroupDev &g, const pyst_col *key, const pyst_col *val, const int32_t *sel,
                          const int64_t *d_nsel, int skip_empty, GbPlan *plan, int mode, hipStream_t stream) {
   if (key->n == 0) return PYST_OK;
-  const int64_t few = std::min<int64_t>(ceil_div(key->n, kPreUnit), std::max(1, ctx_num_cus(ctx) / 2));
+  const bool repeat = g.cap_alloc < key->n / 8;
+  const int64_t few = repeat ? 1 : std::min<int64_t>(ceil_div(key->n, kPreUnit), std::max(1, ctx_num_cus(ctx) / 2));
   const int blocks = static_cast<int>(std::max<int64_t>(grid_for(ctx, key->n, 1024, 2), few));
   k_gb_insert<<<blocks, 1024, 0, stream>>>(key->data, key->dtype == PYST_I64, val->data, val->dtype == PYST_I64, sel,
                                           d_nsel, key->n, g, ctx_err_word(ctx), skip_empty, plan, mode);
